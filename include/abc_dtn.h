@@ -116,11 +116,12 @@ typedef struct {
   int batch;          /* wavefunctions sharing grid, V and boundary (>= 1)  */
   int meanfield;      /* ABC_MF_NONE | ABC_MF_T0T3                          */
   double t0, t3;      /* mean-field coefficients                            */
-  int path;           /* ABC_PATH_AUTO: the one-pass sweep (all four stages
-                         in one launch per step) where it covers the
-                         parameters (for the first order only on rows of
-                         128 columns), else the two-stage fused kernels,
-                         else the staged path.  ABC_PATH_FUSED / ABC_PATH_ONEPASS
+  int path;           /* ABC_PATH_AUTO: of the one-pass sweep (all four
+                         stages in one launch per step) and the two-stage
+                         fused kernels (two launches per step) the one
+                         estimated faster for the box, order and dtype;
+                         where neither covers the parameters the staged
+                         path.  ABC_PATH_FUSED / ABC_PATH_ONEPASS
                          force those kernels (ABC_ENOTSUP when they do not
                          cover the parameters): R = 1, window 0, nx, ny >= 4,
                          nz >= 5; the one-pass sweep also one orbital, no
@@ -255,10 +256,11 @@ abc_status abc_adjoint(abc_ctx* ctx, const void* psi0, const void* V,
                        void* grad_psi0, double* grad_V, double* J_out,
                        void* stream);
 
-/* Tile-depth tuner for the fused path: times a few steps with each tile depth
- * (4, 8 or 16 z-planes per tile, as the box and order allow) on the given
- * buffers and keeps the fastest for later abc_step calls; *tz_out (may be
- * NULL) receives it (0 on the staged path, which has nothing to tune).  The
+/* Tile-depth tuner for the two-stage fused path: times a few steps with each
+ * limit on the tile depth (4, 8 or 16 z-planes per tile, as the box and order
+ * allow; the depth taken under a limit follows from the tile count) on the
+ * given buffers and keeps the fastest for later abc_step calls; *tz_out (may
+ * be NULL) receives the limit (0 on the staged path, which has nothing to tune).  The
  * state is restored afterwards; the call allocates temporary copies of psi
  * and aux and synchronises the stream. */
 abc_status abc_tune(abc_ctx* ctx, void* psi, void* aux, const void* V,
@@ -269,7 +271,7 @@ abc_status abc_tune(abc_ctx* ctx, void* psi, void* aux, const void* V,
  * Instances that run on the fused path are grouped by (order, precision);
  * every group is stepped by one descriptor-driven launch per half step over
  * the concatenated tiles of all its boxes, with one tile depth per group
- * (abc_tune_batch picks it by timing).  Other instances are stepped one by
+ * (abc_tune_batch picks its limit by timing).  Other instances are stepped one by
  * one with abc_step.  abc_step_batch advances instance i's psi[i] (and
  * aux[i], first and second order; V[i] may be NULL, V itself may be NULL for V = 0) by
  * n_steps on the stream; with ABC_BATCH_GRAPH in flags the whole call is
@@ -288,7 +290,7 @@ abc_status abc_tune_batch(abc_batch* b, void* const* psi, void* const* aux,
                           const void* const* V, void* stream);
 /* aux elements of instance i (as abc_aux_elems), 0 if out of range */
 size_t abc_batch_aux_elems(const abc_batch* b, int i);
-/* number of descriptor-driven launch groups, and the tile depth of one */
+/* number of descriptor-driven launch groups, and the tile-depth limit of one */
 int abc_batch_launch_groups(const abc_batch* b);
 int abc_batch_tile_depth(const abc_batch* b, int group);
 void abc_destroy_batch(abc_batch* b);

@@ -148,7 +148,8 @@ struct abc_launch {
   int fused_stages;            // 4: one launch per step; 2: two launches
   int fused_shell;             // one-pass sweep plus boundary-shell rounds (first order, window > 0)
   ShellScratch shell;
-  int fused_tz;                // planes per tile of the two-stage kernel (4, 8, 16)
+  int fused_tz;                // planes per tile of the two-stage kernel
+  int fused_limit;             // most planes per tile it may take (4, 8, 16; the tuner's choice)
   // box form
   const double2* box_mat;
   const double2* box_q;       // Lyapunov weight (H_gs H_gs^T)^{-1}, n x n
@@ -253,18 +254,18 @@ hipError_t launch_step_staged(const abc_launch& L, const abc_scratch& S, void* p
                               const void* V, int n_steps, hipStream_t st, abc_timer* tm = nullptr,
                               void* const* keep = nullptr, const void* psi_in = nullptr,
                               const double2* aux_in = nullptr);
-// One fused step out of place (psi_in, aux_in) -> (psi_out, aux_out) on the
-// two-stage kernels (L must satisfy fused_supported), keeping the Horner
-// intermediates u1, u2, u3 of the step in keep[0..2] (psi-sized).
-hipError_t launch_step_fused_keep(const abc_launch& L, const abc_scratch& S, const void* psi_in,
-                                  const double2* aux_in, void* psi_out, double2* aux_out, const void* V,
-                                  void* const* keep, hipStream_t st);
-// The same (complex128) keeping the increments u1 - z, u2 - z, u3 - z of the
-// intermediates over the step's input z in keep[0..2] (differences without
-// cancellation); uses S.y[1] for u2.
-hipError_t launch_step_fused_keepd(const abc_launch& L, const abc_scratch& S, const void* psi_in,
-                                   const double2* aux_in, void* psi_out, double2* aux_out, const void* V,
-                                   void* const* keep, hipStream_t st);
+// One step (complex128) out of place on the two-stage kernels (L must satisfy
+// fused_supported): psi_mid receives the state between the step's two factors,
+// keep[0..1] their stage-1 outputs.
+hipError_t launch_step_fused_keep(const abc_launch& L, const abc_scratch& S, const double2* psi_in,
+                                  const double2* aux_in, double2* psi_mid, double2* psi_out, double2* aux_out,
+                                  const double* V, double2* const* keep, hipStream_t st);
+// One adjoint step of (lam, mu) in place on the same kernels with the adjoint
+// operators La, adding the step's part of the gradient with respect to V to
+// gV; z, v, t as launch_step_fused_keep left them, dt the forward time step.
+hipError_t launch_step_fused_grad(const abc_launch& La, const abc_scratch& S, double2* lam, double2* mu,
+                                  const double2* z, const double2* v, double2* const* t, const double* V, double* gV,
+                                  double dt, hipStream_t st);
 // Discrete adjoint (adjoint.hip).  La is L with the adjoint operators
 // (dt -> -dt, conjugate-transposed boundary operators, rescaled aux).
 struct abc_adjoint_args {

@@ -428,7 +428,7 @@ abc_status abc_setup(const abc_params* pp, abc_ctx** out) {
       ob.S.assign(p.batch, abc_scratch{});
       const bool first = p.order == ABC_FIRST;
       const size_t np = (size_t)L.g.npts, nf = (size_t)ob.L1.g.face_off[6];
-      for (int i = 0; i < 3 && st == ABC_OK; ++i) {
+      for (int i = 0; i < 2 && st == ABC_OK; ++i) {
         st = dev_alloc(c, &ob.soa[i], (size_t)p.batch * np * csz);
         if (st == ABC_OK && first) {
           st = dev_alloc(c, &tmp, (size_t)p.batch * nf * 16);
@@ -943,18 +943,23 @@ abc_status abc_tune(abc_ctx* c, void* psi, void* aux, const void* V, void* strea
   if (c->aux_elems && !aux) return fail(ABC_EINVAL, "first and second order need the aux buffer");
   hipStream_t st = static_cast<hipStream_t>(stream);
   if (!c->use_fused || c->orb || c->L.fused_stages != 2) {
-    if (tz_out) *tz_out = c->use_fused ? c->L.fused_tz : 0;
+    if (tz_out) *tz_out = c->use_fused ? c->L.fused_limit : 0;
     return ABC_OK;
   }
   Saved sv;
   abc_status s = sv.save(psi, psi_bytes(c), st);
   if (s == ABC_OK) s = sv.save(aux, c->aux_elems * sizeof(double2), st);
   if (s != ABC_OK) return s;
-  int best = c->L.fused_tz;
+  const abc_params& p = c->p;
+  auto limit_to = [&](int tz) {
+    c->L.fused_limit = tz;
+    c->L.fused_tz = fused_pick_depth(p.order, tz, {{p.nx, p.ny, p.nz, 1}});
+  };
+  int best = c->L.fused_limit;
   float best_ms = 1e30f;
   for (int tz : {4, 8, 16}) {
-    if (!fused_tz_valid(c->L, tz)) continue;
-    c->L.fused_tz = tz;
+    if (tz > fused_max_limit(p.order, p.nz)) continue;
+    limit_to(tz);
     float ms = 0;
     s = time_steps([&](int n) { return launch_step_fused(c->L, c->S, psi, static_cast<double2*>(aux), V, n, st); },
                    st, &ms);
@@ -964,7 +969,7 @@ abc_status abc_tune(abc_ctx* c, void* psi, void* aux, const void* V, void* strea
       best = tz;
     }
   }
-  c->L.fused_tz = best;
+  limit_to(best);
   if (tz_out) *tz_out = best;
   return sv.restore(st);
 }
@@ -972,7 +977,7 @@ abc_status abc_tune(abc_ctx* c, void* psi, void* aux, const void* V, void* strea
 struct abc_batch {
   std::vector<abc_ctx*> inst;
   struct Group {
-    int order = 0, dtype = 0, tz = 8;
+    int order = 0, dtype = 0, limit = 16, tz = 8;  // limit on the tile depth, the depth
     std::vector<int> idx;
     void* host = nullptr;  // pinned descriptor staging
     void* dev = nullptr;   // descriptors of eager calls
@@ -1009,6 +1014,16 @@ void abc_destroy_batch(abc_batch* b) {
   }
   for (abc_ctx* c : b->inst) abc_destroy(c);
   delete b;
+}
+
+// the group's tile depth under a limit, the same for all its boxes (their
+// tiles share its launches)
+static void set_group_depth(abc_batch* b, abc_batch::Group& g, int limit) {
+  std::vector<FusedBox> boxes;
+  for (int i : g.idx) boxes.push_back({b->inst[i]->p.nx, b->inst[i]->p.ny, b->inst[i]->p.nz, 1});
+  g.limit = limit;
+  g.tz = fused_pick_depth(g.order, limit, boxes);
+  for (int i : g.idx) b->inst[i]->L.fused_tz = g.tz;
 }
 
 abc_status abc_setup_batch(const abc_params* ps, int n, abc_batch** out) {
@@ -1056,8 +1071,8 @@ abc_status abc_setup_batch(const abc_params* ps, int n, abc_batch** out) {
     return fail(ABC_EDEVICE, "batch stream or events");
   }
   for (auto& g : b->groups) {
-    for (int i : g.idx) g.tz = std::min(g.tz, fused_max_tz(g.order, b->inst[i]->p.nz));
-    for (int i : g.idx) b->inst[i]->L.fused_tz = g.tz;
+    for (int i : g.idx) g.limit = std::min(g.limit, fused_max_limit(g.order, b->inst[i]->p.nz));
+    set_group_depth(b, g, g.limit);
     const size_t bytes = fused_batch_desc_bytes((int)g.idx.size());
     if (hipHostMalloc(&g.host, bytes) != hipSuccess || hipMalloc(&g.dev, bytes) != hipSuccess ||
         hipMalloc(&g.gdev, bytes) != hipSuccess || hipEventCreate(&g.copied) != hipSuccess) {
@@ -1078,7 +1093,7 @@ int abc_batch_launch_groups(const abc_batch* b) { return b ? (int)b->groups.size
 
 int abc_batch_tile_depth(const abc_batch* b, int group) {
   if (!b || group < 0 || group >= (int)b->groups.size()) return 0;
-  return b->groups[group].tz;
+  return b->groups[group].limit;
 }
 
 namespace {
@@ -1141,7 +1156,7 @@ abc_status abc_step_batch(abc_batch* b, void* const* psi, void* const* aux, cons
       auto& g = b->groups[k];
       // the staging buffer is reused once its previous copy has completed
       if (g.pending && hipEventSynchronize(g.copied) != hipSuccess) return fail(ABC_EDEVICE, "event wait failed");
-      totals[k] = fused_batch_build(members(b, g, psi, aux, V), g.host, n_steps);
+      totals[k] = fused_batch_build(members(b, g, psi, aux, V), g.host);
       if (hipMemcpyAsync(g.dev, g.host, fused_batch_desc_bytes((int)g.idx.size()), hipMemcpyHostToDevice, st) !=
               hipSuccess ||
           hipEventRecord(g.copied, st) != hipSuccess)
@@ -1166,7 +1181,7 @@ abc_status abc_step_batch(abc_batch* b, void* const* psi, void* const* aux, cons
       auto& g = b->groups[k];
       if (g.pending && hipEventSynchronize(g.copied) != hipSuccess) return fail(ABC_EDEVICE, "event wait failed");
       g.pending = false;
-      totals[k] = fused_batch_build(members(b, g, psi, aux, V), g.host, n_steps);
+      totals[k] = fused_batch_build(members(b, g, psi, aux, V), g.host);
       if (hipMemcpy(g.gdev, g.host, fused_batch_desc_bytes((int)g.idx.size()), hipMemcpyHostToDevice) != hipSuccess)
         return fail(ABC_EDEVICE, "descriptor upload failed");
     }
@@ -1203,43 +1218,44 @@ abc_status abc_tune_batch(abc_batch* b, void* const* psi, void* const* aux, cons
     if (s == ABC_OK && aux) s = sv.save(aux[i], b->inst[i]->aux_elems * sizeof(double2), st);
     if (s != ABC_OK) return s;
   }
-  // On every exit, each instance's tile depth is its group's (the depth the
-  // group's kernels are instantiated at) and the callers' states are back.
+  // On every exit the callers' states are back (each instance's tile depth is
+  // its group's throughout: the depth the group's kernels are instantiated at)
   auto finish = [&](abc_status r) {
-    for (auto& g : b->groups)
-      for (int i : g.idx) b->inst[i]->L.fused_tz = g.tz;
     const abc_status rr = sv.restore(st);
     return r != ABC_OK ? r : rr;
   };
   for (auto& g : b->groups) {
-    int max_tz = 16;
-    for (int i : g.idx) max_tz = std::min(max_tz, fused_max_tz(g.order, b->inst[i]->p.nz));
+    int top = 16;
+    for (int i : g.idx) top = std::min(top, fused_max_limit(g.order, b->inst[i]->p.nz));
     const auto m = members(b, g, psi, aux, V);
-    int best = g.tz;
+    int best = g.limit;
     float best_ms = 1e30f;
     for (int tz : {4, 8, 16}) {
-      if (tz > max_tz) continue;
-      for (int i : g.idx) b->inst[i]->L.fused_tz = tz;
+      if (tz > top) continue;
+      set_group_depth(b, g, tz);
       float ms = 0;
       s = time_steps(
           [&](int n) {
             if (g.pending && hipEventSynchronize(g.copied) != hipSuccess) return hipErrorUnknown;
-            const int total = fused_batch_build(m, g.host, n);
+            const int total = fused_batch_build(m, g.host);
             hipError_t e = hipMemcpyAsync(g.dev, g.host, fused_batch_desc_bytes((int)g.idx.size()),
                                           hipMemcpyHostToDevice, st);
             if (e == hipSuccess) e = hipEventRecord(g.copied, st);
             g.pending = true;
-            if (e == hipSuccess) e = launch_batch_fused(m, tz, g.dev, total, n, st, nullptr);
+            if (e == hipSuccess) e = launch_batch_fused(m, g.tz, g.dev, total, n, st, nullptr);
             return e;
           },
           st, &ms);
-      if (s != ABC_OK) return finish(s);
+      if (s != ABC_OK) {
+        set_group_depth(b, g, best);
+        return finish(s);
+      }
       if (ms < best_ms) {
         best_ms = ms;
         best = tz;
       }
     }
-    g.tz = best;
+    set_group_depth(b, g, best);
   }
   // a cached graph was captured with the old depths
   if (b->exec) hipGraphExecDestroy(b->exec);

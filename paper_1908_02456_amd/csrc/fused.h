@@ -22,16 +22,20 @@ abc_status fused_prepare(const abc_params& p, abc_launch& L, std::vector<void*>*
 hipError_t launch_step_fused(const abc_launch& L, const abc_scratch& S, void* psi, double2* aux, const void* V,
                              int n_steps, hipStream_t st, abc_timer* tm = nullptr);
 
-// largest tile depth (planes) the two-stage kernel can use for this order/box
-int fused_max_tz(int order, int nz);
-bool fused_tz_valid(const abc_launch& L, int tz);
+// Tile depth (planes) of the two-stage kernels for boxes launched together
+// (`count` of each), at most `limit`; limits are 4, 8 or 16, the largest one
+// an order allows in a box of nz planes being fused_max_limit.
+struct FusedBox {
+  int nx, ny, nz, count;
+};
+int fused_max_limit(int order, int nz);
+int fused_pick_depth(int order, int limit, const std::vector<FusedBox>& boxes);
 
 // Batched two-stage launch over boxes sharing (order, precision, tile depth).
-// fused_batch_build writes 4 descriptor sets (step parity x half) for an
-// n-step call into `host` (fused_batch_desc_bytes(nbox) bytes) and returns the
-// total tile count; once they are in device memory at `dev`,
-// launch_batch_fused runs the n steps as 2 launches per step over the
-// concatenated tiles of all boxes.
+// fused_batch_build writes 2 descriptor sets (one per launch of a step) into
+// `host` (fused_batch_desc_bytes(nbox) bytes) and returns the total tile
+// count; once they are in device memory at `dev`, launch_batch_fused runs n
+// steps as 2 launches per step over the concatenated tiles of all boxes.
 struct FusedMember {
   const abc_launch* L;
   const abc_scratch* S;
@@ -40,7 +44,7 @@ struct FusedMember {
   const void* V;
 };
 size_t fused_batch_desc_bytes(int nbox);
-int fused_batch_build(const std::vector<FusedMember>& m, void* host, int n);
+int fused_batch_build(const std::vector<FusedMember>& m, void* host);
 hipError_t launch_batch_fused(const std::vector<FusedMember>& m, int tz, const void* dev, int total, int n,
                               hipStream_t st, abc_timer* tm);
 
@@ -53,8 +57,8 @@ struct OrbitalBatch {
   abc_launch L1;                   // the launch of one orbital (batch 1 geometry)
   int B = 0;                       // orbitals
   int tz = 8;
-  void* soa[3] = {nullptr, nullptr, nullptr};  // psi arrays [B][npts]: state A, state B, u2
-  double2* soa_f[3] = {nullptr, nullptr, nullptr};  // aux arrays [B][nface]: A, B, aux of u2
+  void* soa[2] = {nullptr, nullptr};     // psi arrays [B][npts]: the state, and its other buffer
+  double2* soa_f[2] = {nullptr, nullptr};  // aux arrays [B][nface], the same
   void* veff = nullptr;            // V + mean field (psi's real type), or null
   // descriptors of the two-stage launches, one set per step-count parity,
   // built on first use for a given potential buffer and reused after that
@@ -68,6 +72,5 @@ struct OrbitalBatch {
   bool pending = false;
   std::vector<abc_scratch> S;      // per-orbital scratch views into soa / soa_f
 };
-size_t orbital_batch_bytes(const abc_launch& L1, int B, bool first, bool meanfield);
 hipError_t launch_step_orbitals(OrbitalBatch& ob, void* psi, double2* aux, const void* V, int n_steps,
                                 hipStream_t st, abc_timer* tm);

@@ -1,10 +1,12 @@
 // Fused Taylor-4 step kernels (Sec. 4 Taylor propagator applied to the
 // dynamics of Sec. 3), for R = 1 and local (window 0) face operators.
 //
-// The step U = sum_{k<=4} (dt L)^k / k! is evaluated in Horner form, the same
-// polynomial with a different rounding order:
-//   u3 = z0 + (dt/4) L z0,  u2 = z0 + (dt/3) L u3,  u1 = z0 + (dt/2) L u2,
-//   z' = z0 + dt L u1,       z0 = (psi, f).
+// The step U = sum_{k<=4} (dt L)^k / k! is evaluated as the product of its two
+// real quadratic factors, the same polynomial with a different rounding order:
+//   t = a1 z + b1 dt L z,  v  = z + dt L t,       z = (psi, f),
+//   s = a2 v + b2 dt L v,  z' = v + dt L s.
+// Each factor reads nothing but its own input, so a launch of two stages
+// moves 2 c + r bytes per point, and two launches need no second state buffer.
 //
 // Sweep layout:
 //   * a workgroup owns an output tile of one x chunk (the whole row up to 128
@@ -15,8 +17,8 @@
 //     each end (conflict-free, branch-free x neighbours);
 //   * the workgroup marches z: when plane zi is loaded, stage k works on plane
 //     zi - k with its input's below/centre planes in registers, the plane above
-//     being the previous stage's fresh output; the initial state needed by the
-//     Horner stages rides along in a register delay line;
+//     being the previous stage's fresh output; a factor's input at the plane
+//     of its second stage is the oldest plane of the first stage's queue;
 //   * tiles are numbered so that consecutive tiles share an XCD and its L2.
 // fused2_kernel runs two of the four stages per launch (two launches per step,
 // two-deep halos) and also carries the zeroth- and first-order conditions.
@@ -25,16 +27,19 @@
 // through small LDS rings; on the z-face plane by the row waves from
 // registers.  The face sources enter the stage outputs of the face points
 // (whole rows on y and z faces, one column at each end of a row on x faces).
-// The state is read from one buffer and written to another, since
-// neighbouring tiles read halos that a tile overwrites.
+// A launch reads one buffer and writes another, since neighbouring tiles read
+// halos that a tile overwrites.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstdlib>
 #include <type_traits>
 #include <utility>
 
 #include "fused.h"
+
+using abc::Geometry;
 
 namespace {
 
@@ -151,43 +156,69 @@ __device__ __forceinline__ C dpp_shift_edge_c(C v, bool right, T ex, T ey) {
   return o;
 }
 
-// Half of the Horner step per launch:
-//   half A:  u3 = psi + (dt/4) L psi,  u2 = psi + (dt/3) L u3   -> u2
-//   half B:  u1 = psi + (dt/2) L u2,   psi' = psi + dt L u1      -> psi'
-// w is the field the first stage differentiates (psi in A, u2 in B), base the
-// Horner base psi (the same buffer in A).  Tiles are TY = 8 rows by TZ
-// planes (TZ in {4, 8, 16}, chosen by the tuner) by one x chunk: the whole
+// One quadratic factor of the step per launch, y = (1 + sA X + b X^2) in with
+// X = dt L:
+//   stage 1:  t = sA in + cA L in   (cA = b dt),
+//   stage 2:  out = in + cB L t     (cB = dt).
+// Tiles are TY = 8 rows by TZ planes (pick_depth) by one x chunk: the whole
 // row when nx <= 128, else chunks of at most 124 output columns loaded with
 // a two-column halo on each side (the chunk edges see zero neighbours, which
 // only corrupts the halo columns, never an output).  12 waves.
+//
+// Horner form reads the step's initial state again in its second launch
+// (3 c + r bytes per point there) and needs a third state buffer: 256^3
+// without a condition, 186 + 255 us per step at 8 planes against 2 x 181.
 constexpr int kTY2 = 8, kHalo2 = 2, kChunk = kCols - 2 * kHalo2;
+// tile depth: a launch of `tiles` tiles takes ceil(tiles / kTileSlots) rounds
+// of TZ + 2 kHalo2 planes each, and a tile's start (LDS cleared, face data and
+// first planes fetched) costs about kTileStart planes.  The depth of least
+// cost is within 4 % of the fastest measured one from 31^3 to 256^3 (first
+// order c128, us per step: 31^3 16.9 with 2 planes, 33.5 with 8; 96^3 31.8 with
+// 5, 40.2 with 8, 45.9 with 4; 128^3 45.0 with 8, 66 with 16; 160^3 122 with 16,
+// 131 with 8)
+constexpr int kTileSlots = 256, kTileStart = 2;
 
 // one box of a (possibly batched) two-stage launch
 struct Box2 {
   FusedArgs a;
-  const void* w;
-  const void* base;
+  const void* in;
   void* out;
   const void* V;
   const double2* av;
-  const double2* fb;
   double2* aux_out;
   int tile_begin;  // first global tile of this box in the launch
   int pad;
 };
 
-// KEEPD (the adjoint's Horner steps): keep1 receives the stage-1 increment
-// (output minus base) instead of the output, and keep2 the stage-2 increment,
-// so that differences of the intermediates carry no cancellation.
-template <typename T, int ORDER, bool SAME_BASE, int TZ, int PF, bool KEEPD = false>
+// What a launch does beside the factor (the adjoint's needs): kKeep writes
+// the stage-1 output t of its own points to `keep`; kGrad accumulates the
+// gradient with respect to V (Grad2).
+enum { kPlain = 0, kKeep = 1, kGrad = 2 };
+
+// Gradient with respect to V of one factor, F = 1 + a X + b X^2 with X = dt L
+// and dL/dV = -i: for the adjoint state l at the factor's output side, the
+// forward factor's input y and stage-1 output t = a y + b X y, and the
+// adjoint factor's own stage-1 output tau = a l + b X^H l,
+//   gV += dt (Im(conj(l) t) + Im(conj(tau - a l) y)).
+// The adjoint launch holds l and tau of its own points when it writes its
+// output, so the gradient costs the reads of t and y and the update of gV
+// instead of three kept adjoint stages and a pass of its own (first order,
+// 96^3 x 48 steps with sqrt checkpoints: 8.6 to 5.9 ms with the depth rule).
+template <typename C>
+struct Grad2 {
+  const C* t;
+  const C* y;
+  double* gV;
+  double dt;
+};
+
+template <typename T, int ORDER, int TZ, int MODE>
 __device__ __forceinline__ void fused2_body(const typename cpx<T>::t* __restrict__ w_in,
-                                            const typename cpx<T>::t* __restrict__ base_in,
                                             typename cpx<T>::t* __restrict__ out, const T* __restrict__ V,
-                                            const FusedArgs& a, double cA, double cB,
-                                            const double2* __restrict__ av, const double2* __restrict__ fb,
-                                            double2* __restrict__ aux_out, int tile,
-                                            typename cpx<T>::t* __restrict__ keep1 = nullptr,
-                                            typename cpx<T>::t* __restrict__ keep2 = nullptr) {
+                                            const FusedArgs& a, double sA, double cA, double cB,
+                                            const double2* __restrict__ av, double2* __restrict__ aux_out, int tile,
+                                            typename cpx<T>::t* __restrict__ keep,
+                                            const Grad2<typename cpx<T>::t>& gr) {
   using C = typename cpx<T>::t;
   constexpr int TY = kTY2, H = kHalo2;
   constexpr int ROWS = TY + 2 * H;
@@ -196,16 +227,14 @@ __device__ __forceinline__ void fused2_body(const typename cpx<T>::t* __restrict
   constexpr bool FO = ORDER == 3;
   constexpr int FP = TZ + 2, FR = ROWS - 2;
   // first-order face data in LDS (sizes in double2; 1 = unused)
-  constexpr int NXG = FO ? 2 * FP * FR : 1, NXF = FO ? 2 * TZ * TY : 1;
-  constexpr int NYG = FO ? FP * kCols : 1, NYF = FO && !SAME_BASE ? TZ * kCols : 1;
-  constexpr int NZF = FO && !SAME_BASE ? TY * kCols : 1;
+  constexpr int NXG = FO ? 2 * FP * FR : 1, NYG = FO ? FP * kCols : 1;
   constexpr int NVX = FO ? 2 * TY * 2 : 1, NVY = FO ? 2 * kCols : 1;
   // Rows published for the y/x neighbours: the stage-1 inputs w of every row
   // and the stage-1 outputs s1 of rows 1 .. ROWS-2 (the only rows stage 2
   // reads).  Double-buffered (one barrier per plane) when both buffers fit in
   // the 160 KiB of LDS beside the face data.
   constexpr int kPlaneBytes = (2 * ROWS - 2) * 2 * 66 * (int)sizeof(C);
-  constexpr int kFaceBytes = 16 * (NXG + NXF + NYG + NYF + NZF + NVX + NVY);
+  constexpr int kFaceBytes = 16 * (NXG + NYG + NVX + NVY);
   constexpr int DBN = 2 * kPlaneBytes + kFaceBytes <= 160 * 1024 ? 2 : 1;
   __shared__ C plw[DBN][ROWS][2][66];
   __shared__ C pls[DBN][ROWS - 2][2][66];
@@ -229,63 +258,54 @@ __device__ __forceinline__ void fused2_body(const typename cpx<T>::t* __restrict
   for (int i = threadIdx.x; i < DBN * (ROWS - 2) * 2 * 66; i += NT) (&pls[0][0][0][0])[i] = czero<C>();
 
   C Yc[2][2], Yb[2][2];  // stage inputs: centre / below (j = 0: w, j = 1: stage-1 output)
-  C Bd[2][2];            // base at planes zi-1, zi-2 (separate base only)
   T Vd[2][2];            // V at planes zi-1, zi-2
-  C pf[PF][2], pb[PF][2];  // fields of the next PF planes (ring indexed by plane)
-  T pv[PF][2];
+  C pf[2];               // the next plane's fields
+  T pv[2];
 #pragma unroll
   for (int c = 0; c < 2; ++c) {
 #pragma unroll
     for (int j = 0; j < 2; ++j) {
-      Yc[j][c] = Yb[j][c] = Bd[j][c] = czero<C>();
+      Yc[j][c] = Yb[j][c] = czero<C>();
       Vd[j][c] = T(0);
     }
-#pragma unroll
-    for (int q = 0; q < PF; ++q) pb[q][c] = czero<C>();
   }
   const T diag = T(a.diag), off = T(a.off);
   const unsigned cbytes = (unsigned)(nz * sz) * (unsigned)sizeof(C);
-  const __amdgpu_buffer_rsrc_t rw = make_rsrc(w_in, cbytes), rbase = make_rsrc(base_in, cbytes);
+  const __amdgpu_buffer_rsrc_t rw = make_rsrc(w_in, cbytes);
   const __amdgpu_buffer_rsrc_t rv = make_rsrc(V, a.has_V ? (unsigned)(nz * sz) * (unsigned)sizeof(T) : 0u);
 
-  // plane zz into ring slot q; cells outside the box read as zero
-  auto fetch = [&](int zz, int q) {
+  // plane zz; cells outside the box read as zero
+  auto fetch = [&](int zz) {
     const bool ok = row_in && zz >= 0 && zz < nz;
 #pragma unroll
     for (int c = 0; c < 2; ++c) {
       const int x = xb + 2 * lane + c;
       const bool in = ok && x >= 0 && x < nx;
       const unsigned idx = in ? (unsigned)(zz * sz + ybase + x) : 0u;
-      bload(rw, in ? idx * (unsigned)sizeof(C) : kOob, pf[q][c]);
-      if (!SAME_BASE) bload(rbase, in ? idx * (unsigned)sizeof(C) : kOob, pb[q][c]);
-      bload(rv, in ? idx * (unsigned)sizeof(T) : kOob, pv[q][c]);
+      bload(rw, in ? idx * (unsigned)sizeof(C) : kOob, pf[c]);
+      bload(rv, in ? idx * (unsigned)sizeof(T) : kOob, pv[c]);
     }
   };
-#pragma unroll
-  for (int q = 0; q < PF; ++q) fetch(z0 - H + q, q);
+  fetch(z0 - H);
+  const T s1 = T(sA);
 
   // First order: the tile's face data, read once before the sweep.
   //  * x faces (both sides), in LDS: the auxiliary input g = av over the
-  //    stage-1 planes z0-1 .. z0+TZ and rows 1 .. ROWS-2, and the base
-  //    f0 = fb over the own planes and rows (the halo waves form v and the
-  //    outputs).
+  //    stage-1 planes z0-1 .. z0+TZ and rows 1 .. ROWS-2 (the halo waves form
+  //    v and the outputs).
   //  * the tile's z-face plane, if it has one (at most one when
   //    nz >= TZ + 2): each row wave holds g of its own row there in
-  //    registers; f0 over the own rows is staged in LDS when the base is a
-  //    separate buffer (half B) and is g itself otherwise.
+  //    registers.
   //  * the tile's y-face row, if it has one (at most one when
-  //    ny >= TY + 2), in LDS: g over the stage-1 planes and, with a separate
-  //    base, f0 over the own planes.  The halo waves form its stage-2 source
-  //    and auxiliary outputs during the sweep, as for the x faces.
-  // The stage-2 source is v = f0 + cA (b g + a w) and the auxiliary output
-  // f0 + cB (b v + a s1).  Every thread issues all of its loads before using
+  //    ny >= TY + 2), in LDS: g over the stage-1 planes.  The halo waves form
+  //    its stage-2 source and auxiliary outputs during the sweep, as for the
+  //    x faces.
+  // The stage-2 source is v = sA g + cA (b g + a w) and the auxiliary output
+  // g + cB (b v + a t).  Every thread issues all of its loads before using
   // any, so the staging costs one memory round trip, overlapped with the
   // first plane fetch.
   __shared__ double2 fxg[NXG];  // [side][plane][row]
-  __shared__ double2 fxf[NXF];  // [side][own plane][own row]
   __shared__ double2 fyg[NYG];  // [plane][local column]
-  __shared__ double2 fyf[NYF];  // [own plane][local column]
-  __shared__ double2 fzf[NZF];  // [own row][local column]
   // z face: g of this wave's row at the face plane, per column
   double2 gz[2] = {make_double2(0, 0), make_double2(0, 0)};
   // auxiliary stages v of the next two planes: x faces [plane & 1][own row]
@@ -305,10 +325,8 @@ __device__ __forceinline__ void fused2_body(const typename cpx<T>::t* __restrict
     else if (zlo <= nz - 1 && nz - 1 < zlo + FP) zface = 5;
     off_y = yface == 3 ? a.face_off[3] : a.face_off[2];
     off_z = zface == 5 ? a.face_off[5] : a.face_off[4];
-    constexpr int NXA = NXG + NXF;
-    constexpr int KX = (NXA + NT - 1) / NT, KYG = (NYG + NT - 1) / NT, KYF = (NYF + NT - 1) / NT;
-    constexpr int KZF = (NZF + NT - 1) / NT;
-    double2 rx[KX], ryg[KYG], ryf[KYF], rzf[KZF];
+    constexpr int KX = (NXG + NT - 1) / NT, KYG = (NYG + NT - 1) / NT;
+    double2 rx[KX], ryg[KYG];
     if (zface >= 0 && row_in && r >= 1 && r < ROWS - 1) {
 #pragma unroll
       for (int c = 0; c < 2; ++c) {
@@ -324,11 +342,6 @@ __device__ __forceinline__ void fused2_body(const typename cpx<T>::t* __restrict
         const int rr = i % FR, pl = (i / FR) % FP, side = i / (FR * FP);
         const int yy = ylo + rr, zz = zlo + pl;
         if (yy >= 0 && yy < ny && zz >= 0 && zz < nz) rx[j] = av[(side ? off_x1 : off_x0) + zz * ny + yy];
-      } else if (i < NXA) {
-        const int e = i - NXG;
-        const int jj = e % TY, pl = (e / TY) % TZ, side = e / (TY * TZ);
-        const int yy = y0 + jj, zz = z0 + pl;
-        if (yy < ny && zz < nz) rx[j] = fb[(side ? off_x1 : off_x0) + zz * ny + yy];
       }
     }
 #pragma unroll
@@ -340,43 +353,14 @@ __device__ __forceinline__ void fused2_body(const typename cpx<T>::t* __restrict
       if (yface >= 0 && i < NYG && xx >= 0 && xx < nx && zz >= 0 && zz < nz) ryg[j] = av[off_y + zz * nx + xx];
     }
 #pragma unroll
-    for (int j = 0; j < KYF; ++j) {
-      const int i = threadIdx.x + j * NT;
-      const int lx = i % kCols, pl = i / kCols;
-      const int xx = xb + lx, zz = z0 + pl;
-      ryf[j] = make_double2(0, 0);
-      if (!SAME_BASE && yface >= 0 && i < NYF && xx >= 0 && xx < nx && zz < nz) ryf[j] = fb[off_y + zz * nx + xx];
-    }
-#pragma unroll
-    for (int j = 0; j < KZF; ++j) {
-      const int i = threadIdx.x + j * NT;
-      const int lx = i % kCols, jj = i / kCols;
-      const int xx = xb + lx, yy = y0 + jj;
-      rzf[j] = make_double2(0, 0);
-      if (!SAME_BASE && zface >= 0 && i < NZF && xx >= 0 && xx < nx && yy < ny) rzf[j] = fb[off_z + yy * nx + xx];
-    }
-#pragma unroll
     for (int j = 0; j < KX; ++j) {
       const int i = threadIdx.x + j * NT;
       if (i < NXG) fxg[i] = rx[j];
-      else if (i < NXA) fxf[i - NXG] = rx[j];
     }
 #pragma unroll
     for (int j = 0; j < KYG; ++j) {
       const int i = threadIdx.x + j * NT;
       if (i < NYG) fyg[i] = ryg[j];
-    }
-    if constexpr (!SAME_BASE) {
-#pragma unroll
-      for (int j = 0; j < KYF; ++j) {
-        const int i = threadIdx.x + j * NT;
-        if (i < NYF) fyf[i] = ryf[j];
-      }
-#pragma unroll
-      for (int j = 0; j < KZF; ++j) {
-        const int i = threadIdx.x + j * NT;
-        if (i < NZF) fzf[i] = rzf[j];
-      }
     }
   }
   __syncthreads();
@@ -399,16 +383,34 @@ __device__ __forceinline__ void fused2_body(const typename cpx<T>::t* __restrict
     auto& psn = pls[DBN == 2 ? ((it + 1) & 1) : 0];
     C prev[2];
     T vcur[2];
-    C bcur[2], wm2[2];  // base at plane zi; w at plane zi - 2 (before the slide)
-    const int q = it % PF;  // ring slot of plane zi (the loop is unrolled)
+    C wm2[2], tau[2];  // the input and the stage-1 output at plane zi - 2 (before the slide)
 #pragma unroll
     for (int c = 0; c < 2; ++c) {
-      prev[c] = pf[q][c];
-      vcur[c] = pv[q][c];
-      bcur[c] = SAME_BASE ? pf[q][c] : pb[q][c];
+      prev[c] = pf[c];
+      vcur[c] = pv[c];
       wm2[c] = Yb[0][c];
+      tau[c] = Yc[1][c];
     }
-    if (it + PF < ITERS) fetch(zi + PF, q);
+    if (it + 1 < ITERS) fetch(zi + 1);
+    const int z2 = zi - 2;
+    const bool own_out = own_row && it >= 2 * H && z2 < nz;
+    // the gradient's operands at this iteration's output plane
+    C gt[2], gy[2];
+    double g0[2];
+    if constexpr (MODE == kGrad) {
+#pragma unroll
+      for (int c = 0; c < 2; ++c) {
+        const int x = xb + 2 * lane + c;
+        gt[c] = gy[c] = czero<C>();
+        g0[c] = 0;
+        if (own_out && x >= xo && x < xe) {
+          const int idx = z2 * sz + ybase + x;
+          gt[c] = gr.t[idx];
+          gy[c] = gr.y[idx];
+          g0[c] = gr.gV[idx];
+        }
+      }
+    }
     // The halo waves' face work below runs after their prefetch is issued,
     // so that its latency overlaps the work.
     if (ORDER == 3 && (r == 0 || r == ROWS - 1) && lane < 2 * TY) {
@@ -416,9 +418,9 @@ __device__ __forceinline__ void fused2_body(const typename cpx<T>::t* __restrict
       // (idle in both stages), one lane per (own row, side).  They read the
       // rows published at the end of the previous iteration: pw holds w at
       // plane zi-1 and ps the stage-1 output s1 at plane zi-2.
-      //  * top wave: v_f = fb_f + cA (b av_f + a w) at plane zi-1, for the
+      //  * top wave: v_f = sA g_f + cA (b g_f + a w) at plane zi-1, for the
       //    next iteration's stage 2 (LDS ring);
-      //  * bottom wave: the auxiliary output fb_f + cB (b v_f + a s1) at
+      //  * bottom wave: the auxiliary output g_f + cB (b v_f + a t) at
       //    plane zi-2 (v_f from the ring, written an iteration earlier).
       const int j = lane >> 1, side = lane & 1;
       const int rj = H + j, yj = y0 + j;
@@ -429,17 +431,16 @@ __device__ __forceinline__ void fused2_body(const typename cpx<T>::t* __restrict
         if (r == 0 && p1 >= z0 && p1 < z0 + TZ && p1 < nz) {
           const int pl = p1 - (z0 - 1);
           const double2 g = fxg[(side * FP + pl) * FR + rr];
-          const double2 f0 = fxf[(side * TZ + (p1 - z0)) * TY + j];
           const C wv = pw[rj][ci][li];
           const double2 bg = cmul(a.b0, g), aw = cmul(a.a0, make_double2((double)wv.x, (double)wv.y));
-          const double2 v = make_double2(f0.x + cA * (bg.x + aw.x), f0.y + cA * (bg.y + aw.y));
+          const double2 v = make_double2(sA * g.x + cA * (bg.x + aw.x), sA * g.y + cA * (bg.y + aw.y));
           vx[((p1 & 1) * TY + j) * 2 + side] = v;
         }
         if (r == ROWS - 1 && p2 >= z0 && p2 < z0 + TZ && p2 < nz && xf >= xo && xf < xe) {
-          const double2 f0 = fxf[(side * TZ + (p2 - z0)) * TY + j];
+          const double2 f0 = fxg[(side * FP + p2 - (z0 - 1)) * FR + rr];
           const double2 v = vx[((p2 & 1) * TY + j) * 2 + side];
-          const C s1 = ps[rj - 1][ci][li];
-          const double2 bv = cmul(a.b0, v), as1 = cmul(a.a0, make_double2((double)s1.x, (double)s1.y));
+          const C t1 = ps[rj - 1][ci][li];
+          const double2 bv = cmul(a.b0, v), as1 = cmul(a.a0, make_double2((double)t1.x, (double)t1.y));
           aux_out[(side ? off_x1 : off_x0) + p2 * ny + yj] =
               make_double2(f0.x + cB * (bv.x + as1.x), f0.y + cB * (bv.y + as1.y));
         }
@@ -447,8 +448,8 @@ __device__ __forceinline__ void fused2_body(const typename cpx<T>::t* __restrict
     }
     if (ORDER == 3 && ryown >= 0 && (r == 0 || r == ROWS - 1)) {
       // The y-face row, by the same two halo waves over its whole width: the
-      // top wave forms v = f0 + cA (b g + a w) at plane zi-1 into the ring;
-      // the bottom wave writes the auxiliary output f0 + cB (b v + a s1) at
+      // top wave forms v = sA g + cA (b g + a w) at plane zi-1 into the ring;
+      // the bottom wave writes the auxiliary output g + cB (b v + a t) at
       // plane zi-2.
       const int p = r == 0 ? zi - 1 : zi - 2;
       if (p >= z0 && p < z0 + TZ && p < nz) {
@@ -457,16 +458,15 @@ __device__ __forceinline__ void fused2_body(const typename cpx<T>::t* __restrict
           const int lx = 2 * lane + c, x = xb + lx;
           if (x < 0 || x >= nx) continue;
           const double2 g = fyg[(p - z0 + 1) * kCols + lx];
-          const double2 f0 = SAME_BASE ? g : fyf[(p - z0) * kCols + lx];
           if (r == 0) {
             const C wv = pw[ryown][c][lane + 1];
             const double2 bg = cmul(a.b0, g), aw = cmul(a.a0, make_double2((double)wv.x, (double)wv.y));
-            vy[(p & 1) * kCols + lx] = make_double2(f0.x + cA * (bg.x + aw.x), f0.y + cA * (bg.y + aw.y));
+            vy[(p & 1) * kCols + lx] = make_double2(sA * g.x + cA * (bg.x + aw.x), sA * g.y + cA * (bg.y + aw.y));
           } else if (x >= xo && x < xe) {
             const double2 v = vy[(p & 1) * kCols + lx];
-            const C s1 = ps[ryown - 1][c][lane + 1];
-            const double2 bv = cmul(a.b0, v), as1 = cmul(a.a0, make_double2((double)s1.x, (double)s1.y));
-            aux_out[off_y + p * nx + x] = make_double2(f0.x + cB * (bv.x + as1.x), f0.y + cB * (bv.y + as1.y));
+            const C t1 = ps[ryown - 1][c][lane + 1];
+            const double2 bv = cmul(a.b0, v), as1 = cmul(a.a0, make_double2((double)t1.x, (double)t1.y));
+            aux_out[off_y + p * nx + x] = make_double2(g.x + cB * (bv.x + as1.x), g.y + cB * (bv.y + as1.y));
           }
         }
       }
@@ -497,8 +497,6 @@ __device__ __forceinline__ void fused2_body(const typename cpx<T>::t* __restrict
       const T cf = T(k == 1 ? cA : cB);
       const bool active = r >= k && r < ROWS - k && it >= 2 * k && row_in && zk >= 0 && zk < nz;
       C o[2];
-      C dk[2];  // the stage's increment (KEEPD only)
-      if constexpr (KEEPD) dk[0] = dk[1] = czero<C>();
 #pragma unroll
       for (int c = 0; c < 2; ++c) {
         const int lx = 2 * lane + c, x = xb + lx;
@@ -506,15 +504,18 @@ __device__ __forceinline__ void fused2_body(const typename cpx<T>::t* __restrict
         o[c] = czero<C>();
         if (!active) continue;
         const C cen = Yc[k - 1][c], bel = Yb[k - 1][c], abv = prev[c];
-        // stage k reads rows r-1 .. r+1 of w (k = 1) or of s1 (k = 2)
+        // stage k reads rows r-1 .. r+1 of the input (k = 1) or of t (k = 2)
         auto row = [&](int rr) -> C(&)[2][66] { return k == 1 ? pw[rr] : ps[rr - 1]; };
         const C ym = row(r - 1)[c][lane + 1];
         const C yp = row(r + 1)[c][lane + 1];
         const C xm = c == 0 ? row(r)[1][lane] : Yc[k - 1][0];
         const C xp = c == 0 ? Yc[k - 1][1] : row(r)[0][lane + 2];
-        C b0;
-        if (SAME_BASE) b0 = k == 1 ? Yc[0][c] : wm2[c];
-        else b0 = Bd[k - 1][c];
+        // base: the factor's input, scaled in stage 1
+        C b0 = wm2[c];
+        if (k == 1) {
+          b0.x = s1 * cen.x;
+          b0.y = s1 * cen.y;
+        }
         const T v = Vd[k - 1][c];
         T hr = diag * cen.x + off * (bel.x + abv.x + ym.x + yp.x + xm.x + xp.x) + v * cen.x;
         T hi = diag * cen.y + off * (bel.y + abv.y + ym.y + yp.y + xm.y + xp.y) + v * cen.y;
@@ -530,15 +531,11 @@ __device__ __forceinline__ void fused2_body(const typename cpx<T>::t* __restrict
         // columns outside the box stay zero (they are x neighbours)
         o[c].x = in ? b0.x + cf * hi : T(0);
         o[c].y = in ? b0.y - cf * hr : T(0);
-        if constexpr (KEEPD) {
-          dk[c].x = in ? cf * hi : T(0);
-          dk[c].y = in ? -cf * hr : T(0);
-        }
       }
       if (ORDER == 3 && active) {
         // First order: the psi stage also sees -i sum_f g_f at face points,
         // with g = the auxiliary input (stage 1) or the auxiliary stage
-        // v_f = fb_f + cA (b av_f + a w) (stage 2), added to the plain stage
+        // v_f = sA g_f + cA (b g_f + a w) (stage 2), added to the plain stage
         // output as -i cf g.
         const int pl = zk - (z0 - 1);
         const double cf2 = k == 1 ? cA : cB;
@@ -552,12 +549,6 @@ __device__ __forceinline__ void fused2_body(const typename cpx<T>::t* __restrict
             o[0].y += -cf2 * (c0 ? g.x : 0.0);
             o[1].x += cf2 * (c1 ? g.y : 0.0);
             o[1].y += -cf2 * (c1 ? g.x : 0.0);
-            if constexpr (KEEPD) {
-              dk[0].x += cf2 * (c0 ? g.y : 0.0);
-              dk[0].y += -cf2 * (c0 ? g.x : 0.0);
-              dk[1].x += cf2 * (c1 ? g.y : 0.0);
-              dk[1].y += -cf2 * (c1 ? g.x : 0.0);
-            }
           } else {
             const T dx = T(cf2 * g.y), dy = T(-cf2 * g.x);
             o[0].x += c0 ? dx : T(0);
@@ -581,25 +572,24 @@ __device__ __forceinline__ void fused2_body(const typename cpx<T>::t* __restrict
             double sr = 0, si = 0;
             double2 as1 = make_double2(0, 0);
             if (k == 2 && own) as1 = cmul(ba, make_double2((double)Yc[1][c].x, (double)Yc[1][c].y));
-            // stage 1 adds g; stage 2 adds v = f0 + cA (b g + a w), w at this
-            // plane, and at owned points writes f0 + cB b v + cB a s1
+            // stage 1 adds g; stage 2 adds v = sA g + cA (b g + a w), w at this
+            // plane, and at owned points writes g + cB b v + cB a t
             const double2 wv = make_double2((double)wm2[c].x, (double)wm2[c].y);
-            auto face = [&](const double2 g, const double2 f0, int oidx) {
+            auto face = [&](const double2 g, int oidx) {
               if (k == 1) {
                 sr += g.x;
                 si += g.y;
                 return;
               }
               const double2 bg = cmul(a.b0, g), aw = cmul(a.a0, wv);
-              const double2 v = make_double2(f0.x + cA * (bg.x + aw.x), f0.y + cA * (bg.y + aw.y));
+              const double2 v = make_double2(sA * g.x + cA * (bg.x + aw.x), sA * g.y + cA * (bg.y + aw.y));
               sr += v.x;
               si += v.y;
               if (own) {
                 const double2 bv = cmul(a.b0, v);
-                aux_out[oidx] = make_double2(f0.x + cB * bv.x + as1.x, f0.y + cB * bv.y + as1.y);
+                aux_out[oidx] = make_double2(g.x + cB * bv.x + as1.x, g.y + cB * bv.y + as1.y);
               }
             };
-            const double2 zero = make_double2(0, 0);
             if (fy) {
               // stage 1: g; stage 2: v from the halo wave's ring (the
               // auxiliary outputs are written there too)
@@ -607,29 +597,20 @@ __device__ __forceinline__ void fused2_body(const typename cpx<T>::t* __restrict
               sr += g.x;
               si += g.y;
             }
-            if (fz) {
-              const double2 f0 = SAME_BASE ? gz[c] : (k == 2 ? fzf[(r - H) * kCols + lx] : zero);
-              face(gz[c], f0, off_z + y * nx + x);
-            }
+            if (fz) face(gz[c], off_z + y * nx + x);
             o[c].x += T(cf2 * si);
             o[c].y += T(-cf2 * sr);
-            if constexpr (KEEPD) {
-              dk[c].x += T(cf2 * si);
-              dk[c].y += T(-cf2 * sr);
-            }
           }
         }
       }
-      C* kp = k == 1 ? keep1 : (KEEPD ? keep2 : nullptr);
-      if (kp && own_row && zk >= z0 && zk < z0 + TZ && zk < nz) {
-        // the stage-1 output (or with KEEPD the stage's increment) at the
-        // tile's own points, kept for the adjoint
+      if constexpr (MODE == kKeep) {
+        if (k == 1 && own_row && zk >= z0 && zk < z0 + TZ && zk < nz) {
+          // the stage-1 output at the tile's own points
 #pragma unroll
-        for (int c = 0; c < 2; ++c) {
-          const int x = xb + 2 * lane + c;
-          C v = o[c];
-          if constexpr (KEEPD) v = dk[c];
-          if (x >= xo && x < xe) kp[zk * sz + ybase + x] = v;
+          for (int c = 0; c < 2; ++c) {
+            const int x = xb + 2 * lane + c;
+            if (x >= xo && x < xe) keep[zk * sz + ybase + x] = o[c];
+          }
         }
       }
 #pragma unroll
@@ -639,18 +620,19 @@ __device__ __forceinline__ void fused2_body(const typename cpx<T>::t* __restrict
         prev[c] = o[c];
       }
     }
-    const int z2 = zi - 2;
-    const bool own_out = own_row && it >= 2 * H && z2 < nz;
 #pragma unroll
     for (int c = 0; c < 2; ++c) {
       const int x = xb + 2 * lane + c;
-      if (own_out && x >= xo && x < xe) out[z2 * sz + ybase + x] = prev[c];
+      if (own_out && x >= xo && x < xe) {
+        out[z2 * sz + ybase + x] = prev[c];
+        if constexpr (MODE == kGrad) {
+          const double dx = tau[c].x - sA * wm2[c].x, dy = tau[c].y - sA * wm2[c].y;
+          gr.gV[z2 * sz + ybase + x] =
+              g0[c] + gr.dt * ((wm2[c].x * gt[c].y - wm2[c].y * gt[c].x) + (dx * gy[c].y - dy * gy[c].x));
+        }
+      }
       Vd[1][c] = Vd[0][c];
       Vd[0][c] = vcur[c];
-      if (!SAME_BASE) {
-        Bd[1][c] = Bd[0][c];
-        Bd[0][c] = bcur[c];
-      }
     }
     // publish this plane's stage inputs; with a single buffer every wave
     // must first be done reading the previous ones
@@ -665,34 +647,20 @@ __device__ __forceinline__ void fused2_body(const typename cpx<T>::t* __restrict
 }
 
 // one box, arguments in the kernel argument segment
-template <typename T, int ORDER, bool SAME_BASE, int TZ, int PF = 1>
+template <typename T, int ORDER, int TZ, int MODE>
 __global__ void __launch_bounds__(64 * (kTY2 + 2 * kHalo2)) fused2_kernel(
-    const typename cpx<T>::t* __restrict__ w_in, const typename cpx<T>::t* __restrict__ base_in,
-    typename cpx<T>::t* __restrict__ out, const T* __restrict__ V, FusedArgs a, double cA, double cB,
-    const double2* __restrict__ av, const double2* __restrict__ fb, double2* __restrict__ aux_out,
-    typename cpx<T>::t* __restrict__ keep1) {
+    const typename cpx<T>::t* __restrict__ in, typename cpx<T>::t* __restrict__ out, const T* __restrict__ V,
+    FusedArgs a, double sA, double cA, double cB, const double2* __restrict__ av, double2* __restrict__ aux_out,
+    typename cpx<T>::t* __restrict__ keep, Grad2<typename cpx<T>::t> gr) {
   int tile = blockIdx.x;
   if (a.tiles_per_xcd) tile = (blockIdx.x & 7) * a.tiles_per_xcd + (blockIdx.x >> 3);
-  fused2_body<T, ORDER, SAME_BASE, TZ, PF>(w_in, base_in, out, V, a, cA, cB, av, fb, aux_out, tile, keep1);
-}
-
-// the same keeping the stage increments (the adjoint's Horner steps)
-template <typename T, int ORDER, bool SAME_BASE, int TZ>
-__global__ void __launch_bounds__(64 * (kTY2 + 2 * kHalo2)) fused2_keepd_kernel(
-    const typename cpx<T>::t* __restrict__ w_in, const typename cpx<T>::t* __restrict__ base_in,
-    typename cpx<T>::t* __restrict__ out, const T* __restrict__ V, FusedArgs a, double cA, double cB,
-    const double2* __restrict__ av, const double2* __restrict__ fb, double2* __restrict__ aux_out,
-    typename cpx<T>::t* __restrict__ keep1, typename cpx<T>::t* __restrict__ keep2) {
-  int tile = blockIdx.x;
-  if (a.tiles_per_xcd) tile = (blockIdx.x & 7) * a.tiles_per_xcd + (blockIdx.x >> 3);
-  fused2_body<T, ORDER, SAME_BASE, TZ, 1, true>(w_in, base_in, out, V, a, cA, cB, av, fb, aux_out, tile, keep1,
-                                               keep2);
+  fused2_body<T, ORDER, TZ, MODE>(in, out, V, a, sA, cA, cB, av, aux_out, tile, keep, gr);
 }
 
 // many boxes in one launch: the grid is the concatenation of the boxes' tiles
 // (padded to a multiple of 8 for the XCD-aware order); each workgroup finds
 // its box by binary search over the boxes' first tiles
-template <typename T, int ORDER, bool SAME_BASE, int TZ, int PF = 1>
+template <typename T, int ORDER, int TZ>
 __global__ void __launch_bounds__(64 * (kTY2 + 2 * kHalo2)) fused2_batch_kernel(
     const Box2* __restrict__ boxes, int nbox, int total_tiles, int half) {
   using C = typename cpx<T>::t;
@@ -706,11 +674,10 @@ __global__ void __launch_bounds__(64 * (kTY2 + 2 * kHalo2)) fused2_batch_kernel(
     else hi = mid - 1;
   }
   const Box2& b = boxes[lo];
-  // Horner coefficients of the box's own time step: (dt/4, dt/3) or (dt/2, dt)
-  const double cA = half ? b.a.coef[2] : b.a.coef[4], cB = half ? b.a.coef[1] : b.a.coef[3];
-  fused2_body<T, ORDER, SAME_BASE, TZ, PF>(static_cast<const C*>(b.w), static_cast<const C*>(b.base),
-                                       static_cast<C*>(b.out), static_cast<const T*>(b.V), b.a, cA, cB, b.av, b.fb,
-                                       b.aux_out, t - b.tile_begin);
+  // coefficients of the box's own time step
+  fused2_body<T, ORDER, TZ, kPlain>(static_cast<const C*>(b.in), static_cast<C*>(b.out), static_cast<const T*>(b.V),
+                                    b.a, half ? b.a.sa2 : b.a.sa1, half ? b.a.coef[2] : b.a.coef[4], b.a.coef[1],
+                                    b.av, b.aux_out, t - b.tile_begin, nullptr, Grad2<C>{});
 }
 
 // ---------------------------------------------------------------------------
@@ -720,7 +687,7 @@ __global__ void __launch_bounds__(64 * (kTY2 + 2 * kHalo2)) fused2_batch_kernel(
 // TZ planes, with four-deep halos in y and z; stage k is computed on rows
 // k .. ROWS-1-k and planes z0-(4-k) .. z0+TZ+(3-k), so each stage is exact
 // where the next reads it.  Register state per lane (two columns): the
-// centre and below planes of each stage's input, the Horner base at the two
+// centre and below planes of each stage's input, the factor's base at the two
 // oldest planes and V at the four stage planes.  The stage inputs' centre
 // planes are published in LDS, level j (the output of stage j, level 0 =
 // psi) only on the rows stage j+1 reads, double-buffered (one barrier per
@@ -1185,6 +1152,17 @@ __global__ void __launch_bounds__(64 * rows4<T>()) fused4_kernel(const typename 
   }
 }
 
+// the step polynomial's factors: stage k reads coef[5 - k]
+void set_factors(const abc_launch& L, FusedArgs& a) {
+  a.coef[4] = L.fused_b1 * L.dt;
+  a.coef[3] = L.dt;
+  a.coef[2] = L.fused_b2 * L.dt;
+  a.coef[1] = L.dt;
+  a.coef[0] = 0;
+  a.sa1 = L.fused_a1;
+  a.sa2 = L.fused_a2;
+}
+
 template <typename T>
 FusedArgs make_args4(const abc_launch& L) {
   FusedArgs a{};
@@ -1200,14 +1178,7 @@ FusedArgs make_args4(const abc_launch& L) {
   const double s = 1.0 / (2.0 * L.h * L.h);
   a.diag = -3.0 * L.c[0] * s;
   a.off = -L.c[1] * s;
-  // stage k reads coef[5 - k]: the factored form's coefficients
-  a.coef[4] = L.fused_b1 * L.dt;
-  a.coef[3] = L.dt;
-  a.coef[2] = L.fused_b2 * L.dt;
-  a.coef[1] = L.dt;
-  a.coef[0] = 0;
-  a.sa1 = L.fused_a1;
-  a.sa2 = L.fused_a2;
+  set_factors(L, a);
   for (int f = 0; f < 7; ++f) a.face_off[f] = (int)L.g.face_off[f];
   a.m0 = L.fused_m0;
   a.b0 = L.fused_b0;
@@ -1231,7 +1202,7 @@ FusedArgs make_args(const abc_launch& L) {
   const double s = 1.0 / (2.0 * L.h * L.h);
   a.diag = -3.0 * L.c[0] * s;
   a.off = -L.c[1] * s;
-  for (int k = 1; k <= 4; ++k) a.coef[k] = L.dt / k;
+  set_factors(L, a);
   for (int f = 0; f < 7; ++f) a.face_off[f] = (int)L.g.face_off[f];
   a.m0 = L.fused_m0;
   a.b0 = L.fused_b0;
@@ -1239,52 +1210,146 @@ FusedArgs make_args(const abc_launch& L) {
   return a;
 }
 
-// launch one two-stage kernel instance for a runtime tile depth
-template <typename T, int ORDER, bool SB, typename... A>
-void launch2(abc_timer* tm, const char* label, int tz, dim3 g, dim3 b, hipStream_t st, A... args) {
+// the tile depths the two-stage kernels are built for, and the kernel for one
+constexpr int kDepths[] = {2, 3, 4, 5, 6, 8, 12, 16};
 
-  if constexpr (ORDER == 3) {
-    if (tz == 4) return abc_launch_kernel(tm, label, fused2_kernel<T, ORDER, SB, 4>, g, b, st, args...);
-    return abc_launch_kernel(tm, label, fused2_kernel<T, ORDER, SB, 8>, g, b, st, args...);
-  } else {
-    if (tz == 4) return abc_launch_kernel(tm, label, fused2_kernel<T, ORDER, SB, 4>, g, b, st, args...);
-    if (tz == 16) return abc_launch_kernel(tm, label, fused2_kernel<T, ORDER, SB, 16>, g, b, st, args...);
-    return abc_launch_kernel(tm, label, fused2_kernel<T, ORDER, SB, 8>, g, b, st, args...);
+template <typename F>
+hipError_t with_depth(int tz, F f) {
+  switch (tz) {
+    case 2: f(std::integral_constant<int, 2>()); break;
+    case 3: f(std::integral_constant<int, 3>()); break;
+    case 4: f(std::integral_constant<int, 4>()); break;
+    case 5: f(std::integral_constant<int, 5>()); break;
+    case 6: f(std::integral_constant<int, 6>()); break;
+    case 8: f(std::integral_constant<int, 8>()); break;
+    case 12: f(std::integral_constant<int, 12>()); break;
+    case 16: f(std::integral_constant<int, 16>()); break;
+    default: return hipErrorInvalidValue;
+  }
+  return hipSuccess;
+}
+
+// ORDER template argument of an order without periodic wrap
+template <typename F>
+hipError_t with_order(int order, F f) {
+  switch (order) {
+    case ABC_FIRST: return f(std::integral_constant<int, 3>());
+    case ABC_ZEROTH: return f(std::integral_constant<int, 2>());
+    default: return f(std::integral_constant<int, 0>());
   }
 }
 
-template <typename T, int ORDER, bool SB, typename... A>
-void launch2_keepd(int tz, dim3 g, dim3 b, hipStream_t st, A... args) {
-  if constexpr (ORDER == 3) {
-    if (tz == 4) return abc_launch_kernel(nullptr, "", fused2_keepd_kernel<T, ORDER, SB, 4>, g, b, st, args...);
-    return abc_launch_kernel(nullptr, "", fused2_keepd_kernel<T, ORDER, SB, 8>, g, b, st, args...);
-  } else {
-    if (tz == 4) return abc_launch_kernel(nullptr, "", fused2_keepd_kernel<T, ORDER, SB, 4>, g, b, st, args...);
-    if (tz == 16) return abc_launch_kernel(nullptr, "", fused2_keepd_kernel<T, ORDER, SB, 16>, g, b, st, args...);
-    return abc_launch_kernel(nullptr, "", fused2_keepd_kernel<T, ORDER, SB, 8>, g, b, st, args...);
-  }
+// one factor (half 0: the first, 1: the second) from (in, fin) to (out, fout)
+template <typename T, int MODE>
+hipError_t launch_factor(const abc_launch& L, const FusedArgs& a, int half, const typename cpx<T>::t* in,
+                         typename cpx<T>::t* out, const double2* fin, double2* fout, const T* V,
+                         typename cpx<T>::t* keep, Grad2<typename cpx<T>::t> gr, hipStream_t st, abc_timer* tm) {
+  const dim3 g(a.ntiles), b(64 * (kTY2 + 2 * kHalo2));
+  const double sA = half ? a.sa2 : a.sa1, cA = half ? a.coef[2] : a.coef[4], cB = a.coef[1];
+  const char* label = half ? "fused2_half_b" : "fused2_half_a";
+  return with_order(L.order, [&](auto ord) {
+    return with_depth(L.fused_tz, [&](auto tz) {
+      abc_launch_kernel(tm, label, fused2_kernel<T, decltype(ord)::value, decltype(tz)::value, MODE>, g, b, st, in, out,
+                        V, a, sA, cA, cB, fin, fout, keep, gr);
+    });
+  });
 }
 
-template <typename T, int ORDER, bool SB>
-void launch2_batch(abc_timer* tm, const char* label, int tz, dim3 g, hipStream_t st, const Box2* boxes, int nbox,
-                   int total, int half) {
-  const dim3 b(64 * (kTY2 + 2 * kHalo2));
-  if constexpr (ORDER == 3) {
-    if (tz == 4) return abc_launch_kernel(tm, label, fused2_batch_kernel<T, ORDER, SB, 4>, g, b, st, boxes, nbox, total, half);
-    return abc_launch_kernel(tm, label, fused2_batch_kernel<T, ORDER, SB, 8>, g, b, st, boxes, nbox, total, half);
-  } else {
-    if (tz == 4) return abc_launch_kernel(tm, label, fused2_batch_kernel<T, ORDER, SB, 4>, g, b, st, boxes, nbox, total, half);
-    if (tz == 16) return abc_launch_kernel(tm, label, fused2_batch_kernel<T, ORDER, SB, 16>, g, b, st, boxes, nbox, total, half);
-    return abc_launch_kernel(tm, label, fused2_batch_kernel<T, ORDER, SB, 8>, g, b, st, boxes, nbox, total, half);
-  }
+template <typename T>
+hipError_t launch_factor_batch(int order, int tz, int half, const Box2* boxes, int nbox, int total, hipStream_t st,
+                               abc_timer* tm) {
+  const dim3 g((unsigned)((total + 7) / 8 * 8)), b(64 * (kTY2 + 2 * kHalo2));
+  const char* label = half ? "fused2_batch_b" : "fused2_batch_a";
+  return with_order(order, [&](auto ord) {
+    return with_depth(tz, [&](auto d) {
+      abc_launch_kernel(tm, label, fused2_batch_kernel<T, decltype(ord)::value, decltype(d)::value>, g, b, st, boxes,
+                        nbox, total, half);
+    });
+  });
+}
+
+int max_depth(int order, int nz) {
+  // first order: one z-face plane per tile needs nz >= TZ + 2
+  return order == ABC_FIRST ? std::min(16, nz - 2) : 16;
 }
 
 }  // namespace
 
-int fused_max_tz(int order, int nz) {
-  // first order: one z-face plane per tile needs nz >= TZ + 2
-  if (order == ABC_FIRST) return nz >= 10 ? 8 : 4;
-  return 16;
+int fused_max_limit(int order, int nz) {
+  const int m = max_depth(order, nz);
+  return m >= 16 ? 16 : (m >= 8 ? 8 : 4);
+}
+
+namespace {
+
+// rounds of workgroups that a launch takes; over many rounds the partly
+// filled last one hardly counts
+double tile_rounds(long long tiles) {
+  const double r = (double)tiles / kTileSlots;
+  return r < 4 ? std::ceil(r) : r;
+}
+
+long long tiles2(const FusedBox& b, int tz) {
+  const int ntx = b.nx > kCols ? (b.nx + kChunk - 1) / kChunk : 1;
+  return (long long)b.count * ntx * ((b.ny + kTY2 - 1) / kTY2) * ((b.nz + tz - 1) / tz);
+}
+
+// Whether the one-pass sweep takes less time than two launches of two stages
+// for one orbital in a box that both cover.  Either is estimated as rounds x
+// planes marched x the time of a plane, the latter as measured at 128^3 and
+// around it (us; the first order's one-pass sweep is slower on partial rows):
+//                    two-stage   one-pass
+//   c128 first         1.45        1.65, 1.85 on rows under 128 columns
+//   c128 zeroth        1.22        1.29
+//   c128 no condition  1.12        1.15
+//   c64  first         1.19        1.52, 1.74
+//   c64  zeroth        0.88        1.20
+//   c64  no condition  0.79        1.02
+// and the two launches not faster than their 2 (2 c + r) bytes per point, at
+// 5.2 TB/s while state, scratch and potential stay in the last-level cache
+// (180 MB) and 4.6 TB/s beyond.  Measured (two-stage / one-pass, us per
+// step): first order c128, 64 x 64 x 128 21.6 / 41.1, 128^3 40.8 / 43.0, 512 x
+// 512 x 128 582 / 730; c64 128^3 33.5 / 28.1; zeroth order c128, 96 x 96 x 128
+// 25.7 / 32.3, 128^3 35.6 / 33.9, 256 x 256 x 128 145 / 128.
+bool onepass_faster(const abc_params& p, const Geometry& g) {
+  const bool c64 = p.dtype == ABC_C64, first = p.order == ABC_FIRST, full = p.nx == kCols;
+  const int o = first ? 0 : (p.order == ABC_ZEROTH ? 1 : 2);
+  constexpr double c2[2][3] = {{1.45, 1.22, 1.12}, {1.19, 0.88, 0.79}};
+  constexpr double c4[2][3] = {{1.65, 1.29, 1.15}, {1.52, 1.20, 1.02}};
+  const FusedBox b{p.nx, p.ny, p.nz, 1};
+  const int tz = fused_pick_depth(p.order, 16, {b});
+  const int ty4 = c64 ? Tile4<float>::TY : Tile4<double>::TY, tz4 = c64 ? Tile4<float>::TZ : Tile4<double>::TZ;
+  const long long n4 = (long long)((p.ny + ty4 - 1) / ty4) * ((p.nz + tz4 - 1) / tz4);
+  const double n = (double)g.npts, csz = c64 ? 8 : 16;
+  const double bytes = 2 * n * 2.5 * csz, rate = n * 2.5 * csz < 180e6 ? 5.2e6 : 4.6e6;
+  const double est2 =
+      std::max(2 * (tile_rounds(tiles2(b, tz)) * (tz + 2 * kHalo2) + kTileStart) * c2[c64][o], bytes / rate);
+  const double est4 = (tile_rounds(n4) * (tz4 + 2 * kHalo4) + kTileStart) * c4[c64][o] * (first && !full ? 1.13 : 1.0);
+  return est4 <= est2;
+}
+
+}  // namespace
+
+int fused_pick_depth(int order, int limit, const std::vector<FusedBox>& boxes) {
+  int best = 4;
+  double best_cost = 0;
+  bool any = false;
+  for (int tz : kDepths) {
+    bool ok = tz <= limit;
+    long long tiles = 0;
+    for (const FusedBox& b : boxes) {
+      ok = ok && tz <= max_depth(order, b.nz);
+      tiles += tiles2(b, tz);
+    }
+    if (!ok) continue;
+    const double cost = tile_rounds(tiles) * (tz + 2 * kHalo2 + kTileStart);
+    if (!any || cost < best_cost) {
+      any = true;
+      best = tz;
+      best_cost = cost;
+    }
+  }
+  return best;
 }
 
 bool fused_supported(const abc_params& p, std::string* why) {
@@ -1376,31 +1441,30 @@ bool taylor4_quadratic_factors(double* a1, double* b1, double* a2, double* b2) {
 abc_status fused_prepare(const abc_params& p, abc_launch& L, std::vector<void*>* allocs, size_t* bytes,
                          std::string& err) {
   // the one-pass sweep where it covers the parameters (automatic path) or
-  // when asked for, else two launches of two Horner stages per step, whose
-  // tile depth (4, 8 or 16 planes) starts at 8 and is set by the tuner
+  // when asked for, else two launches of two stages per step, whose tile
+  // depth the tuner may limit (4, 8 or 16 planes)
   L.fused_stages = 2;
-  // Automatic choice: the one-pass sweep wherever it covers the parameters,
-  // except the first order on rows narrower than 128 columns, where its
-  // x-face sources need selects and it measured slower than the two-stage
-  // kernels (96^3: 48 against 39 us per step)
-  // (a windowed first-order operator takes the one-pass sweep with the
+  if (!taylor4_quadratic_factors(&L.fused_a1, &L.fused_b1, &L.fused_a2, &L.fused_b2)) {
+    err = "fused path: factoring the Taylor polynomial failed";
+    return ABC_EDEVICE;
+  }
+  // Automatic choice, one orbital: by the estimate of onepass_faster, up to
+  // the largest state it was measured on (2.95 GB); beyond that the one-pass
+  // sweep where it covers the parameters (first order: rows of 128 columns).
+  // A windowed first-order operator takes the one-pass sweep with the
   // boundary-shell rounds only when asked for: at 128^3 it measured level
   // with the staged path, w = 8 145 against 141 us per step, exact sections
-  // 182 against 185)
+  // 182 against 185.
   // Orbital batches and the mean field (orbitals as boxes of one launch):
-  // the one-pass sweep for complex64 (the 96^3 x 32-orbital TDHF batch: 0.61
-  // against 0.70 ms per step); complex128 measured level (0.95 against 0.94)
-  // and stays on the two-stage kernels.
+  // the one-pass sweep for complex64, two launches for complex128.
   const bool orbitals = p.batch > 1 || p.meanfield != ABC_MF_NONE;
+  const bool large = (double)L.g.npts * (p.dtype == ABC_C64 ? 8 : 16) > 3e9;
   const bool auto4 = fused4_supported(p, nullptr) && !fused_shell_case(p) &&
-                     (orbitals ? p.dtype == ABC_C64 : (p.order != ABC_FIRST || p.nx == kCols));
+                     (orbitals ? p.dtype == ABC_C64
+                               : (large ? p.order != ABC_FIRST || p.nx == kCols : onepass_faster(p, L.g)));
   L.fused_shell = 0;
   if (p.path == ABC_PATH_ONEPASS || (p.path == ABC_PATH_AUTO && auto4)) {
     if (!fused4_supported(p, &err)) return ABC_ENOTSUP;
-    if (!taylor4_quadratic_factors(&L.fused_a1, &L.fused_b1, &L.fused_a2, &L.fused_b2)) {
-      err = "one-pass sweep: factoring the Taylor polynomial failed";
-      return ABC_EDEVICE;
-    }
     L.fused_stages = 4;
     if (fused_shell_case(p)) {
       // four psi-sized and two face-aux buffers for the boundary-shell rounds
@@ -1421,12 +1485,9 @@ abc_status fused_prepare(const abc_params& p, abc_launch& L, std::vector<void*>*
       }
     }
   }
-  L.fused_tz = std::min(8, fused_max_tz(p.order, p.nz));
+  L.fused_limit = fused_max_limit(p.order, p.nz);
+  L.fused_tz = fused_pick_depth(p.order, L.fused_limit, {{p.nx, p.ny, p.nz, p.batch}});
   return ABC_OK;
-}
-
-bool fused_tz_valid(const abc_launch& L, int tz) {
-  return (tz == 4 || tz == 8 || tz == 16) && tz <= fused_max_tz(L.order, L.g.nz);
 }
 
 namespace {
@@ -1513,154 +1574,53 @@ hipError_t step_t(const abc_launch& L, const abc_scratch& S, void* psi_v, double
   using C = typename cpx<T>::t;
   FusedArgs a = make_args<T>(L);
   a.has_V = V_v != nullptr;
-  C* user = static_cast<C*>(psi_v);
-  C* scr = static_cast<C*>(S.y[0]);
+  C* psi = static_cast<C*>(psi_v);
   C* mid = static_cast<C*>(S.y[1]);
-  double2* fuser = aux;
-  double2* fscr = S.facc;
   double2* vmid = S.g[0];
-  const bool first = L.order == ABC_FIRST;
-  const size_t pbytes = (size_t)L.g.npts * sizeof(C);
-  const size_t fbytes = (size_t)L.g.face_off[6] * sizeof(double2);
-  // arrange the ping-pong so that the last step writes the caller's buffers
-  C* src = user;
-  C* dst = scr;
-  double2* fsrc = fuser;
-  double2* fdst = fscr;
-  if (n & 1) {
-    hipError_t e = hipMemcpyAsync(scr, user, pbytes, hipMemcpyDeviceToDevice, st);
-    if (e != hipSuccess) return e;
-    if (first) {
-      e = hipMemcpyAsync(fscr, fuser, fbytes, hipMemcpyDeviceToDevice, st);
-      if (e != hipSuccess) return e;
-    }
-    src = scr;
-    dst = user;
-    fsrc = fscr;
-    fdst = fuser;
-  }
   const T* V = static_cast<const T*>(V_v);
-  const int nthreads2 = 64 * (kTY2 + 2 * kHalo2);
-  const double dt = L.dt;
-  const int tz = L.fused_tz;
-  const dim3 g1(a.ntiles), b2(nthreads2);
-  const double2* none = nullptr;
-  double2* none_w = nullptr;
+  // the state goes to the scratch and back: each factor reads only its input
   for (int s = 0; s < n; ++s) {
-    {
-      if (L.order == ABC_ZEROTH) {
-        launch2<T, 2, true>(tm, "fused2_half_a", tz, g1, b2, st, (const C*)src, (const C*)src, mid, V, a, dt / 4,
-                            dt / 3, none, none, none_w, (C*)nullptr);
-        launch2<T, 2, false>(tm, "fused2_half_b", tz, g1, b2, st, (const C*)mid, (const C*)src, dst, V, a, dt / 2,
-                             dt, none, none, none_w, (C*)nullptr);
-      } else if (first) {
-        launch2<T, 3, true>(tm, "fused2_half_a", tz, g1, b2, st, (const C*)src, (const C*)src, mid, V, a, dt / 4,
-                            dt / 3, (const double2*)fsrc, (const double2*)fsrc, vmid, (C*)nullptr);
-        launch2<T, 3, false>(tm, "fused2_half_b", tz, g1, b2, st, (const C*)mid, (const C*)src, dst, V, a, dt / 2,
-                             dt, (const double2*)vmid, (const double2*)fsrc, fdst, (C*)nullptr);
-      } else {
-        launch2<T, 0, true>(tm, "fused2_half_a", tz, g1, b2, st, (const C*)src, (const C*)src, mid, V, a, dt / 4,
-                            dt / 3, none, none, none_w, (C*)nullptr);
-        launch2<T, 0, false>(tm, "fused2_half_b", tz, g1, b2, st, (const C*)mid, (const C*)src, dst, V, a, dt / 2,
-                             dt, none, none, none_w, (C*)nullptr);
-      }
-    }
+    hipError_t e = launch_factor<T, kPlain>(L, a, 0, psi, mid, aux, vmid, V, nullptr, {}, st, tm);
+    if (e == hipSuccess) e = launch_factor<T, kPlain>(L, a, 1, mid, psi, vmid, aux, V, nullptr, {}, st, tm);
+    if (e != hipSuccess) return e;
     if (tm) tm->end_step();
-    std::swap(src, dst);
-    std::swap(fsrc, fdst);
-  }
-  return hipGetLastError();
-}
-
-// One step out of place on the two-stage kernels, keeping the Horner
-// intermediates u1, u2, u3 of the step (keep[0..2], psi-sized): half A writes
-// u2 and keeps its stage-1 output u3, half B keeps u1.
-template <typename T>
-hipError_t step_keep_t(const abc_launch& L, const abc_scratch& S, const void* psi_in, const double2* aux_in,
-                       void* psi_out, double2* aux_out, const void* V_v, void* const* keep, hipStream_t st) {
-  using C = typename cpx<T>::t;
-  FusedArgs a = make_args<T>(L);
-  a.has_V = V_v != nullptr;
-  const C* src = static_cast<const C*>(psi_in);
-  C* dst = static_cast<C*>(psi_out);
-  C* u1 = static_cast<C*>(keep[0]);
-  C* u2 = static_cast<C*>(keep[1]);
-  C* u3 = static_cast<C*>(keep[2]);
-  const T* V = static_cast<const T*>(V_v);
-  const double dt = L.dt;
-  const int tz = L.fused_tz;
-  const dim3 g1(a.ntiles), b2(64 * (kTY2 + 2 * kHalo2));
-  const double2* none = nullptr;
-  double2* none_w = nullptr;
-  double2* vmid = S.g[0];
-  if (L.order == ABC_ZEROTH) {
-    launch2<T, 2, true>(nullptr, "", tz, g1, b2, st, src, src, u2, V, a, dt / 4, dt / 3, none, none, none_w, u3);
-    launch2<T, 2, false>(nullptr, "", tz, g1, b2, st, (const C*)u2, src, dst, V, a, dt / 2, dt, none, none, none_w,
-                         u1);
-  } else if (L.order == ABC_FIRST) {
-    launch2<T, 3, true>(nullptr, "", tz, g1, b2, st, src, src, u2, V, a, dt / 4, dt / 3, aux_in, aux_in, vmid, u3);
-    launch2<T, 3, false>(nullptr, "", tz, g1, b2, st, (const C*)u2, src, dst, V, a, dt / 2, dt,
-                         (const double2*)vmid, aux_in, aux_out, u1);
-  } else {
-    launch2<T, 0, true>(nullptr, "", tz, g1, b2, st, src, src, u2, V, a, dt / 4, dt / 3, none, none, none_w, u3);
-    launch2<T, 0, false>(nullptr, "", tz, g1, b2, st, (const C*)u2, src, dst, V, a, dt / 2, dt, none, none, none_w,
-                         u1);
-  }
-  return hipGetLastError();
-}
-
-// The same keeping the increments: keep[2] = u3 - z, keep[1] = u2 - z,
-// keep[0] = u1 - z (z the step's input); u2 itself goes to S.y[1].
-template <typename T>
-hipError_t step_keepd_t(const abc_launch& L, const abc_scratch& S, const void* psi_in, const double2* aux_in,
-                        void* psi_out, double2* aux_out, const void* V_v, void* const* keep, hipStream_t st) {
-  using C = typename cpx<T>::t;
-  FusedArgs a = make_args<T>(L);
-  a.has_V = V_v != nullptr;
-  const C* src = static_cast<const C*>(psi_in);
-  C* dst = static_cast<C*>(psi_out);
-  C* mid = static_cast<C*>(S.y[1]);
-  C* d1 = static_cast<C*>(keep[0]);
-  C* d2 = static_cast<C*>(keep[1]);
-  C* d3 = static_cast<C*>(keep[2]);
-  const T* V = static_cast<const T*>(V_v);
-  const double dt = L.dt;
-  const int tz = L.fused_tz;
-  const dim3 g1(a.ntiles), b2(64 * (kTY2 + 2 * kHalo2));
-  const double2* none = nullptr;
-  double2* none_w = nullptr;
-  double2* vmid = S.g[0];
-  C* nul = nullptr;
-  if (L.order == ABC_ZEROTH) {
-    launch2_keepd<T, 2, true>(tz, g1, b2, st, src, src, mid, V, a, dt / 4, dt / 3, none, none, none_w, d3, d2);
-    launch2_keepd<T, 2, false>(tz, g1, b2, st, (const C*)mid, src, dst, V, a, dt / 2, dt, none, none, none_w, d1,
-                               nul);
-  } else if (L.order == ABC_FIRST) {
-    launch2_keepd<T, 3, true>(tz, g1, b2, st, src, src, mid, V, a, dt / 4, dt / 3, aux_in, aux_in, vmid, d3, d2);
-    launch2_keepd<T, 3, false>(tz, g1, b2, st, (const C*)mid, src, dst, V, a, dt / 2, dt, (const double2*)vmid,
-                               aux_in, aux_out, d1, nul);
-  } else {
-    launch2_keepd<T, 0, true>(tz, g1, b2, st, src, src, mid, V, a, dt / 4, dt / 3, none, none, none_w, d3, d2);
-    launch2_keepd<T, 0, false>(tz, g1, b2, st, (const C*)mid, src, dst, V, a, dt / 2, dt, none, none, none_w, d1,
-                               nul);
   }
   return hipGetLastError();
 }
 
 }  // namespace
 
-hipError_t launch_step_fused_keepd(const abc_launch& L, const abc_scratch& S, const void* psi_in,
-                                   const double2* aux_in, void* psi_out, double2* aux_out, const void* V,
-                                   void* const* keep, hipStream_t st) {
+// One step out of place, psi_in -> psi_mid -> psi_out: keep receives each
+// factor's stage-1 output t.
+hipError_t launch_step_fused_keep(const abc_launch& L, const abc_scratch& S, const double2* psi_in,
+                                  const double2* aux_in, double2* psi_mid, double2* psi_out, double2* aux_out,
+                                  const double* V, double2* const* keep, hipStream_t st) {
   if (L.dtype != ABC_C128) return hipErrorInvalidValue;
-  return step_keepd_t<double>(L, S, psi_in, aux_in, psi_out, aux_out, V, keep, st);
+  FusedArgs a = make_args<double>(L);
+  a.has_V = V != nullptr;
+  hipError_t e = launch_factor<double, kKeep>(L, a, 0, psi_in, psi_mid, aux_in, S.g[0], V, keep[0], {}, st, nullptr);
+  if (e == hipSuccess)
+    e = launch_factor<double, kKeep>(L, a, 1, psi_mid, psi_out, S.g[0], aux_out, V, keep[1], {}, st, nullptr);
+  return e == hipSuccess ? hipGetLastError() : e;
 }
 
-hipError_t launch_step_fused_keep(const abc_launch& L, const abc_scratch& S, const void* psi_in,
-                                  const double2* aux_in, void* psi_out, double2* aux_out, const void* V,
-                                  void* const* keep, hipStream_t st) {
-  if (L.dtype == ABC_C64) return step_keep_t<float>(L, S, psi_in, aux_in, psi_out, aux_out, V, keep, st);
-  return step_keep_t<double>(L, S, psi_in, aux_in, psi_out, aux_out, V, keep, st);
+// One adjoint step of (lam, mu), in place through the scratch, adding the
+// step's part of the gradient with respect to V to gV: La is the adjoint
+// operator set, z, v and t the forward step's input, its state between the
+// factors and the factors' stage-1 outputs, dt the forward time step.
+hipError_t launch_step_fused_grad(const abc_launch& La, const abc_scratch& S, double2* lam, double2* mu,
+                                  const double2* z, const double2* v, double2* const* t, const double* V, double* gV,
+                                  double dt, hipStream_t st) {
+  if (La.dtype != ABC_C128) return hipErrorInvalidValue;
+  FusedArgs a = make_args<double>(La);
+  a.has_V = V != nullptr;
+  double2* mid = static_cast<double2*>(S.y[1]);
+  hipError_t e = launch_factor<double, kGrad>(La, a, 1, lam, mid, mu, S.g[0], V, nullptr,
+                                              Grad2<double2>{t[1], v, gV, dt}, st, nullptr);
+  if (e == hipSuccess)
+    e = launch_factor<double, kGrad>(La, a, 0, mid, lam, S.g[0], mu, V, nullptr, Grad2<double2>{t[0], z, gV, dt}, st,
+                                     nullptr);
+  return e == hipSuccess ? hipGetLastError() : e;
 }
 
 hipError_t launch_step_fused(const abc_launch& L, const abc_scratch& S, void* psi, double2* aux, const void* V,
@@ -1674,54 +1634,33 @@ hipError_t launch_step_fused(const abc_launch& L, const abc_scratch& S, void* ps
 // boxes that share (order, precision, tile depth).
 // ---------------------------------------------------------------------------
 
-size_t fused_batch_desc_bytes(int nbox) { return (size_t)4 * nbox * sizeof(Box2); }
+size_t fused_batch_desc_bytes(int nbox) { return (size_t)2 * nbox * sizeof(Box2); }
 
-int fused_batch_build(const std::vector<FusedMember>& m, void* host, int n) {
+int fused_batch_build(const std::vector<FusedMember>& m, void* host) {
   const int nb = (int)m.size();
   Box2* hb = static_cast<Box2*>(host);
   int total = 0;
-  // descriptor sets [parity][half]; each box keeps its own ping-pong, arranged
-  // like the single-box path so that the last step writes the caller's buffers
   for (int i = 0; i < nb; ++i) {
     const abc_launch& L = *m[i].L;
     const abc_scratch& S = *m[i].S;
-    FusedArgs a = L.dtype == ABC_C64 ? make_args<float>(L) : make_args<double>(L);
-    a.has_V = m[i].V != nullptr;
-    char* user = static_cast<char*>(m[i].psi);
-    char* scr = static_cast<char*>(S.y[0]);
-    char* mid = static_cast<char*>(S.y[1]);
-    double2* fuser = m[i].aux;
-    double2* fscr = S.facc;
-    double2* vmid = S.g[0];
     const bool first = L.order == ABC_FIRST;
-    char* src0 = (n & 1) ? scr : user;
-    char* dst0 = (n & 1) ? user : scr;
-    double2* fsrc0 = (n & 1) ? fscr : fuser;
-    double2* fdst0 = (n & 1) ? fuser : fscr;
-    for (int q = 0; q < 2; ++q) {
-      char* src = q == 0 ? src0 : dst0;
-      char* dst = q == 0 ? dst0 : src0;
-      double2* fsrc = q == 0 ? fsrc0 : fdst0;
-      double2* fdst = q == 0 ? fdst0 : fsrc0;
-      Box2& A = hb[(q * 2 + 0) * nb + i];
-      Box2& B = hb[(q * 2 + 1) * nb + i];
-      A.a = a;
-      A.w = src;
-      A.base = src;
-      A.out = mid;
-      A.V = m[i].V;
-      A.av = first ? fsrc : nullptr;
-      A.fb = first ? fsrc : nullptr;
-      A.aux_out = first ? vmid : nullptr;
-      A.tile_begin = total;
-      A.pad = 0;
-      B = A;
-      B.w = mid;
-      B.av = first ? vmid : nullptr;
-      B.out = dst;
-      B.aux_out = first ? fdst : nullptr;
-    }
-    total += a.ntiles;
+    Box2& A = hb[i];
+    Box2& B = hb[nb + i];
+    A.a = L.dtype == ABC_C64 ? make_args<float>(L) : make_args<double>(L);
+    A.a.has_V = m[i].V != nullptr;
+    A.in = m[i].psi;
+    A.out = S.y[1];
+    A.V = m[i].V;
+    A.av = first ? m[i].aux : nullptr;
+    A.aux_out = first ? S.g[0] : nullptr;
+    A.tile_begin = total;
+    A.pad = 0;
+    B = A;
+    B.in = S.y[1];
+    B.out = m[i].psi;
+    B.av = first ? S.g[0] : nullptr;
+    B.aux_out = first ? m[i].aux : nullptr;
+    total += A.a.ntiles;
   }
   return total;
 }
@@ -1735,39 +1674,15 @@ hipError_t launch_batch_fused(const std::vector<FusedMember>& m, int tz, const v
   // instantiated at tz, so every box must have been built at that depth
   for (int i = 0; i < nb; ++i)
     if (m[i].L->fused_tz != tz) return hipErrorInvalidValue;
-  if (n & 1)
-    for (int i = 0; i < nb; ++i) {
-      const abc_launch& L = *m[i].L;
-      const size_t csz = L.dtype == ABC_C64 ? 8 : 16;
-      hipError_t e = hipMemcpyAsync(m[i].S->y[0], m[i].psi, (size_t)L.g.npts * csz, hipMemcpyDeviceToDevice, st);
-      if (e == hipSuccess && L.order == ABC_FIRST)
-        e = hipMemcpyAsync(m[i].S->facc, m[i].aux, (size_t)L.g.face_off[6] * sizeof(double2),
-                           hipMemcpyDeviceToDevice, st);
+  const Box2* db = static_cast<const Box2*>(dev);
+  for (int s = 0; s < n; ++s) {
+    for (int half = 0; half < 2; ++half) {
+      const hipError_t e =
+          L0.dtype == ABC_C64
+              ? launch_factor_batch<float>(L0.order, tz, half, db + half * nb, nb, total, st, tm)
+              : launch_factor_batch<double>(L0.order, tz, half, db + half * nb, nb, total, st, tm);
       if (e != hipSuccess) return e;
     }
-  const Box2* db = static_cast<const Box2*>(dev);
-  const dim3 g((unsigned)((total + 7) / 8 * 8));
-  const int order = L0.order;
-  const bool c64 = L0.dtype == ABC_C64;
-  for (int s = 0; s < n; ++s) {
-    const int q = s & 1;
-    const Box2* dA = db + (q * 2 + 0) * nb;
-    const Box2* dB = db + (q * 2 + 1) * nb;
-#define ABC_BATCH_PAIR(T, ORD)                                                        \
-  do {                                                                                \
-    launch2_batch<T, ORD, true>(tm, "fused2_batch_a", tz, g, st, dA, nb, total, 0);   \
-    launch2_batch<T, ORD, false>(tm, "fused2_batch_b", tz, g, st, dB, nb, total, 1);  \
-  } while (0)
-    if (c64) {
-      if (order == ABC_FIRST) ABC_BATCH_PAIR(float, 3);
-      else if (order == ABC_ZEROTH) ABC_BATCH_PAIR(float, 2);
-      else ABC_BATCH_PAIR(float, 0);
-    } else {
-      if (order == ABC_FIRST) ABC_BATCH_PAIR(double, 3);
-      else if (order == ABC_ZEROTH) ABC_BATCH_PAIR(double, 2);
-      else ABC_BATCH_PAIR(double, 0);
-    }
-#undef ABC_BATCH_PAIR
     if (tm) tm->end_step();
   }
   return hipGetLastError();
@@ -1835,40 +1750,7 @@ __global__ void __launch_bounds__(256) meanfield_soa_kernel(const typename cpx<T
   veff[p] = base + t0 * rho + t3 * rho * rho;
 }
 
-// one step of parity q over every box of a batch (descriptors already on the
-// device, ping-pong arranged by fused_batch_build)
-hipError_t launch_batch_step(const abc_launch& L0, int nb, int tz, const void* dev, int total, int q,
-                             hipStream_t st, abc_timer* tm) {
-  const Box2* db = static_cast<const Box2*>(dev);
-  const dim3 g((unsigned)((total + 7) / 8 * 8));
-  const Box2* dA = db + (q * 2 + 0) * nb;
-  const Box2* dB = db + (q * 2 + 1) * nb;
-  const int order = L0.order;
-#define ABC_BATCH_PAIR(T, ORD)                                                        \
-  do {                                                                                \
-    launch2_batch<T, ORD, true>(tm, "fused2_batch_a", tz, g, st, dA, nb, total, 0);   \
-    launch2_batch<T, ORD, false>(tm, "fused2_batch_b", tz, g, st, dB, nb, total, 1);  \
-  } while (0)
-  if (L0.dtype == ABC_C64) {
-    if (order == ABC_FIRST) ABC_BATCH_PAIR(float, 3);
-    else if (order == ABC_ZEROTH) ABC_BATCH_PAIR(float, 2);
-    else ABC_BATCH_PAIR(float, 0);
-  } else {
-    if (order == ABC_FIRST) ABC_BATCH_PAIR(double, 3);
-    else if (order == ABC_ZEROTH) ABC_BATCH_PAIR(double, 2);
-    else ABC_BATCH_PAIR(double, 0);
-  }
-#undef ABC_BATCH_PAIR
-  return hipGetLastError();
-}
-
 }  // namespace
-
-size_t orbital_batch_bytes(const abc_launch& L1, int B, bool first, bool meanfield) {
-  const size_t csz = L1.dtype == ABC_C64 ? 8 : 16, rsz = L1.dtype == ABC_C64 ? 4 : 8;
-  return 3 * (size_t)B * L1.g.npts * csz + (first ? 3 * (size_t)B * L1.g.face_off[6] * 16 : 0) +
-         (meanfield ? (size_t)L1.g.npts * rsz : 0) + 2 * fused_batch_desc_bytes(B);
-}
 
 hipError_t launch_step_orbitals(OrbitalBatch& ob, void* psi, double2* aux, const void* V, int n, hipStream_t st,
                                 abc_timer* tm) {
@@ -1879,9 +1761,10 @@ hipError_t launch_step_orbitals(OrbitalBatch& ob, void* psi, double2* aux, const
   const bool c64 = L1.dtype == ABC_C64;
   const bool first = L1.order == ABC_FIRST;
   const size_t csz = c64 ? 8 : 16;
-  // the initial state goes where fused_batch_build expects it (array B for
-  // an odd count), so that the result ends in array A
-  const int in = (n & 1) ? 1 : 0;
+  // the result ends in array 0: the one-pass sweep alternates between the two
+  // arrays (an odd count starts in array 1), the two-stage launches go to
+  // array 1 and back
+  const int in = (L1.fused_stages == 4 && (n & 1)) ? 1 : 0;
   hipError_t e = c64 ? transpose<float2>(psi, ob.soa[in], np, B, true, st)
                      : transpose<double2>(psi, ob.soa[in], np, B, true, st);
   if (e == hipSuccess && first) e = transpose<double2>(aux, ob.soa_f[in], nf, B, true, st);
@@ -1889,12 +1772,8 @@ hipError_t launch_step_orbitals(OrbitalBatch& ob, void* psi, double2* aux, const
   std::vector<FusedMember> m(B);
   for (int b = 0; b < B; ++b) {
     abc_scratch& S = ob.S[b];
-    S.y[0] = static_cast<char*>(ob.soa[1]) + (size_t)b * np * csz;
-    S.y[1] = static_cast<char*>(ob.soa[2]) + (size_t)b * np * csz;
-    if (first) {
-      S.facc = ob.soa_f[1] + (size_t)b * nf;
-      S.g[0] = ob.soa_f[2] + (size_t)b * nf;
-    }
+    S.y[1] = static_cast<char*>(ob.soa[1]) + (size_t)b * np * csz;
+    if (first) S.g[0] = ob.soa_f[1] + (size_t)b * nf;
     m[b] = {&L1, &S, static_cast<char*>(ob.soa[0]) + (size_t)b * np * csz, first ? ob.soa_f[0] + (size_t)b * nf : nullptr,
             ob.veff ? ob.veff : V};
   }
@@ -1942,7 +1821,7 @@ hipError_t launch_step_orbitals(OrbitalBatch& ob, void* psi, double2* aux, const
       return hipErrorStreamCaptureUnsupported;
     if (ob.pending && hipEventSynchronize(ob.copied) != hipSuccess) return hipErrorUnknown;
     void* dhost = static_cast<char*>(ob.desc_host) + par * dbytes;
-    ob.desc_total = fused_batch_build(m, dhost, n);
+    ob.desc_total = fused_batch_build(m, dhost);
     e = hipMemcpyAsync(const_cast<void*>(ddev), dhost, dbytes, hipMemcpyHostToDevice, st);
     if (e == hipSuccess) e = hipEventRecord(ob.copied, st);
     if (e != hipSuccess) return e;
@@ -1952,10 +1831,8 @@ hipError_t launch_step_orbitals(OrbitalBatch& ob, void* psi, double2* aux, const
   }
   const int total = ob.desc_total;
   for (int s = 0; s < n; ++s) {
-    const int q = s & 1;
     if (ob.veff) {
-      // the current state: array `in` for even s, the other one for odd s
-      const void* cur = ob.soa[q == 0 ? in : 1 - in];
+      const void* cur = ob.soa[0];
       const unsigned blocks = (unsigned)((np + 255) / 256);
       if (L1.meanfield == ABC_MF_SKYRME)
         e = skyrme_veff(*L1.pot, cur, true, B, c64, V, ob.veff, L1.t0, L1.t3, st, tm);
@@ -1969,7 +1846,10 @@ hipError_t launch_step_orbitals(OrbitalBatch& ob, void* psi, double2* aux, const
                           static_cast<double*>(ob.veff), np, B, L1.t0, L1.t3);
       if (e != hipSuccess) return e;
     }
-    e = launch_batch_step(L1, B, ob.tz, ddev, total, q, st, tm);
+    const Box2* db = static_cast<const Box2*>(ddev);
+    for (int half = 0; half < 2 && e == hipSuccess; ++half)
+      e = c64 ? launch_factor_batch<float>(L1.order, ob.tz, half, db + half * B, B, total, st, tm)
+              : launch_factor_batch<double>(L1.order, ob.tz, half, db + half * B, B, total, st, tm);
     if (e != hipSuccess) return e;
     if (tm) tm->end_step();
   }
