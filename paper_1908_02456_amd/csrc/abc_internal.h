@@ -93,15 +93,16 @@ struct PotentialSolver {
   double v0 = 0, a = 1, e2 = 0, tol = 1e-12;
   int maxit = 1000, nblk = 0;
   double *rho = nullptr, *wy = nullptr, *wc = nullptr;  // density, Yukawa and Coulomb fields (persist)
-  double *r = nullptr, *p = nullptr, *q = nullptr;      // CG vectors
-  double *part = nullptr, *scal = nullptr;              // 3 nblk partial sums, scalar slots
-  double* host = nullptr;                               // pinned: convergence flag, iteration count
+  double *r = nullptr, *p = nullptr, *q = nullptr, *z = nullptr;  // CG vectors, one per field
+  double *part = nullptr, *scal = nullptr;              // 8 max(nblk, nz) partial sums, 8 scalar slots per field
+  double* host = nullptr;                               // pinned: convergence flag, iteration count per field
   int fixed = 0;                                        // > 0: iterations per solve, no host reads
   double* tally = nullptr;                              // device: Yukawa, Coulomb iterations, unconverged solves
-  // sine-transform preconditioner: DST-I matrices and R = 1 eigenvalues per
-  // axis, its work vectors, the preconditioned residual and a rocBLAS handle
+  // sine-transform preconditioner: DST-I matrices (zero-padded to multiples
+  // of 16) and R = 1 eigenvalues per axis, its work vectors (t1 one per field)
+  // and, for planes beyond LDS, t2 and a rocBLAS handle
   double *sx = nullptr, *sy = nullptr, *sz = nullptr, *ex = nullptr, *ey = nullptr, *ez = nullptr;
-  double *t1 = nullptr, *t2 = nullptr, *z = nullptr;
+  double *t1 = nullptr, *t2 = nullptr;
   void* blas = nullptr;
   long long iters_y = 0, iters_c = 0, solves = 0;
 };
@@ -284,6 +285,7 @@ abc_status face_fft_setup(const abc::Geometry& g, int R, int w, const std::vecto
 
 // V + t0 rho + t3 rho^2 + W_Y + W_C for psi ([point][orbital], or orbital
 // arrays when soa) into veff; synchronises the stream during the solves
+bool potential_needs_blas(const PotentialSolver& ps);
 hipError_t potential_warmup(PotentialSolver& ps);
 hipError_t skyrme_veff(PotentialSolver& ps, const void* psi, bool soa, int B, bool c64, const void* V, void* veff,
                        double t0, double t3, hipStream_t st, abc_timer* tm);

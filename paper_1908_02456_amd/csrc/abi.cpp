@@ -355,9 +355,11 @@ abc_status abc_setup(const abc_params* pp, abc_ctx** out) {
     ps.fixed = p.pcg_fixed;
     const size_t np = (size_t)L.g.npts;
     ps.nblk = (int)std::min<size_t>(1024, (np + 255) / 256);
-    double** vec[9] = {&ps.rho, &ps.wy, &ps.wc, &ps.r, &ps.p, &ps.q, &ps.t1, &ps.t2, &ps.z};
-    for (int i = 0; i < 9 && st == ABC_OK; ++i) {
-      st = dev_alloc(c, &tmp, np * sizeof(double));
+    const bool blas = potential_needs_blas(ps);
+    const size_t fields = (p.v0 != 0.0 ? 1 : 0) + (p.e2 != 0.0 ? 1 : 0);
+    double** vec[9] = {&ps.rho, &ps.wy, &ps.wc, &ps.r, &ps.p, &ps.q, &ps.z, &ps.t1, &ps.t2};
+    for (int i = 0; i < (blas ? 9 : 8) && st == ABC_OK; ++i) {
+      st = dev_alloc(c, &tmp, np * (i < 3 || i == 8 ? 1 : std::max<size_t>(fields, 1)) * sizeof(double));
       *vec[i] = static_cast<double*>(tmp);
     }
     // sine transforms and R = 1 eigenvalues per axis (preconditioner)
@@ -366,10 +368,11 @@ abc_status abc_setup(const abc_params* pp, abc_ctx** out) {
     double** eigs[3] = {&ps.ex, &ps.ey, &ps.ez};
     for (int a = 0; a < 3 && st == ABC_OK; ++a) {
       const int n = dims[a];
-      std::vector<double> S((size_t)n * n), ev(n);
+      const int n16 = (n + 15) / 16 * 16;
+      std::vector<double> S((size_t)n16 * n16, 0.0), ev(n);
       for (int j = 0; j < n; ++j) {
         ev[j] = (2.0 - 2.0 * std::cos(M_PI * (j + 1) / (n + 1))) / (p.h * p.h);
-        for (int k = 0; k < n; ++k) S[(size_t)j * n + k] = std::sin(M_PI * (double)(j + 1) * (k + 1) / (n + 1));
+        for (int k = 0; k < n; ++k) S[(size_t)j * n16 + k] = std::sin(M_PI * (double)(j + 1) * (k + 1) / (n + 1));
       }
       st = dev_alloc(c, &tmp, S.size() * sizeof(double));
       *mats[a] = static_cast<double*>(tmp);
@@ -379,21 +382,21 @@ abc_status abc_setup(const abc_params* pp, abc_ctx** out) {
                            hipMemcpy(*eigs[a], ev.data(), ev.size() * sizeof(double), hipMemcpyHostToDevice) != hipSuccess))
         st = fail(ABC_EDEVICE, "hipMemcpy failed");
     }
-    if (st == ABC_OK) {
+    if (st == ABC_OK && blas) {
       rocblas_handle hb = nullptr;
       if (rocblas_create_handle(&hb) != rocblas_status_success) st = fail(ABC_EDEVICE, "rocblas_create_handle failed");
       else ps.blas = hb;
     }
     if (st == ABC_OK && potential_warmup(ps) != hipSuccess) st = fail(ABC_EDEVICE, "potential solver set-up failed");
-    if (st == ABC_OK) st = dev_alloc(c, &tmp, 3 * (size_t)ps.nblk * sizeof(double));
+    if (st == ABC_OK) st = dev_alloc(c, &tmp, 8 * (size_t)std::max(ps.nblk, ps.nz) * sizeof(double));
     ps.part = static_cast<double*>(tmp);
-    if (st == ABC_OK) st = dev_alloc(c, &tmp, 8 * sizeof(double));
+    if (st == ABC_OK) st = dev_alloc(c, &tmp, 16 * sizeof(double));
     ps.scal = static_cast<double*>(tmp);
     if (st == ABC_OK) st = dev_alloc(c, &tmp, 3 * sizeof(double));
     ps.tally = static_cast<double*>(tmp);
     if (st == ABC_OK && hipMemset(ps.tally, 0, 3 * sizeof(double)) != hipSuccess)
       st = fail(ABC_EDEVICE, "hipMemset failed");
-    if (st == ABC_OK && hipHostMalloc(&tmp, 2 * sizeof(double)) != hipSuccess) st = fail(ABC_ENOMEM, "pinned memory");
+    if (st == ABC_OK && hipHostMalloc(&tmp, 4 * sizeof(double)) != hipSuccess) st = fail(ABC_ENOMEM, "pinned memory");
     if (st == ABC_OK) ps.host = static_cast<double*>(tmp);
     // the potentials start at zero (the first solve starts from zero)
     if (st == ABC_OK && (hipMemset(ps.wy, 0, np * sizeof(double)) != hipSuccess ||
