@@ -77,9 +77,16 @@ struct BoxReduced {
   double2* red = nullptr;
   int r = 0;
 };
+// First order with the theorem's pair: A = -i H_{Gamma,Sigma} H_{Sigma,Gamma},
+// which couples only points of one axis line near a face, as rows of
+// (column, value of the real product); empty for the other orders.
+struct BoxCoupling {
+  std::vector<int> row, col;  // row[i] .. row[i + 1]: entries of row i
+  std::vector<double> val;
+};
 abc_status build_box_ops(const abc_params& p, double2** mat_dev, double2** q_dev, int* n_gamma,
                          std::vector<int>& gamma_lin, double* spectral_bound, int* subspace_dim, BoxReduced* reduced,
-                         std::string& err);
+                         BoxCoupling* coupling, std::string& err);
 
 }  // namespace abc
 
@@ -130,6 +137,22 @@ struct ShellScratch {
   double2* face[2];
 };
 
+// Box form, one orbital: the product with an n x n operator B, w_i B_ij
+// symmetric, read as its upper triangle (box_half_kernel).
+struct BoxHalf {
+  const int2* units;    // strip and first column of each workgroup; null: not used
+  const int* strip0;    // first unit of each strip (one past the last at the end)
+  const double* w;      // weights w_i with w_i B_ij symmetric; null: all 1
+  double2* rowpart;     // [unit][row of the strip]
+  double2* colpart;     // [strip][column]
+  int nunit, cols;      // units, columns of a unit
+};
+// units, strips and column count for an n x n operator
+void box_half_plan(int n, std::vector<int2>& units, std::vector<int>& strip0, int* cols);
+// smallest n for which the half product is used
+int box_half_min();
+size_t box_half_scratch(int n, size_t nunit);  // elements of rowpart and colpart together
+
 struct abc_launch {
   abc::Geometry g;
   double h, dt;
@@ -161,6 +184,13 @@ struct abc_launch {
   const double* box_Ut;
   const double2* box_red;
   int box_r;
+  // first order, theorem's pair: A by its entries (rows box_arow[i] ..
+  // box_arow[i + 1], real values of i A); null otherwise
+  const int* box_arow;
+  const int* box_acol;
+  const double* box_aval;
+  // the operator's upper triangle alone (box_half_plan); box_w null: M = M^T
+  BoxHalf box_half;
   const int* gamma_lin;       // gamma index -> linear point index
   const int* point_gamma;     // linear point index -> gamma index or -1
   int n_gamma;

@@ -65,6 +65,17 @@ abc_status dev_alloc(abc_ctx* c, void** ptr, size_t bytes) {
   return ABC_OK;
 }
 
+template <typename E>
+abc_status dev_upload(abc_ctx* c, const E** ptr, const std::vector<E>& v) {
+  void* p = nullptr;
+  const abc_status st = dev_alloc(c, &p, v.size() * sizeof(E));
+  if (st != ABC_OK) return st;
+  if (hipMemcpy(p, v.data(), v.size() * sizeof(E), hipMemcpyHostToDevice) != hipSuccess)
+    return fail(ABC_EDEVICE, "hipMemcpy failed");
+  *ptr = static_cast<const E*>(p);
+  return ABC_OK;
+}
+
 abc_status check_params(const abc_params& p) {
   if (p.nx < 1 || p.ny < 1 || p.nz < 1) return fail(ABC_EINVAL, "box sizes must be positive");
   if (p.radius < 1 || p.radius > abc::kMaxR) return fail(ABC_EINVAL, "radius must be 1, 2 or 3");
@@ -227,8 +238,9 @@ abc_status abc_setup(const abc_params* pp, abc_ctx** out) {
     std::vector<int> glin;
     double bound = 0;
     abc::BoxReduced red;
+    abc::BoxCoupling coupling;
     st = abc::build_box_ops(p, &c->box_mat, &c->box_q, &c->n_gamma, glin, &bound, &c->box_rank,
-                            p.batch == 1 ? &red : nullptr, err);
+                            p.batch == 1 ? &red : nullptr, &coupling, err);
     c->box_bound = bound;
     if (st != ABC_OK) { abc_destroy(c); return fail(st, err); }
     if (red.red) {
@@ -263,6 +275,38 @@ abc_status abc_setup(const abc_params* pp, abc_ctx** out) {
     }
     L.gamma_lin = static_cast<const int*>(gl);
     L.point_gamma = static_cast<const int*>(pgd);
+    if (!coupling.row.empty() &&
+        ((st = dev_upload(c, &L.box_arow, coupling.row)) != ABC_OK ||
+         (st = dev_upload(c, &L.box_acol, coupling.col)) != ABC_OK ||
+         (st = dev_upload(c, &L.box_aval, coupling.val)) != ABC_OK)) {
+      abc_destroy(c);
+      return st;
+    }
+    // The operator's upper triangle is enough where w_i B_ij is symmetric:
+    // M = K(s0) itself; B = s1 I - A K(s1)^{-1} with A diagonal (R = 1, one
+    // entry per row), w = 1 / (i A_ii).
+    const bool diag_a = !coupling.row.empty() && (int)coupling.col.size() == c->n_gamma;
+    if (p.batch == 1 && c->n_gamma >= box_half_min() && (p.order == ABC_ZEROTH || diag_a)) {
+      BoxHalf& bh = L.box_half;
+      std::vector<int2> units;
+      std::vector<int> strip0;
+      box_half_plan(c->n_gamma, units, strip0, &bh.cols);
+      bh.nunit = (int)units.size();
+      void* part = nullptr;
+      if ((st = dev_upload(c, &bh.strip0, strip0)) == ABC_OK &&
+          (st = dev_alloc(c, &part, box_half_scratch(c->n_gamma, units.size()) * sizeof(double2))) == ABC_OK) {
+        bh.rowpart = static_cast<double2*>(part);
+        bh.colpart = bh.rowpart + (size_t)bh.nunit * 64;
+        if (diag_a) {
+          std::vector<double> w(coupling.val);
+          const double w0 = w[0];
+          for (double& v : w) v = w0 / v;
+          st = dev_upload(c, &bh.w, w);
+        }
+      }
+      if (st == ABC_OK) st = dev_upload(c, &bh.units, units);
+      if (st != ABC_OK) { abc_destroy(c); return st; }
+    }
     // zeroth: M adds to H; first and second: the boundary block (B, or the
     // (f, g) block [[0, I], [B0, B1]]) beside H, coupled through blocks of
     // the size of H_{Gamma,Sigma}

@@ -1038,6 +1038,25 @@ hipError_t face_fft_apply(const abc_launch& L, const double2* gin, double2* gout
 // vector from the caches (31^3, R = 3: 4.18 against 4.44 ms per first-order
 // step, 6.1 to 6.5 TB/s)
 // ---------------------------------------------------------------------------
+// The first order's A E y with the theorem's pair, A by its few entries per
+// row (columns in Gamma, values of i A), E y through the Gamma index.  The dense
+// A is as large as B; reading it beside B doubled a product's time (20^3, R = 3:
+// 598 against 341 us per step; 24^3, 32 orbitals 584 against 307).
+template <typename T>
+struct BoxCpl {
+  const int *row, *col;
+  const double* val;
+  const typename cpx<T>::t* y;
+  const int* gamma_lin;
+  __device__ __forceinline__ void add(double2& t, int i, int batch, int b) const {
+    for (int e = row[i]; e < row[i + 1]; ++e) {
+      const auto v = y[(long long)gamma_lin[col[e]] * batch + b];
+      t.x += val[e] * (double)v.y;
+      t.y -= val[e] * (double)v.x;
+    }
+  }
+};
+
 constexpr int kBoxRows = 4, kBoxRowsMin = 4096;
 constexpr int kGemvPlain = 3;
 typedef double stream_d2 __attribute__((ext_vector_type(2)));
@@ -1046,10 +1065,11 @@ __device__ __forceinline__ double2 stream_load(const double2* p) {
   return make_double2(v.x, v.y);
 }
 
+template <typename T>
 __global__ void __launch_bounds__(kBlock) box_gemv_rows_kernel(
-    const double2* __restrict__ mat, int nrow, int naux, int ncol, int ident, const double2* __restrict__ gin,
-    const double2* __restrict__ x2, double2* __restrict__ gout, double2* __restrict__ facc,
-    double2* __restrict__ aux_out, double coef, int mode) {
+    const double2* __restrict__ mat, long long ld, int nrow, int naux, int ncol, int ident,
+    const double2* __restrict__ gin, const double2* __restrict__ x2, BoxCpl<T> cpl, double2* __restrict__ gout,
+    double2* __restrict__ facc, double2* __restrict__ aux_out, double coef, int mode) {
   constexpr int RB = kBoxRows, NW = kBlock / 64;
   __shared__ double2 red[RB][NW];
   const int row0 = blockIdx.x * RB;
@@ -1057,7 +1077,7 @@ __global__ void __launch_bounds__(kBlock) box_gemv_rows_kernel(
   double sr[RB], si[RB];
 #pragma unroll
   for (int r = 0; r < RB; ++r) {
-    mrow[r] = mat + (long long)min(row0 + r, nrow - 1) * ncol;
+    mrow[r] = mat + min(row0 + r, nrow - 1) * ld;
     sr[r] = si[r] = 0.0;
   }
   // boundary-variable columns; rows below ident skip them (their [0, I]
@@ -1112,6 +1132,7 @@ __global__ void __launch_bounds__(kBlock) box_gemv_rows_kernel(
     gout[row] = t;
     return;
   }
+  if (cpl.row) cpl.add(t, row, 1, 0);
   const double2 gn = make_double2(coef * t.x, coef * t.y);
   if (mode == 0) {
     const double2 g0 = gin[row];
@@ -1130,6 +1151,157 @@ __global__ void __launch_bounds__(kBlock) box_gemv_rows_kernel(
 }
 
 // ---------------------------------------------------------------------------
+// box form, one orbital, from the operator's upper triangle: B with w_i B_ij
+// symmetric (M of the zeroth order with w = 1; B of the first order at R = 1,
+// where A is diagonal), so that an entry B_ij, i < j, read once serves
+//   row i:  B_ij x_j,   and row j:  B_ji x_i = (1 / w_j) B_ij (w_i x_i).
+// The operator is what a stage streams, so this halves its time.  A strip is
+// 64 rows; a unit (one workgroup) is a strip's columns c0 .. c0 + cols - 1 from
+// the diagonal on, 8 waves of 8 rows, a lane per column.  Row sums stay in
+// registers and are reduced over the lanes at the end; column sums are
+// complete within a wave's 8 rows, the waves' are added in LDS, and the
+// strip's go to colpart.  box_half_finish_kernel adds the units of a row and
+// the strips above a column in order (deterministic) and makes the stage
+// update.  The diagonal 64 x 64 block is read whole and adds to rows only.
+// 32^3 (n = 5768, 266 MB read): 54 us, 4.9 TB/s, + 5 us for the finish; four rows
+// per workgroup over the whole matrix 81 us (zeroth), with the dense A beside it
+// 157 us.  Bound by the matrix stream: it needs two workgroups per compute unit
+// (128 VGPRs; at 154, one, 96 us).  Below kHalfMin the strips are too few (us
+// per step, zeroth: n = 2648 141 against 141, n = 3176 137 against 182).
+// ---------------------------------------------------------------------------
+constexpr int kHalfRows = 64, kHalfWaves = 8, kHalfRW = kHalfRows / kHalfWaves, kHalfColsMax = 448;
+constexpr int kHalfMin = 3000;
+
+template <typename T, bool GATHER>
+__global__ void __launch_bounds__(64 * kHalfWaves, 4) box_half_kernel(const double2* __restrict__ mat, long long ld, int n,
+                                                                   BoxHalf bh, const double2* __restrict__ x,
+                                                                   const typename cpx<T>::t* __restrict__ y,
+                                                                   const int* __restrict__ gamma_lin) {
+  extern __shared__ double2 cols[];  // [wave][column of the unit], then the vector
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, nc = bh.cols;
+  const int2 u = bh.units[blockIdx.x];
+  const int r0 = u.x * kHalfRows, c0 = u.y, ce = min(c0 + nc, n);
+  auto vec = [&](int j) {
+    if (!GATHER) return x[j];
+    const auto v = y[gamma_lin[j]];
+    return make_double2((double)v.x, (double)v.y);
+  };
+  // the unit's part of the vector, once for all waves, behind the column sums
+  for (int j = c0 + threadIdx.x; j < ce; j += 64 * kHalfWaves) cols[kHalfWaves * nc + (j - c0)] = vec(j);
+  const double2* mrow[kHalfRW];
+  double2 xr[kHalfRW], acc[kHalfRW];
+#pragma unroll
+  for (int r = 0; r < kHalfRW; ++r) {
+    const int i = r0 + wv * kHalfRW + r;
+    mrow[r] = mat + min(i, n - 1) * ld;
+    xr[r] = make_double2(0, 0);
+    acc[r] = make_double2(0, 0);
+    if (i < n) {  // a row past the end adds nothing to the columns
+      xr[r] = vec(i);
+      if (bh.w) xr[r] = make_double2(bh.w[i] * xr[r].x, bh.w[i] * xr[r].y);
+    }
+  }
+  __syncthreads();
+  for (int j = c0 + lane; j < c0 + nc; j += 64) {
+    double2 cs = make_double2(0, 0);
+    if (j < ce) {
+      double2 m[kHalfRW];
+#pragma unroll
+      for (int r = 0; r < kHalfRW; ++r) m[r] = stream_load(&mrow[r][j]);
+      const double2 v = cols[kHalfWaves * nc + (j - c0)];
+#pragma unroll
+      for (int r = 0; r < kHalfRW; ++r) {
+        acc[r].x += m[r].x * v.x - m[r].y * v.y;
+        acc[r].y += m[r].x * v.y + m[r].y * v.x;
+        cs.x += m[r].x * xr[r].x - m[r].y * xr[r].y;
+        cs.y += m[r].x * xr[r].y + m[r].y * xr[r].x;
+      }
+    }
+    cols[wv * nc + (j - c0)] = cs;
+  }
+#pragma unroll
+  for (int r = 0; r < kHalfRW; ++r) {
+    for (int o = 32; o > 0; o >>= 1) {
+      acc[r].x += __shfl_down(acc[r].x, o, 64);
+      acc[r].y += __shfl_down(acc[r].y, o, 64);
+    }
+    if (lane == 0) bh.rowpart[(long long)blockIdx.x * kHalfRows + wv * kHalfRW + r] = acc[r];
+  }
+  __syncthreads();
+  for (int j = c0 + threadIdx.x; j < ce; j += 64 * kHalfWaves) {
+    if (j < r0 + kHalfRows) continue;
+    double2 s = cols[j - c0];
+#pragma unroll
+    for (int w = 1; w < kHalfWaves; ++w) {
+      const double2 q = cols[w * nc + (j - c0)];
+      s.x += q.x;
+      s.y += q.y;
+    }
+    bh.colpart[(long long)u.x * n + j] = s;
+  }
+}
+
+// row i: its units' row sums and 1 / w_i times the column sums of the strips
+// above, kHalfParts threads per row taking them in turn; then the stage update
+// (first order: with A E y) or the product itself (zeroth)
+constexpr int kHalfParts = 8, kHalfFin = 32;
+template <typename T>
+__global__ void __launch_bounds__(kHalfParts * kHalfFin) box_half_finish_kernel(
+    BoxHalf bh, int n, BoxCpl<T> cpl, const double2* __restrict__ gin, double2* __restrict__ gout,
+    double2* __restrict__ facc, double2* __restrict__ aux_out, double coef, int mode) {
+  __shared__ double2 part[kHalfParts][kHalfFin];
+  const int li = threadIdx.x % kHalfFin, q = threadIdx.x / kHalfFin;
+  const int i = blockIdx.x * kHalfFin + li;
+  double2 t = make_double2(0, 0);
+  if (i < n) {
+    const int s = i / kHalfRows;
+    double2 c = make_double2(0, 0);
+#pragma unroll 4
+    for (int k = q; k < s; k += kHalfParts) {
+      const double2 v = bh.colpart[(long long)k * n + i];
+      c.x += v.x;
+      c.y += v.y;
+    }
+    if (bh.w) c = make_double2(c.x / bh.w[i], c.y / bh.w[i]);
+    for (int k = bh.strip0[s] + q; k < bh.strip0[s + 1]; k += kHalfParts) {
+      const double2 v = bh.rowpart[(long long)k * kHalfRows + i % kHalfRows];
+      t.x += v.x;
+      t.y += v.y;
+    }
+    t.x += c.x;
+    t.y += c.y;
+  }
+  part[q][li] = t;
+  __syncthreads();
+  if (q != 0 || i >= n) return;
+#pragma unroll
+  for (int k = 1; k < kHalfParts; ++k) {
+    t.x += part[k][li].x;
+    t.y += part[k][li].y;
+  }
+  if (!cpl.row) {
+    gout[i] = t;
+    return;
+  }
+  cpl.add(t, i, 1, 0);
+  const double2 gn = make_double2(coef * t.x, coef * t.y);
+  if (mode == 0) {
+    const double2 g0 = gin[i];
+    facc[i] = make_double2(g0.x + gn.x, g0.y + gn.y);
+    gout[i] = gn;
+  } else if (mode == 1) {
+    double2 s2 = facc[i];
+    s2.x += gn.x;
+    s2.y += gn.y;
+    facc[i] = s2;
+    gout[i] = gn;
+  } else {
+    const double2 s2 = facc[i];
+    aux_out[i] = make_double2(s2.x + gn.x, s2.y + gn.y);
+  }
+}
+
+// ---------------------------------------------------------------------------
 // box form: dense operator on Gamma.  One workgroup per row; the row of the
 // rows x ncol matrix times [x1; x2] where x1 = the naux boundary variables of
 // the stage (first and second order) or absent (naux = 0, zeroth), x2 = E y.
@@ -1139,15 +1311,15 @@ __global__ void __launch_bounds__(kBlock) box_gemv_rows_kernel(
 // ---------------------------------------------------------------------------
 template <typename T>
 __global__ void __launch_bounds__(kBlock) box_gemv_kernel(
-    const double2* __restrict__ mat, int naux, int ncol, int ident, const double2* __restrict__ gin,
-    const typename cpx<T>::t* __restrict__ yin, const int* __restrict__ gamma_lin,
+    const double2* __restrict__ mat, long long ld, int naux, int ncol, int ident, const double2* __restrict__ gin,
+    const typename cpx<T>::t* __restrict__ yin, const int* __restrict__ gamma_lin, BoxCpl<T> cpl,
     double2* __restrict__ gout, double2* __restrict__ facc, double2* __restrict__ aux_out,
     int batch, double coef, int mode) {
   __shared__ double2 red[kBlock];
   const int row = blockIdx.x;
   const int b = blockIdx.y;
   double sr = 0, si = 0;
-  const double2* mrow = mat + (long long)row * ncol;
+  const double2* mrow = mat + row * ld;
   const int j0 = row < ident ? naux : 0;
   for (int j = j0 + threadIdx.x; j < ncol; j += blockDim.x) {
     const double2 m = mrow[j];
@@ -1181,6 +1353,7 @@ __global__ void __launch_bounds__(kBlock) box_gemv_kernel(
     red[0].x += gv.x;
     red[0].y += gv.y;
   }
+  if (cpl.row) cpl.add(red[0], row, batch, b);
   const double2 gn = make_double2(coef * red[0].x, coef * red[0].y);
   if (mode == 0) {
     const double2 g0 = gin[e];
@@ -1416,14 +1589,17 @@ __global__ void __launch_bounds__(kBlock) box_gather_kernel(const typename cpx<T
   out[e] = make_double2((double)v.x, (double)v.y);
 }
 
-__global__ void __launch_bounds__(kBlock) box_epilogue_kernel(const double2* __restrict__ t,
+template <typename T>
+__global__ void __launch_bounds__(kBlock) box_epilogue_kernel(const double2* __restrict__ t, BoxCpl<T> cpl, int nb,
                                                               const double2* __restrict__ gin,
                                                               double2* __restrict__ gout, double2* __restrict__ facc,
                                                               double2* __restrict__ aux_out, long long count,
                                                               double coef, int mode) {
   const long long e = (long long)blockIdx.x * blockDim.x + threadIdx.x;
   if (e >= count) return;
-  const double2 gn = make_double2(coef * t[e].x, coef * t[e].y);
+  double2 te = t[e];
+  if (cpl.row) cpl.add(te, (int)(e / nb), nb, (int)(e % nb));
+  const double2 gn = make_double2(coef * te.x, coef * te.y);
   if (mode == 0) {
     const double2 g0 = gin[e];
     facc[e] = make_double2(g0.x + gn.x, g0.y + gn.y);
@@ -1625,11 +1801,12 @@ hipError_t second_reduced_stage(const abc_launch& L, const abc_scratch& S, const
   // 0 .. 2r is not read, g~ is added)
   const int ld = 3 * r;
   const unsigned rb = (unsigned)((r + kBoxRows - 1) / kBoxRows);
-  abc_launch_kernel(tm, "reduced_operator", box_gemv_rows_kernel, dim3(rb), dim3(kBlock), st,
-                    (const double2*)(L.box_red + (long long)r * ld), r, 0, ld, 0, (const double2*)nullptr,
-                    (const double2*)v, t + r, (double2*)nullptr, (double2*)nullptr, 0.0, kGemvPlain);
-  abc_launch_kernel(tm, "reduced_operator", box_gemv_rows_kernel, dim3(rb), dim3(kBlock), st,
-                    (const double2*)L.box_red, r, 2 * r, ld, r, (const double2*)v, (const double2*)(v + 2LL * r), t,
+  abc_launch_kernel(tm, "reduced_operator", box_gemv_rows_kernel<T>, dim3(rb), dim3(kBlock), st,
+                    (const double2*)(L.box_red + (long long)r * ld), (long long)ld, r, 0, ld, 0,
+                    (const double2*)nullptr, (const double2*)v, BoxCpl<T>{}, t + r, (double2*)nullptr, (double2*)nullptr, 0.0, kGemvPlain);
+  abc_launch_kernel(tm, "reduced_operator", box_gemv_rows_kernel<T>, dim3(rb), dim3(kBlock), st,
+                    (const double2*)L.box_red, (long long)ld, r, 2 * r, ld, r, (const double2*)v,
+                    (const double2*)(v + 2LL * r), BoxCpl<T>{}, t,
                     (double2*)nullptr, (double2*)nullptr, 0.0, kGemvPlain);
   abc_launch_kernel(tm, "reduced_pack", pack2_kernel, dim3(nblocks(r)), dim3(kBlock), st, Tp, (const double2*)t, r);
   const long long lift_threads = (long long)(n + kLiftRows - 1) / kLiftRows * 64;
@@ -1664,7 +1841,7 @@ typedef double gemm_d4 __attribute__((ext_vector_type(4)));
 
 template <int NT>
 __global__ void __launch_bounds__(64 * kGemmSplit) box_gemm_kernel(const double2* __restrict__ op, int rows, int ld,
-                                                                  int na, const double2* __restrict__ x1,
+                                                                  int kt, int na, const double2* __restrict__ x1,
                                                                   const double2* __restrict__ x2, int nb,
                                                                   double2* __restrict__ t) {
   __shared__ double2 red[kGemmSplit][NT][4][64];
@@ -1682,18 +1859,18 @@ __global__ void __launch_bounds__(64 * kGemmSplit) box_gemm_kernel(const double2
   gemm_d4 p1[NT], p2[NT], p3[NT];
 #pragma unroll
   for (int u = 0; u < NT; ++u) p1[u] = p2[u] = p3[u] = gemm_d4{0, 0, 0, 0};
-  for (int k0 = 16 * (ksi * kGemmSplit + w); k0 < ld; k0 += 16 * kGemmSplit * ks) {
+  for (int k0 = 16 * (ksi * kGemmSplit + w); k0 < kt; k0 += 16 * kGemmSplit * ks) {
     double2 a[4];
     double2 b[NT][4];
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
       const int k = k0 + 4 * kq + j;
-      a[j] = (arow_ok && k < ld) ? oprow[k] : make_double2(0, 0);
+      a[j] = (arow_ok && k < kt) ? oprow[k] : make_double2(0, 0);
       const double2* xr = k < na ? x1 + (long long)k * nb : x2 + (long long)(k - na) * nb;
 #pragma unroll
       for (int u = 0; u < NT; ++u) {
         const int col = u * 16 + ar;
-        b[u][j] = (k < ld && col < nb) ? xr[col] : make_double2(0, 0);
+        b[u][j] = (k < kt && col < nb) ? xr[col] : make_double2(0, 0);
       }
     }
 #pragma unroll
@@ -1744,7 +1921,7 @@ __global__ void __launch_bounds__(kBlock) box_gemm_reduce_kernel(const double2* 
 // workgroups per row tile: the split (up to kGemmMaxKs, keeping at least two
 // chunks of 16 k per wave) whose last round of workgroups leaves the fewest
 // compute units idle; 1 unless that gains more than 2 %
-int gemm_k_split(int rows, int ld) {
+int gemm_k_split(int rows, int kt) {
   static int cus = 0;
   if (cus == 0) {
     int dev = 0, n = 0;
@@ -1753,7 +1930,7 @@ int gemm_k_split(int rows, int ld) {
       n = 256;
     cus = n;
   }
-  const long long tiles = (rows + 15) / 16, chunks = (ld + 15) / 16;
+  const long long tiles = (rows + 15) / 16, chunks = (kt + 15) / 16;
   int best = 1;
   double best_eff = (double)tiles / (double)(((tiles + cus - 1) / cus) * cus);
   for (int ks = 2; ks <= kGemmMaxKs; ++ks) {
@@ -1768,19 +1945,20 @@ int gemm_k_split(int rows, int ld) {
   return best;
 }
 
-// T = Op [X1; X2] for nb <= 64 orbitals (one to four column tiles); part
+// T = Op [X1; X2] for nb <= 64 orbitals (one to four column tiles), Op the
+// first kt columns of a matrix of row stride ld, X1 of na rows; part
 // (box_gemm_part_elems(rows nb) elements, or null) holds the partial
 // products when K is split over workgroups
-hipError_t box_gemm(abc_timer* tm, const double2* op, int rows, int ld, int na, const double2* x1,
+hipError_t box_gemm(abc_timer* tm, const double2* op, int rows, int ld, int kt, int na, const double2* x1,
                     const double2* x2, int nb, double2* t, double2* part, hipStream_t st) {
-  const int ks = part ? gemm_k_split(rows, ld) : 1;
+  const int ks = part ? gemm_k_split(rows, kt) : 1;
   const dim3 g((unsigned)((rows + 15) / 16), (unsigned)ks), b(64 * kGemmSplit);
   const int nt = (nb + 15) / 16;
   double2* out = ks > 1 ? part : t;
-  if (nt == 1) abc_launch_kernel(tm, "box_gemm", box_gemm_kernel<1>, g, b, st, op, rows, ld, na, x1, x2, nb, out);
-  else if (nt == 2) abc_launch_kernel(tm, "box_gemm", box_gemm_kernel<2>, g, b, st, op, rows, ld, na, x1, x2, nb, out);
-  else if (nt == 3) abc_launch_kernel(tm, "box_gemm", box_gemm_kernel<3>, g, b, st, op, rows, ld, na, x1, x2, nb, out);
-  else if (nt == 4) abc_launch_kernel(tm, "box_gemm", box_gemm_kernel<4>, g, b, st, op, rows, ld, na, x1, x2, nb, out);
+  if (nt == 1) abc_launch_kernel(tm, "box_gemm", box_gemm_kernel<1>, g, b, st, op, rows, ld, kt, na, x1, x2, nb, out);
+  else if (nt == 2) abc_launch_kernel(tm, "box_gemm", box_gemm_kernel<2>, g, b, st, op, rows, ld, kt, na, x1, x2, nb, out);
+  else if (nt == 3) abc_launch_kernel(tm, "box_gemm", box_gemm_kernel<3>, g, b, st, op, rows, ld, kt, na, x1, x2, nb, out);
+  else if (nt == 4) abc_launch_kernel(tm, "box_gemm", box_gemm_kernel<4>, g, b, st, op, rows, ld, kt, na, x1, x2, nb, out);
   else return hipErrorInvalidValue;
   if (ks > 1) {
     const long long cnt = (long long)rows * nb;
@@ -2327,46 +2505,65 @@ hipError_t step_staged_t(const abc_launch& L, const abc_scratch& S, void* psi_v,
       double2* merged_gnext = nullptr;
       if (rec || zeroth) {
         double2* gnext = (k == 4) ? nullptr : S.g[(k - 1) & 1];
+        // first order, theorem's pair: the product is B g alone, A E y comes
+        // from A's entries
+        const BoxCpl<T> cpl{L.box_arow, L.box_acol, L.box_aval, (const C*)ycur, L.gamma_lin};
+        const int nbox = L.n_gamma, ld = abc::box_cols(L.order, nbox);
+        const int ncol = cpl.row ? nbox : ld;  // operator columns that the product reads
         if (box && g.batch > 1) {
           // one complex GEMM over the orbitals on the matrix cores: T =
-          // [B | A] [g; E y] (first), the 2n rows of the second order, or
+          // [B | A] [g; E y] (or B g), the 2n rows of the second order, or
           // M E y (zeroth); the operator is read once for all orbitals
           const int n = L.n_gamma, nb = g.batch;
           const int na = abc::box_aux_rows(L.order, n), rows = abc::box_rows(L.order, n);
-          const int ld = abc::box_cols(L.order, n);
           const long long cnt = (long long)rows * nb, ng = (long long)n * nb;
-          abc_launch_kernel(tm, kBoundLabel[k], box_gather_kernel<T>, dim3(nblocks(ng)), dim3(kBlock), st,
-                            (const C*)ycur, L.gamma_lin, n, nb, S.bwork[0]);
+          if (!cpl.row)
+            abc_launch_kernel(tm, kBoundLabel[k], box_gather_kernel<T>, dim3(nblocks(ng)), dim3(kBlock), st,
+                              (const C*)ycur, L.gamma_lin, n, nb, S.bwork[0]);
           double2* tout = rec ? S.bwork[1] : S.src;
-          const hipError_t ge = box_gemm(tm, L.box_mat, rows, ld, na, rec ? gcur : nullptr,
+          const hipError_t ge = box_gemm(tm, L.box_mat, rows, ld, ncol, na, rec ? gcur : nullptr,
                                          (const double2*)S.bwork[0], nb, tout, S.bpart, st);
           if (ge != hipSuccess) return ge;
           if (rec)
-            abc_launch_kernel(tm, "box_epilogue", box_epilogue_kernel, dim3(nblocks(cnt)), dim3(kBlock), st,
-                              (const double2*)tout, gcur, gnext, S.facc, aux, cnt, coef, mode);
+            abc_launch_kernel(tm, "box_epilogue", box_epilogue_kernel<T>, dim3(nblocks(cnt)), dim3(kBlock), st,
+                              (const double2*)tout, cpl, nb, gcur, gnext, S.facc, aux, cnt, coef, mode);
         } else if (box && g.batch == 1 && L.box_r > 0 && L.order == ABC_SECOND && S.bpack) {
           // second order in the DtN maps' dominant subspace
           const hipError_t e = second_reduced_stage<T>(L, S, (const C*)ycur, gcur, gnext, aux, coef, mode, st, tm,
                                                        kBoundLabel[k]);
           if (e != hipSuccess) return e;
+        } else if (box && L.box_half.units) {
+          // one orbital, symmetric up to weights: the upper triangle
+          const BoxHalf& bh = L.box_half;
+          const size_t lds = (size_t)(kHalfWaves + 1) * bh.cols * sizeof(double2);
+          if (rec)
+            abc_launch_kernel_lds(tm, kBoundLabel[k], box_half_kernel<T, false>, dim3(bh.nunit), dim3(64 * kHalfWaves),
+                                  lds, st, L.box_mat, (long long)ld, nbox, bh, gcur, (const C*)nullptr, L.gamma_lin);
+          else
+            abc_launch_kernel_lds(tm, kBoundLabel[k], box_half_kernel<T, true>, dim3(bh.nunit), dim3(64 * kHalfWaves),
+                                  lds, st, L.box_mat, (long long)ld, nbox, bh, (const double2*)nullptr, (const C*)ycur,
+                                  L.gamma_lin);
+          abc_launch_kernel(tm, kBoundLabel[k], box_half_finish_kernel<T>, dim3((nbox + kHalfFin - 1) / kHalfFin),
+                            dim3(kHalfParts * kHalfFin), st, bh, nbox, cpl, gcur, rec ? gnext : S.src, S.facc, aux,
+                            coef, mode);
         } else if (box && g.batch == 1 && S.bwork[0] && abc::box_rows(L.order, L.n_gamma) >= kBoxRowsMin) {
           // one orbital, large operator: gather E y, then kBoxRows rows per
           // workgroup (below kBoxRowsMin rows the extra launch and the fewer
           // workgroups cost more than the shared vector loads save)
           const int n = L.n_gamma, rows = abc::box_rows(L.order, n);
-          abc_launch_kernel(tm, kBoundLabel[k], box_gather_kernel<T>, dim3(nblocks(n)), dim3(kBlock), st,
-                            (const C*)ycur, L.gamma_lin, n, 1, S.bwork[0]);
-          abc_launch_kernel(tm, kBoundLabel[k], box_gemv_rows_kernel, dim3((rows + kBoxRows - 1) / kBoxRows),
-                            dim3(kBlock), st, (const double2*)L.box_mat, rows, abc::box_aux_rows(L.order, n),
-                            abc::box_cols(L.order, n), L.order == ABC_SECOND ? n : 0, gcur,
-                            (const double2*)S.bwork[0], rec ? gnext : S.src, S.facc, aux, coef, mode);
+          if (!cpl.row)
+            abc_launch_kernel(tm, kBoundLabel[k], box_gather_kernel<T>, dim3(nblocks(n)), dim3(kBlock), st,
+                              (const C*)ycur, L.gamma_lin, n, 1, S.bwork[0]);
+          abc_launch_kernel(tm, kBoundLabel[k], box_gemv_rows_kernel<T>, dim3((rows + kBoxRows - 1) / kBoxRows),
+                            dim3(kBlock), st, (const double2*)L.box_mat, (long long)ld, rows,
+                            abc::box_aux_rows(L.order, n), ncol, L.order == ABC_SECOND ? n : 0, gcur,
+                            (const double2*)S.bwork[0], cpl, rec ? gnext : S.src, S.facc, aux, coef, mode);
         } else if (box) {
           const int n = L.n_gamma;
           dim3 grid(abc::box_rows(L.order, n), g.batch);
-          abc_launch_kernel(tm, kBoundLabel[k], box_gemv_kernel<T>, grid, dim3(kBlock), st, L.box_mat,
-                            abc::box_aux_rows(L.order, n), abc::box_cols(L.order, n),
-                            L.order == ABC_SECOND ? n : 0, gcur, ycur, L.gamma_lin,
-                            rec ? gnext : S.src, S.facc, aux, g.batch, coef, mode);
+          abc_launch_kernel(tm, kBoundLabel[k], box_gemv_kernel<T>, grid, dim3(kBlock), st, L.box_mat, (long long)ld,
+                            abc::box_aux_rows(L.order, n), ncol, L.order == ABC_SECOND ? n : 0, gcur, ycur,
+                            L.gamma_lin, cpl, rec ? gnext : S.src, S.facc, aux, g.batch, coef, mode);
         } else if (L.face_fft) {
           const hipError_t e = face_fft_apply<T, R>(L, gcur, rec ? gnext : S.src, S.facc, aux, ycur, a, coef, mode,
                                                     rec ? 1 : 0, st, tm, kBoundLabel[k]);
@@ -2468,6 +2665,38 @@ hipError_t dispatch_diag(const abc_launch& L, double* red, const void* psi, cons
 }
 
 }  // namespace
+
+int box_half_min() { return kHalfMin; }
+
+// columns of a unit: the count, a multiple of 64, that takes the least time as
+// rounds of units (two workgroups fit a compute unit) times columns, a unit's
+// start and end counted as 128 columns
+void box_half_plan(int n, std::vector<int2>& units, std::vector<int>& strip0, int* cols) {
+  const int strips = (n + kHalfRows - 1) / kHalfRows;
+  auto count = [&](int c) {
+    long long k = 0;
+    for (int s = 0; s < strips; ++s) k += (n - s * kHalfRows + c - 1) / c;
+    return k;
+  };
+  double best = 0;
+  for (int c = 64; c <= kHalfColsMax; c += 64) {
+    const double cost = (double)((count(c) + 511) / 512) * (c + 128);
+    if (c == 64 || cost < best) {
+      best = cost;
+      *cols = c;
+    }
+  }
+  units.clear();
+  strip0.assign(1, 0);
+  for (int s = 0; s < strips; ++s) {
+    for (int c = s * kHalfRows; c < n; c += *cols) units.push_back(make_int2(s, c));
+    strip0.push_back((int)units.size());
+  }
+}
+
+size_t box_half_scratch(int n, size_t nunit) {
+  return nunit * kHalfRows + (size_t)((n + kHalfRows - 1) / kHalfRows) * n;
+}
 
 size_t box_gemm_part_elems(size_t result_elems) { return (size_t)kGemmMaxKs * result_elems; }
 

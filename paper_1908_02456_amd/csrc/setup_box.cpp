@@ -652,7 +652,7 @@ abc_status assemble_second(rocblas_handle hnd, DevBufs& db, double2* out, const 
 
 abc_status build_box_ops(const abc_params& p, double2** mat_dev, double2** q_dev, int* n_gamma,
                          std::vector<int>& gamma_lin, double* spectral_bound, int* subspace_dim, BoxReduced* reduced,
-                         std::string& err) {
+                         BoxCoupling* coupling, std::string& err) {
   *mat_dev = nullptr;
   *q_dev = nullptr;
   BoxGeom bg = box_geometry(p);
@@ -696,6 +696,16 @@ abc_status build_box_ops(const abc_params& p, double2** mat_dev, double2** q_dev
     std::vector<int> hij;
     std::vector<double2> hval;
     gamma_sigma_product(bg, hij, hval);
+    if (coupling && !(p.s2 > 0)) {
+      // entries come sorted by row, then column
+      coupling->row.assign(n + 1, 0);
+      for (size_t e = 0; e < hval.size(); ++e) {
+        ++coupling->row[hij[2 * e] + 1];
+        coupling->col.push_back(hij[2 * e + 1]);
+        coupling->val.push_back(hval[e].x);
+      }
+      for (int i = 0; i < n; ++i) coupling->row[i + 1] += coupling->row[i];
+    }
     int* dij = nullptr;
     double2* dval = nullptr;
     if (st == ABC_OK && (st = upload(db, &dij, hij, err)) == ABC_OK) st = upload(db, &dval, hval, err);
