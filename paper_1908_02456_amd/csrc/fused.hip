@@ -37,9 +37,11 @@
 #include <type_traits>
 #include <utility>
 
+#include "device_util.h"
 #include "fused.h"
 
 using abc::Geometry;
+using namespace abc_dev;
 
 namespace {
 
@@ -70,43 +72,8 @@ __device__ __forceinline__ C czero() {
   return z;
 }
 
-// Workgroup barrier ordering LDS only.  __syncthreads() also waits for every
-// outstanding global load (vmcnt(0)), which would drain the next plane's
-// prefetch at each barrier; here only LDS traffic (lgkmcnt) is waited for.
-// The empty asm statements keep the compiler from moving memory accesses
-// across the barrier; loads still in flight are waited for where their
-// registers are first used.
-__device__ __forceinline__ void sync_lds() {
-  asm volatile("" ::: "memory");
-  __builtin_amdgcn_s_waitcnt(0xC07F);  // gfx9 encoding: vmcnt 63, expcnt 7, lgkmcnt 0
-  __builtin_amdgcn_s_barrier();
-  asm volatile("" ::: "memory");
-}
-
 __device__ __forceinline__ double2 cmul(double2 a, double2 b) {
   return make_double2(a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x);
-}
-
-// Raw buffer loads: an offset at or beyond the buffer's size returns zero,
-// which is how halo cells outside the box read as zero without a select on
-// the loaded value (a select would force the wait right after the load).
-// Buffers are limited to below 4 GiB (checked on the host).
-constexpr unsigned kOob = 0xFFFFFFF0u;
-
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void* p, unsigned bytes) {
-  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), (short)0, (int)bytes, 0x00020000);
-}
-__device__ __forceinline__ void bload(__amdgpu_buffer_rsrc_t r, unsigned off, double2& v) {
-  v = __builtin_bit_cast(double2, __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, 0));
-}
-__device__ __forceinline__ void bload(__amdgpu_buffer_rsrc_t r, unsigned off, float2& v) {
-  v = __builtin_bit_cast(float2, __builtin_amdgcn_raw_buffer_load_b64(r, off, 0, 0));
-}
-__device__ __forceinline__ void bload(__amdgpu_buffer_rsrc_t r, unsigned off, double& v) {
-  v = __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(r, off, 0, 0));
-}
-__device__ __forceinline__ void bload(__amdgpu_buffer_rsrc_t r, unsigned off, float& v) {
-  v = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, off, 0, 0));
 }
 
 // Neighbouring lanes' values by DPP (no LDS traffic): lane i receives lane
@@ -229,15 +196,15 @@ __device__ __forceinline__ void fused2_body(const typename cpx<T>::t* __restrict
   // first-order face data in LDS (sizes in double2; 1 = unused)
   constexpr int NXG = FO ? 2 * FP * FR : 1, NYG = FO ? FP * kCols : 1;
   constexpr int NVX = FO ? 2 * TY * 2 : 1, NVY = FO ? 2 * kCols : 1;
-  // Rows published for the y/x neighbours: the stage-1 inputs w of every row
+  // Rows published for the y neighbours (the x neighbours come by lane shifts): the stage-1 inputs w of every row
   // and the stage-1 outputs s1 of rows 1 .. ROWS-2 (the only rows stage 2
   // reads).  Double-buffered (one barrier per plane) when both buffers fit in
   // the 160 KiB of LDS beside the face data.
-  constexpr int kPlaneBytes = (2 * ROWS - 2) * 2 * 66 * (int)sizeof(C);
+  constexpr int kPlaneBytes = (2 * ROWS - 2) * 2 * 64 * (int)sizeof(C);
   constexpr int kFaceBytes = 16 * (NXG + NYG + NVX + NVY);
   constexpr int DBN = 2 * kPlaneBytes + kFaceBytes <= 160 * 1024 ? 2 : 1;
-  __shared__ C plw[DBN][ROWS][2][66];
-  __shared__ C pls[DBN][ROWS - 2][2][66];
+  __shared__ C plw[DBN][ROWS][2][64];
+  __shared__ C pls[DBN][ROWS - 2][2][64];
 
   const int lane = threadIdx.x & 63;
   const int r = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // wave-uniform row
@@ -254,8 +221,8 @@ __device__ __forceinline__ void fused2_body(const typename cpx<T>::t* __restrict
   const int xo = tx * a.xw, xe = min(xo + a.xw, nx);
   const int xb = a.ntx == 1 ? 0 : xo - H;
 
-  for (int i = threadIdx.x; i < DBN * ROWS * 2 * 66; i += NT) (&plw[0][0][0][0])[i] = czero<C>();
-  for (int i = threadIdx.x; i < DBN * (ROWS - 2) * 2 * 66; i += NT) (&pls[0][0][0][0])[i] = czero<C>();
+  for (int i = threadIdx.x; i < DBN * ROWS * 2 * 64; i += NT) (&plw[0][0][0][0])[i] = czero<C>();
+  for (int i = threadIdx.x; i < DBN * (ROWS - 2) * 2 * 64; i += NT) (&pls[0][0][0][0])[i] = czero<C>();
 
   C Yc[2][2], Yb[2][2];  // stage inputs: centre / below (j = 0: w, j = 1: stage-1 output)
   T Vd[2][2];            // V at planes zi-1, zi-2
@@ -288,6 +255,16 @@ __device__ __forceinline__ void fused2_body(const typename cpx<T>::t* __restrict
   };
   fetch(z0 - H);
   const T s1 = T(sA);
+  T cfA[2], cfB[2];  // the stages' coefficients, zero for columns outside the box
+#pragma unroll
+  for (int c = 0; c < 2; ++c) {
+    const int x = xb + 2 * lane + c;
+    const bool in = x >= 0 && x < nx;
+    cfA[c] = in ? T(cA) : T(0);
+    cfB[c] = in ? T(cB) : T(0);
+  }
+  // stage 1 runs on rows 1 .. ROWS-2, stage 2 on the tile's own rows
+  const bool s1on = r >= 1 && r < ROWS - 1, s2on = r >= 2 && r < ROWS - 2;
 
   // First order: the tile's face data, read once before the sweep.
   //  * x faces (both sides), in LDS: the auxiliary input g = av over the
@@ -426,7 +403,7 @@ __device__ __forceinline__ void fused2_body(const typename cpx<T>::t* __restrict
       const int rj = H + j, yj = y0 + j;
       const int xf = side ? nx - 1 : 0, lxf = xf - xb;
       if (lxf >= 0 && lxf < kCols && yj < ny) {
-        const int ci = lxf & 1, li = (lxf >> 1) + 1, rr = rj - 1;
+        const int ci = lxf & 1, li = lxf >> 1, rr = rj - 1;
         const int p1 = zi - 1, p2 = zi - 2;
         if (r == 0 && p1 >= z0 && p1 < z0 + TZ && p1 < nz) {
           const int pl = p1 - (z0 - 1);
@@ -459,12 +436,12 @@ __device__ __forceinline__ void fused2_body(const typename cpx<T>::t* __restrict
           if (x < 0 || x >= nx) continue;
           const double2 g = fyg[(p - z0 + 1) * kCols + lx];
           if (r == 0) {
-            const C wv = pw[ryown][c][lane + 1];
+            const C wv = pw[ryown][c][lane];
             const double2 bg = cmul(a.b0, g), aw = cmul(a.a0, make_double2((double)wv.x, (double)wv.y));
             vy[(p & 1) * kCols + lx] = make_double2(sA * g.x + cA * (bg.x + aw.x), sA * g.y + cA * (bg.y + aw.y));
           } else if (x >= xo && x < xe) {
             const double2 v = vy[(p & 1) * kCols + lx];
-            const C t1 = ps[ryown - 1][c][lane + 1];
+            const C t1 = ps[ryown - 1][c][lane];
             const double2 bv = cmul(a.b0, v), as1 = cmul(a.a0, make_double2((double)t1.x, (double)t1.y));
             aux_out[off_y + p * nx + x] = make_double2(g.x + cB * (bv.x + as1.x), g.y + cB * (bv.y + as1.y));
           }
@@ -479,8 +456,23 @@ __device__ __forceinline__ void fused2_body(const typename cpx<T>::t* __restrict
     // holding a face column use them.  A branch here, or around the adds
     // below, splits the stage code into blocks that the compiler schedules
     // apart, which costs more than the extra reads and selects.
+    // The y neighbours of both stages come from rows published by the previous
+    // iteration; both columns' reads of a stage (without face data, of both
+    // stages) are issued together, and a stage is one block for the scheduler.
+    // With a branch per column each column's reads were waited for on their
+    // own (160^3, us per step: first order 111 against 105, zeroth 90 against
+    // 82, no condition 79 against 73).
     double2 gx[2] = {make_double2(0, 0), make_double2(0, 0)};
     int cxf = -1;
+    C yn[2][2][2];  // [stage][column][below, above]
+    auto read_rows = [&](int k) {
+#pragma unroll
+      for (int c = 0; c < 2; ++c) {
+        // stage 2: rows 1 and ROWS-2 read a neighbour that they will not use
+        yn[k - 1][c][0] = k == 1 ? pw[r - 1][c][lane] : ps[max(r - 2, 0)][c][lane];
+        yn[k - 1][c][1] = k == 1 ? pw[r + 1][c][lane] : ps[min(r, ROWS - 3)][c][lane];
+      }
+    };
     if (ORDER == 3) {
       const int x0 = xb + 2 * lane;
       cxf = (x0 == 0 || x0 == nx - 1) ? 0 : ((x0 + 1 == nx - 1) ? 1 : -1);
@@ -491,25 +483,21 @@ __device__ __forceinline__ void fused2_body(const typename cpx<T>::t* __restrict
       gx[0] = fxg[(side * FP + plc) * FR + rrc];
       gx[1] = vx[(((zi - 2) & 1) * TY + jc) * 2 + side];
     }
-#pragma unroll
-    for (int k = 1; k <= 2; ++k) {
+    // stage k of this wave's row at plane zi - k, into o
+    auto stage = [&](auto kc, const C* abv2, C* o) {
+      constexpr int k = decltype(kc)::value;
       const int zk = zi - k;
-      const T cf = T(k == 1 ? cA : cB);
-      const bool active = r >= k && r < ROWS - k && it >= 2 * k && row_in && zk >= 0 && zk < nz;
-      C o[2];
+      const double cf2 = k == 1 ? cA : cB;
+      // x neighbours outside this lane's pair of columns (zero past the row's
+      // ends; 32 LDS cycles a stage as reads of the published rows)
+      const C xl = dpp_shift_c(Yc[k - 1][1], true), xr = dpp_shift_c(Yc[k - 1][0], false);
 #pragma unroll
       for (int c = 0; c < 2; ++c) {
-        const int lx = 2 * lane + c, x = xb + lx;
-        const bool in = x >= 0 && x < nx;
-        o[c] = czero<C>();
-        if (!active) continue;
-        const C cen = Yc[k - 1][c], bel = Yb[k - 1][c], abv = prev[c];
-        // stage k reads rows r-1 .. r+1 of the input (k = 1) or of t (k = 2)
-        auto row = [&](int rr) -> C(&)[2][66] { return k == 1 ? pw[rr] : ps[rr - 1]; };
-        const C ym = row(r - 1)[c][lane + 1];
-        const C yp = row(r + 1)[c][lane + 1];
-        const C xm = c == 0 ? row(r)[1][lane] : Yc[k - 1][0];
-        const C xp = c == 0 ? Yc[k - 1][1] : row(r)[0][lane + 2];
+        const int x = xb + 2 * lane + c;
+        const C cen = Yc[k - 1][c], bel = Yb[k - 1][c], abv = abv2[c];
+        const C ym = yn[k - 1][c][0], yp = yn[k - 1][c][1];
+        const C xm = c == 0 ? xl : Yc[k - 1][0];
+        const C xp = c == 0 ? Yc[k - 1][1] : xr;
         // base: the factor's input, scaled in stage 1
         C b0 = wm2[c];
         if (k == 1) {
@@ -517,8 +505,8 @@ __device__ __forceinline__ void fused2_body(const typename cpx<T>::t* __restrict
           b0.y = s1 * cen.y;
         }
         const T v = Vd[k - 1][c];
-        T hr = diag * cen.x + off * (bel.x + abv.x + ym.x + yp.x + xm.x + xp.x) + v * cen.x;
-        T hi = diag * cen.y + off * (bel.y + abv.y + ym.y + yp.y + xm.y + xp.y) + v * cen.y;
+        T hr = (diag + v) * cen.x + off * (((bel.x + abv.x) + (ym.x + yp.x)) + (xm.x + xp.x));
+        T hi = (diag + v) * cen.y + off * (((bel.y + abv.y) + (ym.y + yp.y)) + (xm.y + xp.y));
         if (ORDER == 2) {
           // zeroth-order local term nf m0 y, nf = number of faces at the
           // point (0 inside); computed for every lane without a branch, in
@@ -528,17 +516,18 @@ __device__ __forceinline__ void fused2_body(const typename cpx<T>::t* __restrict
           hr += nf * (m0x * cen.x - m0y * cen.y);
           hi += nf * (m0x * cen.y + m0y * cen.x);
         }
-        // columns outside the box stay zero (they are x neighbours)
-        o[c].x = in ? b0.x + cf * hi : T(0);
-        o[c].y = in ? b0.y - cf * hr : T(0);
+        // columns outside the box stay zero (they are x neighbours): their
+        // base is, and their coefficient
+        const T cfc = k == 1 ? cfA[c] : cfB[c];
+        o[c].x = b0.x + cfc * hi;
+        o[c].y = b0.y - cfc * hr;
       }
-      if (ORDER == 3 && active) {
+      if constexpr (ORDER == 3) {
         // First order: the psi stage also sees -i sum_f g_f at face points,
         // with g = the auxiliary input (stage 1) or the auxiliary stage
         // v_f = sA g_f + cA (b g_f + a w) (stage 2), added to the plain stage
         // output as -i cf g.
         const int pl = zk - (z0 - 1);
-        const double cf2 = k == 1 ? cA : cB;
         // x faces: at most one column per lane, its source read above,
         // added without a branch (zero for the other columns)
         {
@@ -613,12 +602,26 @@ __device__ __forceinline__ void fused2_body(const typename cpx<T>::t* __restrict
           }
         }
       }
-#pragma unroll
-      for (int c = 0; c < 2; ++c) {
-        Yb[k - 1][c] = Yc[k - 1][c];
-        Yc[k - 1][c] = prev[c];
-        prev[c] = o[c];
+    };
+    C o1[2], o2[2];
+    o1[0] = o1[1] = o2[0] = o2[1] = czero<C>();
+    if (it >= 2 && s1on) {
+      const bool in1 = row_in && zi >= 1 && zi - 1 < nz, in2 = row_in && zi >= 2 && zi - 2 < nz;
+      read_rows(1);
+      if (!FO && it >= 4) read_rows(2);
+      if (in1) stage(std::integral_constant<int, 1>(), prev, o1);
+      if (it >= 4 && s2on && in2) {
+        if (FO) read_rows(2);
+        stage(std::integral_constant<int, 2>(), o1, o2);
       }
+    }
+#pragma unroll
+    for (int c = 0; c < 2; ++c) {
+      Yb[0][c] = Yc[0][c];
+      Yc[0][c] = prev[c];
+      Yb[1][c] = Yc[1][c];
+      Yc[1][c] = o1[c];
+      prev[c] = o2[c];
     }
 #pragma unroll
     for (int c = 0; c < 2; ++c) {
@@ -639,8 +642,8 @@ __device__ __forceinline__ void fused2_body(const typename cpx<T>::t* __restrict
     if (DBN == 1) sync_lds();
 #pragma unroll
     for (int c = 0; c < 2; ++c) {
-      pwn[r][c][lane + 1] = Yc[0][c];
-      if (r >= 1 && r < ROWS - 1) psn[r - 1][c][lane + 1] = Yc[1][c];
+      pwn[r][c][lane] = Yc[0][c];
+      if (r >= 1 && r < ROWS - 1) psn[r - 1][c][lane] = Yc[1][c];
     }
     sync_lds();
   }
