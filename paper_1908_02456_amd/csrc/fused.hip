@@ -55,6 +55,7 @@ struct FusedArgs {
   int nx, ny, nz;
   int ntx, xw;  // x chunks and output columns per chunk (two-stage kernel)
   int nty, ntiles, tiles_per_xcd;
+  int rev;  // tiles in reverse (tile_of)
   double diag, off;
   double coef[5];
   double sa1, sa2;  // one-pass sweep: base scales of stages 1 and 3 (factored form)
@@ -63,6 +64,18 @@ struct FusedArgs {
   int has_V;
   long long bstride, fstride;  // one-pass sweep over orbitals: elements between orbitals' psi / aux arrays
 };
+
+// Tile of a workgroup.  Consecutive tiles share an XCD and its L2.  The second
+// factor runs over the tiles in reverse (rev): where the state is larger than
+// the last-level cache it starts at the end that the first one wrote last, which
+// is still there: 256^3 c128 336 -> 320 us/step, c64 186 -> 175, 320^3 c128
+// 637 -> 609; 128^3, all of it in the cache, stays at 33.6.  One-pass launches
+// read more than they write and measured no gain from it (118 -> 118 at
+// 256x256x128, 30.2 -> 31.1 at 128^3 c64).
+__device__ __forceinline__ int tile_of(int b, int ntiles, int per_xcd, int rev) {
+  if (per_xcd) return (b & 7) * per_xcd + (rev ? per_xcd - 1 - (b >> 3) : b >> 3);
+  return rev ? ntiles - 1 - b : b;
+}
 
 template <typename C>
 __device__ __forceinline__ C czero() {
@@ -655,8 +668,7 @@ __global__ void __launch_bounds__(64 * (kTY2 + 2 * kHalo2)) fused2_kernel(
     const typename cpx<T>::t* __restrict__ in, typename cpx<T>::t* __restrict__ out, const T* __restrict__ V,
     FusedArgs a, double sA, double cA, double cB, const double2* __restrict__ av, double2* __restrict__ aux_out,
     typename cpx<T>::t* __restrict__ keep, Grad2<typename cpx<T>::t> gr) {
-  int tile = blockIdx.x;
-  if (a.tiles_per_xcd) tile = (blockIdx.x & 7) * a.tiles_per_xcd + (blockIdx.x >> 3);
+  const int tile = tile_of(blockIdx.x, a.ntiles, a.tiles_per_xcd, a.rev);
   fused2_body<T, ORDER, TZ, MODE>(in, out, V, a, sA, cA, cB, av, aux_out, tile, keep, gr);
 }
 
@@ -667,8 +679,7 @@ template <typename T, int ORDER, int TZ>
 __global__ void __launch_bounds__(64 * (kTY2 + 2 * kHalo2)) fused2_batch_kernel(
     const Box2* __restrict__ boxes, int nbox, int total_tiles, int half) {
   using C = typename cpx<T>::t;
-  const int per_xcd = gridDim.x >> 3;
-  const int t = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
+  const int t = tile_of(blockIdx.x, total_tiles, gridDim.x >> 3, half);
   if (t >= total_tiles) return;
   int lo = 0, hi = nbox - 1;
   while (lo < hi) {
@@ -774,8 +785,7 @@ __global__ void __launch_bounds__(64 * rows4<T>()) fused4_kernel(const typename 
     fin += (long long)blockIdx.y * a.fstride;
     fout += (long long)blockIdx.y * a.fstride;
   }
-  int tile = blockIdx.x;
-  if (a.tiles_per_xcd) tile = (blockIdx.x & 7) * a.tiles_per_xcd + (blockIdx.x >> 3);
+  const int tile = tile_of(blockIdx.x, a.ntiles, a.tiles_per_xcd, a.rev);
   const int ty = tile % a.nty, tz = tile / a.nty;
   const int y0 = ty * TY, z0 = tz * TZ;
   const int nx = a.nx, ny = a.ny, nz = a.nz;
@@ -823,7 +833,6 @@ __global__ void __launch_bounds__(64 * rows4<T>()) fused4_kernel(const typename 
   const int nlo = FO ? min(max(H - y0, 1), ROWS) : 1;            // rows 0 .. nlo-1
   const int hstart = FO ? min(max(ny - y0 + H, 0), ROWS - 1) : ROWS - 1;  // rows hstart ..
   const bool helper = r < nlo || r >= hstart;
-  constexpr int NXI = FO ? 4 * 2 * ROWS : 0;           // x-face items
   const int ycol = r == 0 ? 0 : 1;                     // f0 fetch of the y face
   const bool yfetch = FO && yrow >= 0 && (r == 0 || r == ROWS - 1) && 2 * lane + ycol < nx;
 
@@ -1244,9 +1253,10 @@ hipError_t with_order(int order, F f) {
 
 // one factor (half 0: the first, 1: the second) from (in, fin) to (out, fout)
 template <typename T, int MODE>
-hipError_t launch_factor(const abc_launch& L, const FusedArgs& a, int half, const typename cpx<T>::t* in,
+hipError_t launch_factor(const abc_launch& L, FusedArgs a, int half, const typename cpx<T>::t* in,
                          typename cpx<T>::t* out, const double2* fin, double2* fout, const T* V,
                          typename cpx<T>::t* keep, Grad2<typename cpx<T>::t> gr, hipStream_t st, abc_timer* tm) {
+  a.rev = half;
   const dim3 g(a.ntiles), b(64 * (kTY2 + 2 * kHalo2));
   const double sA = half ? a.sa2 : a.sa1, cA = half ? a.coef[2] : a.coef[4], cB = a.coef[1];
   const char* label = half ? "fused2_half_b" : "fused2_half_a";
