@@ -19,8 +19,10 @@
 #include <cmath>
 
 #include "abc_internal.h"
+#include "device_util.h"
 
 using abc::Geometry;
+using namespace abc_dev;
 
 namespace {
 
@@ -222,66 +224,85 @@ __global__ void __launch_bounds__(kBlock) stage_kernel(
 
 // ---------------------------------------------------------------------------
 // the same sweep tiled, for one orbital with zero outside the box: a
-// workgroup owns kTX x-columns, TY = TW J rows (wave w takes rows w, w + TW,
-// ...) and tz planes, and marches z.  Each thread keeps its J points' 2R + 1
-// z-neighbours in a register queue that advances one plane per step, so the
-// tile's interior is read from memory once; the centre plane goes to LDS with
-// R-wide x and y halos (double buffered: one barrier per plane) for the x
-// and y neighbours.  The next plane's loads are issued before the barrier.
+// workgroup owns kTX x-columns, TY rows (one per wave) and tz planes, and
+// marches z.  Each thread keeps its point's 2R + 1 z-neighbours in a register
+// queue that advances one plane per step, so the tile's interior is read from
+// memory once; the centre plane goes to LDS with R-wide x and y halos (double
+// buffered: one barrier per plane) for the x and y neighbours.  Everything the
+// next plane needs (queue front, halos, potential, running sum, boundary
+// sources) is loaded a plane ahead: the loads are issued before the barrier,
+// which orders LDS only, stay in flight through a plane's arithmetic, and are
+// waited for before that plane's stores are issued (a wait after them would
+// wait for the stores too).  Offsets within a plane are fixed per thread; a
+// plane is one buffer descriptor (out of range: zero).
+// us/step (four stages), before and now, complex128 / complex64: Dirichlet R = 1
+// 64^3 31 / 30 -> 17 / 15 and 128^3 73 / 50 -> 72 / 43 (436 MB, 6.1 TB/s); R = 3
+// 128^3 92 / 55 -> 89 / 50, first order 122 / 81 -> 118 / 72, 256^3 916 / 585 ->
+// 838 / 508.  From 128^3 on bound by memory, below by a plane's latency.
 // ---------------------------------------------------------------------------
 constexpr int kTX = 64;
-// one row per thread; planes per tile and rows per tile by radius (measured
-// at 128^3, us per step, first order w = 0: with 4 rows, R = 3 136 with 16
-// planes against 142 with 8 and 193 with 32, R = 2 117 with 8 against 122
-// with 16, two rows per thread 143 and 129; R = 1, w = 8: 136 with 8 planes,
-// 157 with 16, 159 untiled.  Same-box A/B of the row count: R = 3 129.7 with
-// 4 rows x 16 planes, 129.5 with 8 x 16, 122.9 with 8 x 8, 127.9 with 16 x 8;
-// R = 2 106.0 with 4 x 8, 101.5 with 8 x 8: the y halo's share of each
-// plane's loads halves at 8 rows).
-constexpr int kTileJ = 1;
-constexpr int kTiledMinR = 1;
-constexpr int tile_planes(int R) { return 8; }
-// threads per tile (one row each): kTiledBlock(R) / 64 rows
-constexpr int kTiledBlock(int R) { return R >= 2 ? 512 : 256; }
+// threads per tile (one row per wave): at complex128 and R >= 2 the halo is the
+// larger part of what a tile reads, 8 rows (R = 3, 128^3 Dirichlet 89 us/step,
+// with 4 rows 90; 100 x 140 x 77 72, 86); otherwise 4
+template <typename T>
+constexpr int tiled_block(int R) { return R >= 2 && sizeof(T) == 8 ? 512 : 256; }
 
 struct TileGrid {
   int ntx, nty, ntz, tz;
   int tiles_per_xcd;  // tiles / 8 when that divides, for the XCD-aware order; else 0
 };
 
-template <int R, int J>
+template <typename T, int R>
 struct TileShape {
-  static constexpr int NTB = kTiledBlock(R), TW = NTB / 64;  // threads, waves (rows per pass)
-  static constexpr int TY = TW * J, LX = kTX + 2 * R, LY = TY + 2 * R;
+  static constexpr int NTB = tiled_block<T>(R), TY = NTB / 64;  // threads, rows
+  static constexpr int LX = kTX + 2 * R, LY = TY + 2 * R;
   static constexpr int NH = 2 * R * (kTX + TY);        // halo points per plane
   static constexpr int HPT = (NH + NTB - 1) / NTB;     // per thread
 };
 
-template <typename T, int R, int J>
+// position in Gamma (C order of z, y, x) of a boundary-layer point: full planes
+// at both z ends; between them full rows at both y ends and 2R points a row
+__device__ __forceinline__ long long gamma_index(const Geometry& g, int R, int x, int y, int z) {
+  const long long nx = g.nx, ny = g.ny, nz = g.nz, full = nx * ny, part = full - (nx - 2 * R) * (ny - 2 * R);
+  if (z < R) return z * full + y * nx + x;
+  if (z >= nz - R) return R * full + (nz - 2 * R) * part + (z - nz + R) * full + y * nx + x;
+  const long long base = R * full + (z - R) * part;
+  if (y < R) return base + y * nx + x;
+  if (y >= ny - R) return base + R * nx + (ny - 2 * R) * 2 * R + (y - ny + R) * nx + x;
+  return base + R * nx + (long long)(y - R) * 2 * R + (x < R ? x : x - (nx - 2 * R));
+}
+
+// where a stage's boundary source comes from
+enum { kSrcNone = 0, kSrcFaces = 1, kSrcGamma = 2 };
+
+template <typename T, int R, int SRC>
 __device__ __forceinline__ void stage_tiled_body(
     int tile, const TileGrid& tg, const typename cpx<T>::t* __restrict__ yin, typename cpx<T>::t* __restrict__ yout,
     typename cpx<T>::t* __restrict__ acc, typename cpx<T>::t* __restrict__ state, const T* __restrict__ V,
-    const double2* __restrict__ fsrc, const double2* __restrict__ bsrc, const int* __restrict__ point_gamma,
-    const Geometry& g, const StencilCoef& sc, double coef, int mode) {
+    const double2* __restrict__ src, const Geometry& g, const StencilCoef& sc, double coef, int mode,
+    typename cpx<T>::t* lds) {
   using C = typename cpx<T>::t;
-  using S = TileShape<R, J>;
-  __shared__ C pl[2][S::LY][S::LX];
-  const int tx = threadIdx.x & 63, ty = threadIdx.x >> 6;
+  using S = TileShape<T, R>;
+  C(*pl)[S::LY][S::LX] = reinterpret_cast<C(*)[S::LY][S::LX]>(lds);  // two buffers
+  const int tx = threadIdx.x & 63;
+  const int ty = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // wave-uniform row
   const int bx = tile % tg.ntx, by = (tile / tg.ntx) % tg.nty, bz = tile / (tg.ntx * tg.nty);
   const int x0 = bx * kTX, y0 = by * S::TY, z0 = bz * tg.tz;
   const int z1 = min(z0 + tg.tz, g.nz);
   const int nx = g.nx, ny = g.ny, nz = g.nz;
-  const long long sy = nx, sz = (long long)nx * ny;
-  const int x = x0 + tx;
-  auto load = [&](int xx, int yy, int zz) {
-    C v;
-    v.x = 0;
-    v.y = 0;
-    if (xx >= 0 && xx < nx && yy >= 0 && yy < ny && zz >= 0 && zz < nz) v = yin[zz * sz + yy * sy + xx];
-    return v;
-  };
-  // halo point h of a plane: LDS position and box coordinates
-  auto halo_pos = [&](int h, int& ly, int& lx) {
+  const long long sz = (long long)nx * ny;
+  const int x = x0 + tx, y = y0 + ty;
+  const bool in = x < nx && y < ny;
+  const unsigned cplane = (unsigned)sz * (unsigned)sizeof(C), vplane = (unsigned)sz * (unsigned)sizeof(T);
+  const unsigned pt = (unsigned)y * (unsigned)nx + (unsigned)x;
+  const unsigned co = in ? pt * (unsigned)sizeof(C) : kOob, vo = in ? pt * (unsigned)sizeof(T) : kOob;
+  // halo points of this thread: LDS position and offset within the plane
+  int hpos[S::HPT];
+  unsigned ho[S::HPT];
+#pragma unroll
+  for (int hh = 0; hh < S::HPT; ++hh) {
+    const int h = threadIdx.x + hh * S::NTB;
+    int ly, lx;
     if (h < 2 * R * kTX) {
       const int r = h / kTX, c = h % kTX;
       ly = r < R ? r : S::TY + r;
@@ -291,87 +312,152 @@ __device__ __forceinline__ void stage_tiled_body(
       ly = R + r;
       lx = c < R ? c : kTX + c;
     }
-  };
-  C q[J][2 * R + 1];
-  C hv[S::HPT];
-#pragma unroll
-  for (int j = 0; j < J; ++j)
-#pragma unroll
-    for (int i = 0; i <= 2 * R; ++i) q[j][i] = load(x, y0 + ty + S::TW * j, z0 - R + i);
-#pragma unroll
-  for (int hh = 0; hh < S::HPT; ++hh) {
-    const int h = threadIdx.x + hh * S::NTB;
-    int ly = 0, lx = 0;
-    if (h < S::NH) halo_pos(h, ly, lx);
-    hv[hh] = load(x0 - R + lx, y0 - R + ly, h < S::NH ? z0 : -1);
+    const int hx = x0 - R + lx, hy = y0 - R + ly;
+    const bool ok = h < S::NH && hx >= 0 && hx < nx && hy >= 0 && hy < ny;
+    hpos[hh] = h < S::NH ? ly * S::LX + lx : -1;
+    ho[hh] = ok ? ((unsigned)hy * (unsigned)nx + (unsigned)hx) * (unsigned)sizeof(C) : kOob;
   }
+  auto plane = [&](const C* base, int z) { return make_rsrc(base + z * sz, z >= 0 && z < nz ? cplane : 0u); };
+  // boundary sources of the point at plane z: faces in the order x, y, z, or
+  // Gamma's value
+  const bool edge_x = x0 < R || x0 + kTX > nx - R;  // the tile has columns of an x face
+  const bool fx = in && (x < R || x >= nx - R), fy = y < R || y >= ny - R;
+  const int lx = x < R ? x : nx - 1 - x, ly = y < R ? y : ny - 1 - y;
+  const double2 *px = nullptr, *py = nullptr;
+  if (SRC == kSrcFaces) {
+    px = src + g.face_off[x < R ? 0 : 1] + (long long)lx * nz * ny + y;
+    py = src + g.face_off[y < R ? 2 : 3] + (long long)ly * nz * nx + x;
+  }
+  auto sources = [&](int z, double2* v) {
+    v[0] = v[1] = make_double2(0, 0);
+    if (SRC == kSrcFaces) {
+      if (edge_x && fx) v[0] = px[(long long)z * ny];
+      const bool fz = z < R || z >= nz - R;
+      if ((fy || fz) && in)
+        v[1] = fy ? py[(long long)z * nx] : src[g.face_off[z < R ? 4 : 5] + (long long)(z < R ? z : nz - 1 - z) * sz + pt];
+    } else if (SRC == kSrcGamma) {
+      if (in && (fx || fy || z < R || z >= nz - R)) v[0] = src[gamma_index(g, R, x, y, z)];
+    }
+  };
+  const C* prior = mode == 1 ? state : acc;  // the running sum that modes 1 and 2 continue
+  // a plane's data in flight
+  C nq, nh[S::HPT], na;
+  T nv = T(0);
+  double2 ns[2];
+  na.x = 0;
+  na.y = 0;
+  auto fetch = [&](int z) {
+    const __amdgpu_buffer_rsrc_t r = plane(yin, z);
+#pragma unroll
+    for (int hh = 0; hh < S::HPT; ++hh) bload(r, ho[hh], nh[hh]);
+    bload(plane(yin, z + R), co, nq);
+    if (V) bload(make_rsrc(V + z * sz, vplane), vo, nv);
+    if (mode != 0) bload(plane(prior, z), co, na);
+    sources(z, ns);
+  };
+  C q[2 * R + 1], av;  // the plane worked on
+  T vv;
+  double2 sv;
+#pragma unroll
+  for (int i = 0; i < 2 * R; ++i) bload(plane(yin, z0 - R + i), co, q[i]);
+  fetch(z0);
+  // the plane in flight becomes the one worked on; its rows go to LDS
+  auto arrive = [&](int buf) {
+    C(&p)[S::LY][S::LX] = pl[buf];
+    q[2 * R] = nq;
+#pragma unroll
+    for (int hh = 0; hh < S::HPT; ++hh)
+      if (hpos[hh] >= 0) (&p[0][0])[hpos[hh]] = nh[hh];
+    p[R + ty][R + tx] = q[R];
+    vv = nv;
+    av = na;
+    sv = make_double2(ns[0].x + ns[1].x, ns[0].y + ns[1].y);
+  };
+  arrive(0);
+  if (z0 + 1 < z1) fetch(z0 + 1);
+  sync_lds();
   const T diag = T(sc.diag);
   T off[R + 1];
 #pragma unroll
   for (int k = 1; k <= R; ++k) off[k] = T(sc.off[k]);
+  const T cf = T(coef);
   for (int z = z0; z < z1; ++z) {
     const int buf = (z - z0) & 1;
+    C(&p)[S::LY][S::LX] = pl[buf];
+    const C c0 = q[R];
+    T hr = diag * c0.x, hi = diag * c0.y;
 #pragma unroll
-    for (int j = 0; j < J; ++j) pl[buf][R + ty + S::TW * j][R + tx] = q[j][R];
-#pragma unroll
-    for (int hh = 0; hh < S::HPT; ++hh) {
-      const int h = threadIdx.x + hh * S::NTB;
-      if (h < S::NH) {
-        int ly, lx;
-        halo_pos(h, ly, lx);
-        pl[buf][ly][lx] = hv[hh];
+    for (int k = 1; k <= R; ++k) {
+      const C a0 = p[R + ty][R + tx + k], a1 = p[R + ty][R + tx - k];
+      const C a2 = p[R + ty + k][R + tx], a3 = p[R + ty - k][R + tx];
+      const C a4 = q[R + k], a5 = q[R - k];
+      hr += off[k] * (((a0.x + a1.x) + (a2.x + a3.x)) + (a4.x + a5.x));
+      hi += off[k] * (((a0.y + a1.y) + (a2.y + a3.y)) + (a4.y + a5.y));
+      // one k's LDS reads at a time, used up here: left to itself the compiler
+      // moves the sum behind the branches below and holds all 4R values until
+      // then (143 registers against 107 at R = 3, complex128)
+      if (R > 1) {
+        asm volatile("" : "+v"(hr), "+v"(hi));
+        __builtin_amdgcn_sched_barrier(0);
       }
     }
-    T vv[J];
-    C av[J];
-#pragma unroll
-    for (int j = 0; j < J; ++j) {
-      const int yy = y0 + ty + S::TW * j;
-      const long long pnt = z * sz + yy * sy + x;
-      const bool in = x < nx && yy < ny;
-      vv[j] = (V && in) ? V[pnt] : T(0);
-      av[j].x = 0;
-      av[j].y = 0;
-      if (mode != 0 && in) av[j] = mode == 1 ? state[pnt] : acc[pnt];
-    }
-    C nxt[J];
-    const bool more = z + 1 < z1;
-#pragma unroll
-    for (int j = 0; j < J; ++j) nxt[j] = load(x, y0 + ty + S::TW * j, more ? z + R + 1 : -1);
-#pragma unroll
-    for (int hh = 0; hh < S::HPT; ++hh) {
-      const int h = threadIdx.x + hh * S::NTB;
-      int ly = 0, lx = 0;
-      if (h < S::NH) halo_pos(h, ly, lx);
-      hv[hh] = load(x0 - R + lx, y0 - R + ly, (more && h < S::NH) ? z + 1 : -1);
-    }
-    __syncthreads();
-#pragma unroll
-    for (int j = 0; j < J; ++j) {
-      const int yy = y0 + ty + S::TW * j, ly = R + ty + S::TW * j, lx = R + tx;
-      const C c0 = q[j][R];
-      T hr = diag * c0.x, hi = diag * c0.y;
-#pragma unroll
-      for (int k = 1; k <= R; ++k) {
-        const C a0 = pl[buf][ly][lx + k], a1 = pl[buf][ly][lx - k];
-        const C a2 = pl[buf][ly + k][lx], a3 = pl[buf][ly - k][lx];
-        const C a4 = q[j][R + k], a5 = q[j][R - k];
-        hr += off[k] * (((a0.x + a1.x) + (a2.x + a3.x)) + (a4.x + a5.x));
-        hi += off[k] * (((a0.y + a1.y) + (a2.y + a3.y)) + (a4.y + a5.y));
+    hr += vv * c0.x;
+    hi += vv * c0.y;
+    if (SRC != kSrcNone) {
+      if (SRC == kSrcFaces && fy && (z < R || z >= nz - R) && in) {
+        const double2 t = src[g.face_off[z < R ? 4 : 5] + (long long)(z < R ? z : nz - 1 - z) * sz + pt];
+        sv = make_double2(sv.x + t.x, sv.y + t.y);
       }
-      if (x < nx && yy < ny) {
-        const long long pnt = z * sz + yy * sy + x;
-        stage_tail<T, R>(pnt, pnt, 0, x, yy, z, c0, hr, hi, vv[j], av[j], acc, yout, state, V, fsrc, bsrc,
-                         point_gamma, g, coef, mode);
+      hr += T(sv.x);
+      hi += T(sv.y);
+    }
+    C yn, a;
+    yn.x = cf * hi;
+    yn.y = -cf * hr;
+    a.x = (av.x + c0.x) + yn.x;
+    a.y = (av.y + c0.y) + yn.y;
+    if (z + 1 < z1) {
+#pragma unroll
+      for (int i = 0; i < 2 * R; ++i) q[i] = q[i + 1];
+      arrive(buf ^ 1);
+    }
+    if (in) {
+      const long long o = z * sz + pt;
+      if (mode == 0) {
+        yout[o] = yn;
+      } else if (mode == 1) {
+        acc[o] = a;
+        yout[o] = yn;
+      } else {
+        state[o] = a;
       }
     }
-#pragma unroll
-    for (int j = 0; j < J; ++j) {
-#pragma unroll
-      for (int i = 0; i < 2 * R; ++i) q[j][i] = q[j][i + 1];
-      q[j][2 * R] = nxt[j];
-    }
+    if (z + 2 < z1) fetch(z + 2);
+    sync_lds();
   }
+}
+
+// planes per tile: a tile marches tz planes after 2R that only fill its queue,
+// and a compute unit runs its tiles side by side, but no faster than a number
+// of waves that hides a plane's latency allows.  Measured, Dirichlet R = 1,
+// us/step: 32^3 1 plane 13, 8 planes 26; 64^3 2 planes 17, 1 and 8 18 and 26; 96^3
+// 6 planes 36, 8 40, 2 37; 128^3 8 planes 72, 6 76.  R = 3 from 192^3 on 16 planes
+// (first order 400, 8 planes 409); at R = 1 more than 8 gain nothing
+template <typename T, int R>
+int tile_planes(const Geometry& g) {
+  using S = TileShape<T, R>;
+  const long long cols = (long long)((g.nx + kTX - 1) / kTX) * ((g.ny + S::TY - 1) / S::TY);
+  const long long least = R == 1 ? 6 : 12;  // waves per compute unit
+  static const int kPlanes[] = {1, 2, 3, 4, 6, 8, 16};
+  int best = 1;
+  long long cost = 0;
+  for (const int tz : kPlanes) {
+    if (tz > 8 && R == 1) break;
+    const long long tiles = cols * ((g.nz + tz - 1) / tz);
+    const long long c = std::max(least, (tiles + 255) / 256 * S::TY) * (tz + 2 * R);
+    if (cost == 0 || c < cost) best = tz, cost = c;
+  }
+  return best;
 }
 
 inline TileGrid make_tile_grid(const Geometry& g, int TY, int tz) {
@@ -389,14 +475,14 @@ __device__ __forceinline__ int xcd_tile(int bid, const TileGrid& tg) {
   return tg.tiles_per_xcd ? (bid & 7) * tg.tiles_per_xcd + (bid >> 3) : bid;
 }
 
-template <typename T, int R, int J>
-__global__ void __launch_bounds__(kTiledBlock(R)) stage_tiled_kernel(
+template <typename T, int R, int SRC>
+__global__ void __launch_bounds__(tiled_block<T>(R), 4) stage_tiled_kernel(
     TileGrid tg, const typename cpx<T>::t* __restrict__ yin, typename cpx<T>::t* __restrict__ yout,
     typename cpx<T>::t* __restrict__ acc, typename cpx<T>::t* __restrict__ state, const T* __restrict__ V,
-    const double2* __restrict__ fsrc, const double2* __restrict__ bsrc, const int* __restrict__ point_gamma,
-    Geometry g, StencilCoef sc, double coef, int mode) {
-  stage_tiled_body<T, R, J>(xcd_tile(blockIdx.x, tg), tg, yin, yout, acc, state, V, fsrc, bsrc, point_gamma, g,
-                            sc, coef, mode);
+    const double2* __restrict__ src, Geometry g, StencilCoef sc, double coef, int mode) {
+  using S = TileShape<T, R>;
+  __shared__ typename cpx<T>::t lds[2 * S::LY * S::LX];
+  stage_tiled_body<T, R, SRC>(xcd_tile(blockIdx.x, tg), tg, yin, yout, acc, state, V, src, g, sc, coef, mode, lds);
 }
 
 // ---------------------------------------------------------------------------
@@ -420,11 +506,20 @@ __device__ __forceinline__ void face_body(
   while (e >= g.face_off[f + 1]) ++f;
   const long long r = e - g.face_off[f];
   const int n1 = g.face_n1[f], n2 = g.face_n2[f];
-  const int b = (int)(r % B);
-  const long long q = r / B;
-  const int t2 = (int)(q % n2);
-  const int t1 = (int)((q / n2) % n1);
-  const int l = (int)(q / ((long long)n1 * n2));
+  int b, t1, t2, l;
+  if (g.face_off[6] <= 0x7fffffffLL) {  // 32-bit index arithmetic, as in stage_body
+    const unsigned ur = (unsigned)r, uq = ur / (unsigned)B, u1 = uq / (unsigned)n2, ul = u1 / (unsigned)n1;
+    b = (int)(ur - uq * (unsigned)B);
+    t2 = (int)(uq - u1 * (unsigned)n2);
+    t1 = (int)(u1 - ul * (unsigned)n1);
+    l = (int)ul;
+  } else {
+    b = (int)(r % B);
+    const long long q = r / B;
+    t2 = (int)(q % n2);
+    t1 = (int)((q / n2) % n1);
+    l = (int)(q / ((long long)n1 * n2));
+  }
   const int K = 2 * w + 1;
   double sr = 0, si = 0;
   const int j1lo = max(0, t1 - w), j1hi = min(n1 - 1, t1 + w);
@@ -486,109 +581,183 @@ __global__ void __launch_bounds__(kBlock) face_kernel(
 }
 
 // Face-form boundary operator with a window (w >= 2), one orbital: the same
-// sum as face_kernel, tiled.  A workgroup computes a kFT x kFT tile of one
-// face layer l.  The input it needs ((kFT + 2w)^2 points of each source
-// layer, zero outside the face) and the taps are staged in LDS once; a tap
-// read is the same address for the whole wave.  Each output is summed by
-// kFSplit threads over interleaved tap rows and combined in LDS: the faces
-// are small (6 n^2 outputs), and one thread per output leaves too few waves
-// to hide the latency of the multiply-add chains.  The first order's local
-// A E y term and the stage update follow as in face_kernel.
-constexpr int kFT = 16, kFSplit = 4, kFBlock = kFT * kFT * kFSplit;  // 16 x 16 outputs, 4 threads each
-constexpr int kFaceInMax = 3072, kFaceTapMax = 1024;                  // LDS, in double2
-inline bool face_tiled_ok(int R, int w, int batch) {
+// sum as face_body, tiled.  A workgroup computes a kFT x kFT tile of one face
+// layer l.  The input it needs ((kFT + 2w)^2 points of a source layer, zero
+// outside the face) and the taps are staged in LDS.  A lane holds the four
+// outputs t1 = 4 (lane / 16) + 0..3 of one column t2 and a wave takes every
+// NW-th tap column: down a column, input row i meets the taps i .. i - 3, three
+// of which the row before has loaded already, so that 16 multiply-adds come
+// with two LDS reads, which are a group of four rows ahead.  The taps stand
+// between rows of zeros in place of range checks.  The waves' sums are combined
+// in LDS.
+// w = 8 at 128^3, first order, complex128 / complex64, us/step with the sweep:
+// 135 / 118 with one output per lane, range checks and a launch of its own, now
+// 99 / 78; w = 2 104 / 87 -> 88 / 60, w = 15 261 / 245 -> 158 / 148.
+// The first order's local A E y term and the stage update follow as in
+// face_body.
+constexpr int kFT = 16;
+inline size_t face_window_lds(int w, int threads) {
+  const int S = kFT + 2 * w, K = 2 * w + 1, I = (K + 6) & ~3;
+  return (size_t)std::max((S + 3) * S + K * (I + 3), threads / 64 * kFT * kFT) * sizeof(double2);
+}
+inline bool face_window_ok(int R, int w, int batch) {
   const int K = 2 * w + 1, S = kFT + 2 * w;
-  return batch == 1 && w >= 2 && R * S * S <= kFaceInMax && R * K * K <= kFaceTapMax;
+  return batch == 1 && w >= 2 && R * S * S <= 3072 && R * K * K <= 1024;
+}
+// tiles of all faces and layers
+inline int face_window_tiles(const Geometry& g, int R) {
+  int n = 0;
+  for (int f = 0; f < 6; ++f) n += ((g.face_n1[f] + kFT - 1) / kFT) * ((g.face_n2[f] + kFT - 1) / kFT) * R;
+  return n;
 }
 
-template <typename T, int R>
-__global__ void __launch_bounds__(kFBlock) face_tiled_kernel(
-    const double2* __restrict__ gin, double2* __restrict__ gout, double2* __restrict__ facc,
-    double2* __restrict__ aux_out, const typename cpx<T>::t* __restrict__ yin,
-    const double2* __restrict__ ker, LocalBlock a, Geometry g, int w, double coef, int mode, int first) {
-  __shared__ double2 tin[kFaceInMax];
-  __shared__ double2 tap[kFaceTapMax];
-  __shared__ double2 part[kFSplit - 1][kFT * kFT];
-  const int f = blockIdx.y / R, l = blockIdx.y - f * R;
+template <typename T, int R, int NTB>
+__device__ __forceinline__ void face_window_body(
+    int tile, const double2* __restrict__ gin, double2* __restrict__ gout, double2* __restrict__ facc,
+    double2* __restrict__ aux_out, const typename cpx<T>::t* __restrict__ yin, const double2* __restrict__ ker,
+    const LocalBlock& a, const Geometry& g, int w, double coef, int mode, int first, double2* tin) {
+  constexpr int NW = NTB / 64;
+  int f = 0, nt2;
+  for (;; ++f) {
+    nt2 = (g.face_n2[f] + kFT - 1) / kFT;
+    const int nt = ((g.face_n1[f] + kFT - 1) / kFT) * nt2 * R;
+    if (tile < nt) break;
+    tile -= nt;
+  }
+  const int l = tile % R, t1b = tile / R / nt2 * kFT, t2b = tile / R % nt2 * kFT;
   const int n1 = g.face_n1[f], n2 = g.face_n2[f];
-  const int nt2 = (n2 + kFT - 1) / kFT;
-  if ((int)blockIdx.x >= ((n1 + kFT - 1) / kFT) * nt2) return;  // past this face's tiles
-  const int t1b = ((int)blockIdx.x / nt2) * kFT, t2b = ((int)blockIdx.x % nt2) * kFT;
   const int S = kFT + 2 * w, K = 2 * w + 1;
+  // the output that this thread finishes, and what it needs besides the sum
+  const int o = threadIdx.x, o1 = t1b + o / kFT, o2 = t2b + o % kFT;
+  const bool own = o < kFT * kFT && o1 < n1 && o2 < n2;
+  const long long e = g.face_off[f] + ((long long)l * n1 + o1) * n2 + o2;
+  double2 prior = make_double2(0, 0), yv[R];
+  if (own && first) {
+    prior = (mode == 0 ? gin : facc)[e];
+#pragma unroll
+    for (int lp = 0; lp < R; ++lp) {
+      const auto y = yin[face_point(g, f, lp, o1, o2)];
+      yv[lp] = make_double2((double)y.x, (double)y.y);
+    }
+  }
+  const int q = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const int c = lane & 15, r4 = (lane >> 4) * 4;
+  double2 acc[4];
+#pragma unroll
+  for (int j = 0; j < 4; ++j) acc[j] = make_double2(0, 0);
+  const int I = (K + 6) & ~3;  // input rows of an output group, K + 3, in fours
+  double2* tap = tin + (S + 3) * S;
   for (int lp = 0; lp < R; ++lp) {
-    for (int i = threadIdx.x; i < S * S; i += kFBlock) {
-      const int a1 = i / S, a2 = i - a1 * S;
-      const int j1 = t1b - w + a1, j2 = t2b - w + a2;
-      double2 v = make_double2(0, 0);
-      if (j1 >= 0 && j1 < n1 && j2 >= 0 && j2 < n2) {
-        if (first) {
-          v = gin[g.face_off[f] + ((long long)lp * n1 + j1) * n2 + j2];
-        } else {
-          const auto yv = yin[face_point(g, f, lp, j1, j2)];
-          v = make_double2((double)yv.x, (double)yv.y);
+    if (lp > 0) __syncthreads();
+    const double2* gl = gin + g.face_off[f] + (long long)lp * n1 * n2;
+    const double2* kl = ker + (long long)(l * R + lp) * K * K;
+    constexpr int U = 5;  // loads in flight per thread
+    for (int i0 = threadIdx.x; i0 < (S + 3) * S; i0 += U * NTB) {
+      double2 v[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const unsigned i = i0 + u * NTB, a1 = i / (unsigned)S, a2 = i - a1 * S;
+        const int j1 = t1b - w + (int)a1, j2 = t2b - w + (int)a2;
+        v[u] = make_double2(0, 0);
+        if ((int)a1 < S && j1 >= 0 && j1 < n1 && j2 >= 0 && j2 < n2) {
+          if (first) {
+            v[u] = gl[(long long)j1 * n2 + j2];
+          } else {
+            const auto y = yin[face_point(g, f, lp, j1, j2)];
+            v[u] = make_double2((double)y.x, (double)y.y);
+          }
         }
       }
-      tin[(lp * S + a1) * S + a2] = v;
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+        if (i0 + u * NTB < (S + 3) * S) tin[i0 + u * NTB] = v[u];
     }
-    // taps reversed, so that the input and the tap run the same direction
-    const double2* kl = ker + (long long)(l * R + lp) * K * K;
-    for (int i = threadIdx.x; i < K * K; i += kFBlock) tap[lp * K * K + i] = kl[K * K - 1 - i];
-  }
-  __syncthreads();
-  // thread (q, o): output o of the tile, tap rows d1 = q, q + kFSplit, ...
-  const int q = threadIdx.x / (kFT * kFT), o = threadIdx.x - q * (kFT * kFT);
-  const int o1 = o / kFT, o2 = o - o1 * kFT;
-  double sr = 0, si = 0;
-  for (int lp = 0; lp < R; ++lp) {
-    for (int d1 = q; d1 < K; d1 += kFSplit) {
-      const double2* irow = tin + (lp * S + o1 + d1) * S + o2;
-      const double2* krow = tap + lp * K * K + d1 * K;
-#pragma unroll 4
-      for (int d2 = 0; d2 < K; ++d2) {
-        const double2 kv = krow[d2];
-        const double2 v = irow[d2];
-        sr += kv.x * v.x - kv.y * v.y;
-        si += kv.x * v.y + kv.y * v.x;
+    // column d, row t: the tap of input row i and output j with i - j = t - 3
+    for (int i0 = threadIdx.x; i0 < K * (I + 3); i0 += 2 * NTB) {
+      double2 v[2];
+#pragma unroll
+      for (int u = 0; u < 2; ++u) {
+        const unsigned i = i0 + u * NTB, d = i / (unsigned)(I + 3);
+        const int t = (int)(i - d * (I + 3)) - 3;
+        v[u] = make_double2(0, 0);
+        if ((int)d < K && t >= 0 && t < K) v[u] = kl[(K - 1 - t) * K + (K - 1 - (int)d)];
+      }
+#pragma unroll
+      for (int u = 0; u < 2; ++u)
+        if (i0 + u * NTB < K * (I + 3)) tap[i0 + u * NTB] = v[u];
+    }
+    __syncthreads();
+    for (int d = q; d < K; d += NW) {
+      const double2* ic = tin + r4 * S + c + d;
+      const double2* tc = tap + d * (I + 3);
+      double2 t[7], v[4], tn[4], vn[4];  // taps of rows i - 3 .. i + 3, input rows i .. i + 3; the next four
+#pragma unroll
+      for (int u = 0; u < 7; ++u) t[u] = tc[u];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) v[u] = ic[u * S];
+      for (int i = 0; i < I; i += 4) {
+        const int n = i + 4 < I ? i + 4 : i;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          tn[u] = tc[n + 3 + u];
+          vn[u] = ic[(n + u) * S];
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+#pragma unroll
+          for (int j = 0; j < 4; ++j) {
+            const double2 kv = t[3 + u - j];
+            acc[j].x = fma(-kv.y, v[u].y, fma(kv.x, v[u].x, acc[j].x));
+            acc[j].y = fma(kv.y, v[u].x, fma(kv.x, v[u].y, acc[j].y));
+          }
+#pragma unroll
+        for (int u = 0; u < 3; ++u) t[u] = t[4 + u];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          t[3 + u] = tn[u];
+          v[u] = vn[u];
+        }
       }
     }
   }
-  if (q > 0) part[q - 1][o] = make_double2(sr, si);
   __syncthreads();
-  if (q > 0) return;
 #pragma unroll
-  for (int p = 0; p < kFSplit - 1; ++p) {
-    sr += part[p][o].x;
-    si += part[p][o].y;
+  for (int j = 0; j < 4; ++j) tin[q * kFT * kFT + (r4 + j) * kFT + c] = acc[j];
+  __syncthreads();
+  if (!own) return;
+  double sr = 0, si = 0;
+#pragma unroll
+  for (int p = 0; p < NW; ++p) {
+    const double2 v = tin[p * kFT * kFT + o];
+    sr += v.x;
+    si += v.y;
   }
-  const int t1 = t1b + o1, t2 = t2b + o2;
-  if (t1 >= n1 || t2 >= n2) return;
-  const long long e = g.face_off[f] + ((long long)l * n1 + t1) * n2 + t2;
   if (!first) {
     gout[e] = make_double2(sr, si);
     return;
   }
+#pragma unroll
   for (int lp = 0; lp < R; ++lp) {
     const double2 av = a.m[l * R + lp];
-    const auto yv = yin[face_point(g, f, lp, t1, t2)];
-    const double yr = (double)yv.x, yi = (double)yv.y;
-    sr += av.x * yr - av.y * yi;
-    si += av.x * yi + av.y * yr;
+    sr += av.x * yv[lp].x - av.y * yv[lp].y;
+    si += av.x * yv[lp].y + av.y * yv[lp].x;
   }
-  const double2 gn = make_double2(coef * sr, coef * si);
-  if (mode == 0) {
-    const double2 g0 = gin[e];
-    facc[e] = make_double2(g0.x + gn.x, g0.y + gn.y);
-    gout[e] = gn;
-  } else if (mode == 1) {
-    double2 sacc = facc[e];
-    sacc.x += gn.x;
-    sacc.y += gn.y;
-    facc[e] = sacc;
-    gout[e] = gn;
+  const double2 gn = make_double2(coef * sr, coef * si), s = make_double2(prior.x + gn.x, prior.y + gn.y);
+  if (mode == 2) {
+    aux_out[e] = s;
   } else {
-    const double2 sacc = facc[e];
-    aux_out[e] = make_double2(sacc.x + gn.x, sacc.y + gn.y);
+    facc[e] = s;
+    gout[e] = gn;
   }
+}
+
+template <typename T, int R>
+__global__ void __launch_bounds__(256) face_window_kernel(
+    const double2* __restrict__ gin, double2* __restrict__ gout, double2* __restrict__ facc,
+    double2* __restrict__ aux_out, const typename cpx<T>::t* __restrict__ yin,
+    const double2* __restrict__ ker, LocalBlock a, Geometry g, int w, double coef, int mode, int first) {
+  extern __shared__ double2 fwin[];
+  face_window_body<T, R, 256>(blockIdx.x, gin, gout, facc, aux_out, yin, ker, a, g, w, coef, mode, first, fwin);
 }
 
 // A stage and its boundary-variable stage in one launch, for the orders whose
@@ -613,20 +782,38 @@ __global__ void __launch_bounds__(kBlock) stage_face_kernel(
 }
 
 // the same with the tiled stage sweep in the first tg tiles
-template <typename T, int R, int J>
-__global__ void __launch_bounds__(kTiledBlock(R)) stage_face_tiled_kernel(
+template <typename T, int R>
+__global__ void __launch_bounds__(tiled_block<T>(R), 4) stage_face_tiled_kernel(
     TileGrid tg, const typename cpx<T>::t* __restrict__ yin, typename cpx<T>::t* __restrict__ yout,
     typename cpx<T>::t* __restrict__ acc, typename cpx<T>::t* __restrict__ state, const T* __restrict__ V,
-    const double2* __restrict__ fsrc, const int* __restrict__ point_gamma, StencilCoef sc,
-    const double2* __restrict__ gin, double2* __restrict__ gout, double2* __restrict__ facc,
-    double2* __restrict__ aux_out, const double2* __restrict__ ker, LocalBlock a, Geometry g, int w, double coef,
-    int mode, int fmode, unsigned nsb) {
+    const double2* __restrict__ fsrc, StencilCoef sc, const double2* __restrict__ gin, double2* __restrict__ gout,
+    double2* __restrict__ facc, double2* __restrict__ aux_out, const double2* __restrict__ ker, LocalBlock a,
+    Geometry g, int w, double coef, int mode, int fmode, unsigned nsb) {
+  using S = TileShape<T, R>;
+  __shared__ typename cpx<T>::t lds[2 * S::LY * S::LX];
   if (blockIdx.x < nsb)
-    stage_tiled_body<T, R, J>(xcd_tile(blockIdx.x, tg), tg, yin, yout, acc, state, V, fsrc, nullptr, point_gamma,
-                              g, sc, coef, mode);
+    stage_tiled_body<T, R, kSrcFaces>(xcd_tile(blockIdx.x, tg), tg, yin, yout, acc, state, V, fsrc, g, sc, coef, mode,
+                                      lds);
   else
     face_body<T, R>((long long)(blockIdx.x - nsb) * blockDim.x + threadIdx.x, gin, gout, facc, aux_out, yin, ker, a,
                     g, w, coef, fmode, 1);
+}
+
+// the tiled stage sweep with the windowed faces in the first nwb workgroups
+template <typename T, int R>
+__global__ void __launch_bounds__(tiled_block<T>(R), 4) stage_window_tiled_kernel(
+    TileGrid tg, const typename cpx<T>::t* __restrict__ yin, typename cpx<T>::t* __restrict__ yout,
+    typename cpx<T>::t* __restrict__ acc, typename cpx<T>::t* __restrict__ state, const T* __restrict__ V,
+    const double2* __restrict__ fsrc, StencilCoef sc, const double2* __restrict__ gin, double2* __restrict__ gout,
+    double2* __restrict__ facc, double2* __restrict__ aux_out, const double2* __restrict__ ker, LocalBlock a,
+    Geometry g, int w, double coef, int mode, int fmode, unsigned nwb) {
+  extern __shared__ double2 fwin[];
+  if (blockIdx.x < nwb)
+    face_window_body<T, R, tiled_block<T>(R)>(blockIdx.x, gin, gout, facc, aux_out, yin, ker, a, g, w, coef, fmode, 1,
+                                              fwin);
+  else
+    stage_tiled_body<T, R, kSrcFaces>(xcd_tile(blockIdx.x - nwb, tg), tg, yin, yout, acc, state, V, fsrc, g, sc, coef,
+                                      mode, reinterpret_cast<typename cpx<T>::t*>(fwin));
 }
 
 // ---------------------------------------------------------------------------
@@ -772,14 +959,13 @@ __global__ void __launch_bounds__(kBlock) fft_lines_kernel(double2* __restrict__
 
 // rows: line ln = s n1 + t1 (ln < S n1) of pair q is row t1 of slab s
 template <typename T>
-__global__ void __launch_bounds__(kBlock) fft_rows_fwd_kernel(const double2* __restrict__ gin,
-                                                              const typename cpx<T>::t* __restrict__ yin, int first,
-                                                              Geometry g, FaceFFT ff) {
-  extern __shared__ double2 buf[];
-  const int q = blockIdx.y, f0 = 2 * q;
+__device__ __forceinline__ void fft_rows_fwd_body(int bx, int q, const double2* __restrict__ gin,
+                                                  const typename cpx<T>::t* __restrict__ yin, int first,
+                                                  const Geometry& g, const FaceFFT& ff, double2* buf) {
+  const int f0 = 2 * q;
   const int n1 = g.face_n1[f0], n2 = g.face_n2[f0], R = g.R, B = g.batch;
   const int P1 = ff.P1[q], P2 = ff.P2[q], logL = ff.lg2[q], TW = ff.twr[q];
-  const int nline = ff.S[q] * n1, ln0 = blockIdx.x * TW;
+  const int nline = ff.S[q] * n1, ln0 = bx * TW;
   if (ln0 >= nline) return;
   const int tot = TW * P2;
   const double2* tw = stage_twiddles(buf + tot, ff.tw + ff.twoff[q][0], P2, ff.stwr[q]);
@@ -810,17 +996,24 @@ __global__ void __launch_bounds__(kBlock) fft_rows_fwd_kernel(const double2* __r
   }
 }
 
+template <typename T>
+__global__ void __launch_bounds__(kBlock) fft_rows_fwd_kernel(const double2* __restrict__ gin,
+                                                              const typename cpx<T>::t* __restrict__ yin, int first,
+                                                              Geometry g, FaceFFT ff) {
+  extern __shared__ double2 buf[];
+  fft_rows_fwd_body<T>(blockIdx.x, blockIdx.y, gin, yin, first, g, ff, buf);
+}
+
 // columns: workgroup = (slab group side B + b, TW columns from c0); the R
 // layers of the group sit in LDS one after the other ([l][t][k])
-__global__ void __launch_bounds__(kBlock) fft_cols_kernel(Geometry g, FaceFFT ff) {
-  extern __shared__ double2 buf[];
-  const int q = blockIdx.y;
-  const int n1 = g.face_n1[2 * q], R = g.R, B = g.batch;
+template <int R>
+__device__ __forceinline__ void fft_cols_body(int bx, int q, const Geometry& g, const FaceFFT& ff, double2* buf) {
+  const int n1 = g.face_n1[2 * q], B = g.batch;
   const int P1 = ff.P1[q], P2 = ff.P2[q], logL = ff.lg1[q], TW = ff.twc[q];
   const int per = P2 / TW;
   const int lgTW = __ffs(TW) - 1;  // TW is a power of two
-  if ((int)blockIdx.x >= 2 * B * per) return;
-  const int sg = blockIdx.x / per, c0 = (blockIdx.x % per) * TW;
+  if (bx >= 2 * B * per) return;
+  const int sg = bx / per, c0 = (bx % per) * TW;
   const int side = sg / B, b = sg % B;
   const int tot = TW * P1;
   const long long slab = (long long)P1 * P2;
@@ -841,10 +1034,13 @@ __global__ void __launch_bounds__(kBlock) fft_cols_kernel(Geometry g, FaceFFT ff
   for (int e = threadIdx.x; e < tot; e += blockDim.x) {
     const int t = e & (TW - 1), k = e >> lgTW;
     const long long m = (long long)k * P2 + c0 + t;
-    double2 x[abc::kMaxR];
+    double2 x[R];
+#pragma unroll
     for (int lp = 0; lp < R; ++lp) x[lp] = buf[lp * tot + t * P1 + k];
+#pragma unroll
     for (int l = 0; l < R; ++l) {
       double zr = 0, zi = 0;
+#pragma unroll
       for (int lp = 0; lp < R; ++lp) {
         const double2 kv = spec[(long long)(l * R + lp) * slab + m];
         zr += kv.x * x[lp].x - kv.y * x[lp].y;
@@ -865,6 +1061,12 @@ __global__ void __launch_bounds__(kBlock) fft_cols_kernel(Geometry g, FaceFFT ff
   }
 }
 
+template <int R>
+__global__ void __launch_bounds__(kBlock) fft_cols_kernel(Geometry g, FaceFFT ff) {
+  extern __shared__ double2 buf[];
+  fft_cols_body<R>(blockIdx.x, blockIdx.y, g, ff, buf);
+}
+
 // inverse rows of Z (t1 < n1) and the face_kernel epilogue on t2 < n2
 // mode 3 (shell stages of the one-pass sweep, one orbital): gout = alpha base +
 // beta (B x + A E (yin + y2)), base and y2 optional
@@ -875,15 +1077,14 @@ struct FaceAffine {
 };
 
 template <typename T, int R>
-__global__ void __launch_bounds__(kBlock) fft_rows_inv_kernel(
-    const double2* __restrict__ gin, double2* __restrict__ gout, double2* __restrict__ facc,
-    double2* __restrict__ aux_out, const typename cpx<T>::t* __restrict__ yin, LocalBlock a, Geometry g, FaceFFT ff,
-    double coef, int mode, int first, FaceAffine af) {
-  extern __shared__ double2 buf[];
-  const int q = blockIdx.y, f0 = 2 * q;
+__device__ __forceinline__ void fft_rows_inv_body(
+    int bx, int q, const double2* __restrict__ gin, double2* __restrict__ gout, double2* __restrict__ facc,
+    double2* __restrict__ aux_out, const typename cpx<T>::t* __restrict__ yin, const LocalBlock& a, const Geometry& g,
+    const FaceFFT& ff, double coef, int mode, int first, const FaceAffine& af, double2* buf) {
+  const int f0 = 2 * q;
   const int n1 = g.face_n1[f0], n2 = g.face_n2[f0], B = g.batch;
   const int P1 = ff.P1[q], P2 = ff.P2[q], logL = ff.lg2[q], TW = ff.twr[q];
-  const int nline = ff.S[q] * n1, ln0 = blockIdx.x * TW;
+  const int nline = ff.S[q] * n1, ln0 = bx * TW;
   if (ln0 >= nline) return;
   const double2* Z = ff.Z + ff.woff[q];
   const int tot = TW * P2;
@@ -962,6 +1163,15 @@ __global__ void __launch_bounds__(kBlock) fft_rows_inv_kernel(
   }
 }
 
+template <typename T, int R>
+__global__ void __launch_bounds__(kBlock) fft_rows_inv_kernel(
+    const double2* __restrict__ gin, double2* __restrict__ gout, double2* __restrict__ facc,
+    double2* __restrict__ aux_out, const typename cpx<T>::t* __restrict__ yin, LocalBlock a, Geometry g, FaceFFT ff,
+    double coef, int mode, int first, FaceAffine af) {
+  extern __shared__ double2 buf[];
+  fft_rows_inv_body<T, R>(blockIdx.x, blockIdx.y, gin, gout, facc, aux_out, yin, a, g, ff, coef, mode, first, af, buf);
+}
+
 inline int ilog2(int v) {
   int k = 0;
   while ((1 << k) < v) ++k;
@@ -995,6 +1205,28 @@ hipError_t fft2_slabs(double2* base, int P1, int P2, int S, const double2* tw2, 
   return hipGetLastError();
 }
 
+// launch shape of the three passes
+struct FaceFFTPlan {
+  unsigned nr = 0, nc = 0;  // workgroups of the widest pair
+  size_t lr = 0, lc = 0;    // LDS
+  // threads: one per two points of the widest pair, whole waves, at most
+  // kBlock (the four-point passes leave half of them idle, but the extra
+  // waves hide more latency than the smaller blocks save: 204 against 215 us
+  // per step at 128^3)
+  int br = 64, bc = 64;
+  FaceFFTPlan(const Geometry& g, const FaceFFT& ff) {
+    for (int q = 0; q < 3; ++q) {
+      const int n1 = g.face_n1[2 * q];
+      br = std::max(br, std::min(kBlock, (ff.twr[q] * ff.P2[q] / 2 + 63) / 64 * 64));
+      bc = std::max(bc, std::min(kBlock, (g.R * ff.twc[q] * ff.P1[q] / 2 + 63) / 64 * 64));
+      nr = std::max(nr, (unsigned)((ff.S[q] * n1 + ff.twr[q] - 1) / ff.twr[q]));
+      nc = std::max(nc, (unsigned)(2 * g.batch * (ff.P2[q] / ff.twc[q])));
+      lr = std::max(lr, (size_t)(ff.twr[q] * ff.P2[q] + (ff.stwr[q] ? ff.P2[q] / 2 : 0)) * sizeof(double2));
+      lc = std::max(lc, (size_t)(g.R * ff.twc[q] * ff.P1[q] + (ff.stwc[q] ? ff.P1[q] / 2 : 0)) * sizeof(double2));
+    }
+  }
+};
+
 // the face operator of one stage by FFT: gout (first order: coef (B g + A E
 // y) with the Taylor modes of face_kernel; zeroth: M E y)
 template <typename T, int R>
@@ -1003,25 +1235,10 @@ hipError_t face_fft_apply(const abc_launch& L, const double2* gin, double2* gout
                           hipStream_t st, abc_timer* tm, const char* label, FaceAffine af = FaceAffine{}) {
   const FaceFFT& ff = *L.face_fft;
   const Geometry& g = L.g;
-  unsigned nr = 0, nc = 0;
-  size_t lr = 0, lc = 0;
-  // threads: one per two points of the widest pair, whole waves, at most
-  // kBlock (the four-point passes leave half of them idle, but the extra
-  // waves hide more latency than the smaller blocks save: 204 against 215 us
-  // per step at 128^3)
-  int br = 64, bc = 64;
-  for (int q = 0; q < 3; ++q) {
-    const int n1 = g.face_n1[2 * q];
-    br = std::max(br, std::min(kBlock, (ff.twr[q] * ff.P2[q] / 2 + 63) / 64 * 64));
-    bc = std::max(bc, std::min(kBlock, (g.R * ff.twc[q] * ff.P1[q] / 2 + 63) / 64 * 64));
-    nr = std::max(nr, (unsigned)((ff.S[q] * n1 + ff.twr[q] - 1) / ff.twr[q]));
-    nc = std::max(nc, (unsigned)(2 * g.batch * (ff.P2[q] / ff.twc[q])));
-    lr = std::max(lr, (size_t)(ff.twr[q] * ff.P2[q] + (ff.stwr[q] ? ff.P2[q] / 2 : 0)) * sizeof(double2));
-    lc = std::max(lc, (size_t)(g.R * ff.twc[q] * ff.P1[q] + (ff.stwc[q] ? ff.P1[q] / 2 : 0)) * sizeof(double2));
-  }
-  fft_rows_fwd_kernel<T><<<dim3(nr, 3), br, lr, st>>>(gin, yin, first, g, ff);
-  fft_cols_kernel<<<dim3(nc, 3), bc, lc, st>>>(g, ff);
-  abc_launch_kernel_lds(tm, label, fft_rows_inv_kernel<T, R>, dim3(nr, 3), dim3(br), lr, st, gin, gout, facc,
+  const FaceFFTPlan p(g, ff);
+  fft_rows_fwd_kernel<T><<<dim3(p.nr, 3), p.br, p.lr, st>>>(gin, yin, first, g, ff);
+  fft_cols_kernel<R><<<dim3(p.nc, 3), p.bc, p.lc, st>>>(g, ff);
+  abc_launch_kernel_lds(tm, label, fft_rows_inv_kernel<T, R>, dim3(p.nr, 3), dim3(p.br), p.lr, st, gin, gout, facc,
                         aux_out, yin, a, g, ff, coef, mode, first, af);
   return hipGetLastError();
 }
@@ -2472,14 +2689,16 @@ hipError_t step_staged_t(const abc_launch& L, const abc_scratch& S, void* psi_v,
   const LocalBlock a = make_local(L.a_loc);
   const long long nel = g.npts * g.batch;
   const long long nface = g.face_off[6];
-  // one orbital, zero outside the box: the tiled sweep
-  const bool tiled = !PER && g.batch == 1 && R >= kTiledMinR;
-  const TileGrid tg = make_tile_grid(g, TileShape<R, kTileJ>::TY, tile_planes(R));
+  // one orbital, zero outside the box: the tiled sweep (32-bit offsets within
+  // a plane)
+  const bool tiled = !PER && g.batch == 1 && (long long)g.nx * g.ny * (long long)sizeof(C) < (1LL << 32) - 16;
+  const TileGrid tg = make_tile_grid(g, TileShape<T, R>::TY, tile_planes<T, R>(g));
   const unsigned ntile = (unsigned)(tg.ntx * tg.nty * tg.ntz);
   const bool zeroth = L.order == ABC_ZEROTH;
   // boundary variables with their own recurrence: f (first), f and g (second)
   const bool rec = L.order == ABC_FIRST || L.order == ABC_SECOND;
   const bool box = L.form == ABC_FORM_BOX;
+  const bool window = !box && !L.face_fft && face_window_ok(R, L.w, g.batch);
   for (int s = 0; s < n_steps; ++s) {
     // this step's input state (the first step may read it from elsewhere)
     const C* pin = (s == 0 && psi_in) ? static_cast<const C*>(psi_in) : psi;
@@ -2568,19 +2787,17 @@ hipError_t step_staged_t(const abc_launch& L, const abc_scratch& S, void* psi_v,
           const hipError_t e = face_fft_apply<T, R>(L, gcur, rec ? gnext : S.src, S.facc, aux, ycur, a, coef, mode,
                                                     rec ? 1 : 0, st, tm, kBoundLabel[k]);
           if (e != hipSuccess) return e;
-        } else if (rec && L.w == 0) {
-          // local operator: launched with the stage below (with a window the
-          // face work is heavy enough that the combined launch is slower
-          // than two: 128^3, w = 8, 409 against 333 us per step)
+        } else if (rec && (L.w == 0 || (window && tiled))) {
+          // the stage reads only this operator's input: launched with it below,
+          // the local operator's elements behind the tiles (128^3, R = 3: 118
+          // us/step, in front or between 128 to 130), windowed tiles, which take
+          // longer than a stage tile, in front (w = 8: 99, behind 128)
           merged = true;
           merged_gnext = gnext;
-        } else if (face_tiled_ok(R, L.w, g.batch)) {
-          int tiles = 0;
-          for (int f = 0; f < 6; ++f)
-            tiles = std::max(tiles, ((g.face_n1[f] + kFT - 1) / kFT) * ((g.face_n2[f] + kFT - 1) / kFT));
-          abc_launch_kernel(tm, kBoundLabel[k], face_tiled_kernel<T, R>, dim3(tiles, 6 * R), dim3(kFBlock), st, gcur,
-                            rec ? gnext : S.src, S.facc, aux, ycur, L.face_ker, a, g, L.w, coef, mode,
-                            rec ? 1 : 0);
+        } else if (window) {
+          abc_launch_kernel_lds(tm, kBoundLabel[k], face_window_kernel<T, R>, dim3(face_window_tiles(g, R)), dim3(256),
+                                face_window_lds(L.w, 256), st, gcur, rec ? gnext : S.src, S.facc, aux, ycur,
+                                L.face_ker, a, g, L.w, coef, mode, rec ? 1 : 0);
         } else {
           abc_launch_kernel(tm, kBoundLabel[k], face_kernel<T, R>, dim3(nblocks(nface)), dim3(kBlock), st, gcur,
                             rec ? gnext : S.src, S.facc, aux, ycur, L.face_ker, a, g, L.w, coef, mode,
@@ -2596,19 +2813,31 @@ hipError_t step_staged_t(const abc_launch& L, const abc_scratch& S, void* psi_v,
       // `state`; stage 4 finishes it into the new state
       const int smode = k == 2 ? 1 : (k == 4 ? 2 : 0);
       C* state = k == 2 ? const_cast<C*>(pin) : psi;
-      if (merged && tiled) {
-        abc_launch_kernel(tm, kStageLabel[k], stage_face_tiled_kernel<T, R, kTileJ>,
-                          dim3(ntile + (unsigned)((nface + kTiledBlock(R) - 1) / kTiledBlock(R))),
-                          dim3(kTiledBlock(R)), st, tg, ycur, yout, acc, state, Vuse, fsrc, L.point_gamma, sc, fsrc,
-                          merged_gnext, S.facc, aux, L.face_ker, a, g, L.w, coef, smode, mode, ntile);
+      if (merged && window) {
+        const unsigned nwb = (unsigned)face_window_tiles(g, R);
+        using TS = TileShape<T, R>;
+        const size_t lds = std::max(face_window_lds(L.w, TS::NTB), 2 * TS::LY * TS::LX * sizeof(C));
+        abc_launch_kernel_lds(tm, kStageLabel[k], stage_window_tiled_kernel<T, R>, dim3(nwb + ntile), dim3(TS::NTB),
+                              lds, st, tg, ycur, yout, acc, state, Vuse, fsrc, sc, fsrc, merged_gnext, S.facc, aux,
+                              L.face_ker, a, g, L.w, coef, smode, mode, nwb);
+      } else if (merged && tiled) {
+        const unsigned nfb = (unsigned)((nface + tiled_block<T>(R) - 1) / tiled_block<T>(R));
+        abc_launch_kernel(tm, kStageLabel[k], stage_face_tiled_kernel<T, R>, dim3(ntile + nfb),
+                          dim3(tiled_block<T>(R)), st, tg, ycur, yout, acc, state, Vuse, fsrc, sc, fsrc, merged_gnext,
+                          S.facc, aux, L.face_ker, a, g, L.w, coef, smode, mode, ntile);
       } else if (merged) {
         const unsigned nsb = (unsigned)nblocks(nel);
         abc_launch_kernel(tm, kStageLabel[k], stage_face_kernel<T, R, PER>, dim3(nsb + nblocks(nface)), dim3(kBlock),
                           st, ycur, yout, acc, state, Vuse, fsrc, L.point_gamma, sc, fsrc, merged_gnext, S.facc, aux,
                           L.face_ker, a, g, L.w, coef, smode, mode, nsb);
       } else if (tiled) {
-        abc_launch_kernel(tm, kStageLabel[k], stage_tiled_kernel<T, R, kTileJ>, dim3(ntile), dim3(kTiledBlock(R)), st, tg,
-                          ycur, yout, acc, state, Vuse, fsrc, bsrc, L.point_gamma, g, sc, coef, smode);
+        auto sweep = [&](auto kernel) {
+          abc_launch_kernel(tm, kStageLabel[k], kernel, dim3(ntile), dim3(tiled_block<T>(R)), st, tg, ycur, yout, acc,
+                            state, Vuse, fsrc ? fsrc : bsrc, g, sc, coef, smode);
+        };
+        if (fsrc) sweep(stage_tiled_kernel<T, R, kSrcFaces>);
+        else if (bsrc) sweep(stage_tiled_kernel<T, R, kSrcGamma>);
+        else sweep(stage_tiled_kernel<T, R, kSrcNone>);
       } else {
         abc_launch_kernel(tm, kStageLabel[k], stage_kernel<T, R, PER>, dim3(nblocks(nel)), dim3(kBlock), st, ycur,
                           yout, acc, state, Vuse, fsrc, bsrc, L.point_gamma, g, sc, coef, smode);
