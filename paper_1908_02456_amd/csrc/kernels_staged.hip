@@ -16,6 +16,7 @@
 #include <rocblas/rocblas.h>
 
 #include <algorithm>
+#include <functional>
 #include <cmath>
 
 #include "abc_internal.h"
@@ -1172,6 +1173,27 @@ __global__ void __launch_bounds__(kBlock) fft_rows_inv_kernel(
   fft_rows_inv_body<T, R>(blockIdx.x, blockIdx.y, gin, gout, facc, aux_out, yin, a, g, ff, coef, mode, first, af, buf);
 }
 
+// The column pass of a first-order stage's face operator in the first 3 nf
+// workgroups, the stage's tiles behind them: the sweep reads the operator's
+// input only, and the transforms are a few hundred workgroups of LDS passes
+// that leave the memory idle.  Spreading the tiles over the three passes leaves
+// too few in each (128^3, R = 1, complex128: 198 us/step in thirds, 155 here, 176
+// in launches of their own).
+template <typename T, int R>
+__global__ void __launch_bounds__(tiled_block<T>(R), 4) stage_fft_tiled_kernel(
+    TileGrid tg, const typename cpx<T>::t* __restrict__ yin, typename cpx<T>::t* __restrict__ yout,
+    typename cpx<T>::t* __restrict__ acc, typename cpx<T>::t* __restrict__ state, const T* __restrict__ V,
+    const double2* __restrict__ fsrc, StencilCoef sc, Geometry g, FaceFFT ff, double coef, int mode, unsigned nf) {
+  extern __shared__ double2 buf[];
+  if (blockIdx.x < 3 * nf) {
+    const int q = blockIdx.x / nf;
+    fft_cols_body<R>(blockIdx.x - q * nf, q, g, ff, buf);
+  } else {
+    stage_tiled_body<T, R, kSrcFaces>(xcd_tile(blockIdx.x - 3 * nf, tg), tg, yin, yout, acc, state, V, fsrc, g, sc,
+                                      coef, mode, reinterpret_cast<typename cpx<T>::t*>(buf));
+  }
+}
+
 inline int ilog2(int v) {
   int k = 0;
   while ((1 << k) < v) ++k;
@@ -1228,16 +1250,19 @@ struct FaceFFTPlan {
 };
 
 // the face operator of one stage by FFT: gout (first order: coef (B g + A E
-// y) with the Taylor modes of face_kernel; zeroth: M E y)
+// y) with the Taylor modes of face_kernel; zeroth: M E y).  cols launches the
+// column pass in place of its own kernel
 template <typename T, int R>
 hipError_t face_fft_apply(const abc_launch& L, const double2* gin, double2* gout, double2* facc, double2* aux_out,
                           const typename cpx<T>::t* yin, const LocalBlock& a, double coef, int mode, int first,
-                          hipStream_t st, abc_timer* tm, const char* label, FaceAffine af = FaceAffine{}) {
+                          hipStream_t st, abc_timer* tm, const char* label, FaceAffine af = FaceAffine{},
+                          const std::function<void(const FaceFFTPlan&)>& cols = nullptr) {
   const FaceFFT& ff = *L.face_fft;
   const Geometry& g = L.g;
   const FaceFFTPlan p(g, ff);
   fft_rows_fwd_kernel<T><<<dim3(p.nr, 3), p.br, p.lr, st>>>(gin, yin, first, g, ff);
-  fft_cols_kernel<R><<<dim3(p.nc, 3), p.bc, p.lc, st>>>(g, ff);
+  if (cols) cols(p);
+  else fft_cols_kernel<R><<<dim3(p.nc, 3), p.bc, p.lc, st>>>(g, ff);
   abc_launch_kernel_lds(tm, label, fft_rows_inv_kernel<T, R>, dim3(p.nr, 3), dim3(p.br), p.lr, st, gin, gout, facc,
                         aux_out, yin, a, g, ff, coef, mode, first, af);
   return hipGetLastError();
@@ -2720,7 +2745,7 @@ hipError_t step_staged_t(const abc_launch& L, const abc_scratch& S, void* psi_v,
       const double2* fsrc = nullptr;
       const double2* bsrc = nullptr;
       // the boundary-variable stage runs in the stage's launch (its output)
-      bool merged = false;
+      bool merged = false, fft_merged = false;
       double2* merged_gnext = nullptr;
       if (rec || zeroth) {
         double2* gnext = (k == 4) ? nullptr : S.g[(k - 1) & 1];
@@ -2783,6 +2808,9 @@ hipError_t step_staged_t(const abc_launch& L, const abc_scratch& S, void* psi_v,
           abc_launch_kernel(tm, kBoundLabel[k], box_gemv_kernel<T>, grid, dim3(kBlock), st, L.box_mat, (long long)ld,
                             abc::box_aux_rows(L.order, n), ncol, L.order == ABC_SECOND ? n : 0, gcur, ycur,
                             L.gamma_lin, cpl, rec ? gnext : S.src, S.facc, aux, g.batch, coef, mode);
+        } else if (L.face_fft && rec && tiled) {
+          fft_merged = true;  // below, the stage with it
+          merged_gnext = gnext;
         } else if (L.face_fft) {
           const hipError_t e = face_fft_apply<T, R>(L, gcur, rec ? gnext : S.src, S.facc, aux, ycur, a, coef, mode,
                                                     rec ? 1 : 0, st, tm, kBoundLabel[k]);
@@ -2813,7 +2841,17 @@ hipError_t step_staged_t(const abc_launch& L, const abc_scratch& S, void* psi_v,
       // `state`; stage 4 finishes it into the new state
       const int smode = k == 2 ? 1 : (k == 4 ? 2 : 0);
       C* state = k == 2 ? const_cast<C*>(pin) : psi;
-      if (merged && window) {
+      if (fft_merged) {
+        auto cols = [&](const FaceFFTPlan& p) {
+          using TS = TileShape<T, R>;
+          abc_launch_kernel_lds(tm, kStageLabel[k], stage_fft_tiled_kernel<T, R>, dim3(3 * p.nc + ntile),
+                                dim3(TS::NTB), std::max(p.lc, 2 * TS::LY * TS::LX * sizeof(C)), st, tg, ycur, yout,
+                                acc, state, Vuse, fsrc, sc, g, *L.face_fft, coef, smode, p.nc);
+        };
+        const hipError_t e = face_fft_apply<T, R>(L, fsrc, merged_gnext, S.facc, aux, ycur, a, coef, mode, 1, st, tm,
+                                                  kBoundLabel[k], FaceAffine{}, cols);
+        if (e != hipSuccess) return e;
+      } else if (merged && window) {
         const unsigned nwb = (unsigned)face_window_tiles(g, R);
         using TS = TileShape<T, R>;
         const size_t lds = std::max(face_window_lds(L.w, TS::NTB), 2 * TS::LY * TS::LX * sizeof(C));
