@@ -711,7 +711,7 @@ __global__ void __launch_bounds__(64 * (kTY2 + 2 * kHalo2)) fused2_batch_kernel(
 constexpr int kHalo4 = 4;
 template <typename T> struct Tile4;
 template <> struct Tile4<double> { static constexpr int TY = 4, TZ = 16; };
-template <> struct Tile4<float> { static constexpr int TY = 8, TZ = 8; };
+template <> struct Tile4<float> { static constexpr int TY = 8, TZ = 8; };  // TZ: or 2 TZ (pick_depth4)
 
 template <typename T>
 __host__ __device__ constexpr int rows4() { return Tile4<T>::TY + 2 * kHalo4; }
@@ -745,32 +745,39 @@ __host__ __device__ constexpr int level_base4(int j) { return j * rows4<T>() - j
 //  * the z-face plane: one stage at a time is on it, so the row waves run
 //    its auxiliary stage themselves (slots per thread; f0 read at stage 1).
 // So the first-order tile needs ny > ROWS and nz > TZ + 4 (at most one face
-// row and plane per tile), and one plane buffer (two barriers per plane) to
-// fit the slots in LDS.
+// row and plane per tile), and with complex128 one plane buffer (two barriers
+// per plane) to fit the slots in LDS.
 // FULL: every lane's two columns lie in the box (nx == 128); otherwise the
 // stage outputs of columns x >= nx are forced to zero (they are read as the
 // x neighbours of the last column).
-template <typename T, int ORDER, bool FULL, bool DB>
+template <typename T, int ORDER, bool FULL, bool DB, int TZ>
 __global__ void __launch_bounds__(64 * rows4<T>()) fused4_kernel(const typename cpx<T>::t* __restrict__ pin,
                                                                   typename cpx<T>::t* __restrict__ pout,
                                                                   const T* __restrict__ V, FusedArgs a,
                                                                   const double2* __restrict__ fin,
                                                                   double2* __restrict__ fout) {
   using C = typename cpx<T>::t;
-  constexpr int TY = Tile4<T>::TY, TZ = Tile4<T>::TZ, H = kHalo4;
+  constexpr int TY = Tile4<T>::TY, H = kHalo4;
   constexpr int ROWS = rows4<T>();
   constexpr int NT = 64 * ROWS;
   constexpr int ITERS = TZ + 2 * H;
   constexpr int NLR = level_base4<T>(4);  // published rows over the four levels
   constexpr bool FO = ORDER == 3;
+  // complex64: the z-face slots, which only their own thread reads, in
+  // registers, and the 64 KB of LDS go to the second plane buffer (96^3 x 32
+  // 532 -> 487 us/step); the x-face sources ready in the state's type (445 -> 428).
+  // complex128 has neither the registers nor the LDS for these
+  constexpr bool ZREG = sizeof(T) == 4;
+  constexpr bool XE = FO && sizeof(T) == 4;
   // rows as [column parity][lane] (x neighbours come by DPP, so no guard
   // cells); two buffers (DB: one barrier per plane) or one (two barriers)
   __shared__ C pl[DB ? 2 : 1][NLR][2][64];
   // first-order face data (sizes in double2; 1 when unused)
   constexpr int NXF = FO ? 2 * ROWS * ITERS : 1, NXS = FO ? 2 * 4 * 2 * ROWS : 1, NXB = FO ? 2 * ROWS * 4 : 1;
-  constexpr int NYS = FO ? 2 * 4 * 2 * 64 : 1, NYB = FO ? 4 * 2 * 64 : 1, NZC = FO ? ROWS * 2 * 64 * 2 : 1;
+  constexpr int NYS = FO ? 2 * 4 * 2 * 64 : 1, NYB = FO ? 4 * 2 * 64 : 1, NZC = FO && !ZREG ? ROWS * 2 * 64 * 2 : 1;
   __shared__ double2 xf0[NXF];  // [march plane][side][row]        x-face f0
   __shared__ double2 xsrc[NXS];  // [plane parity][stage][side][row] x-face stage inputs A
+  __shared__ C xe[XE ? NXS : 1];  // xsrc / off in the state's type (XE)
   __shared__ double2 xb[NXB];   // [plane & 3][side][row]          x-face bases
   __shared__ double2 ysrc[NYS];  // [plane parity][stage][c][lane]  y-face stage inputs A
   __shared__ double2 yb[NYB];   // [plane & 3][c][lane]            y-face bases
@@ -875,6 +882,11 @@ __global__ void __launch_bounds__(64 * rows4<T>()) fused4_kernel(const typename 
   };
   fetch(z0 - H, true);
   __syncthreads();
+  const double io = 1.0 / a.off;
+  auto put_xe = [&](int i, double2 v) __attribute__((always_inline)) {
+    xe[i].x = T(v.x * io);
+    xe[i].y = T(v.y * io);
+  };
 
   // one face point's auxiliary stage k: A its input, B the carried base,
   // ce the psi stage input there; returns the output and the next base
@@ -951,13 +963,18 @@ __global__ void __launch_bounds__(64 * rows4<T>()) fused4_kernel(const typename 
               const double2 nA = aux_stage(k, in.A, in.B, in.ce, nB);
               if (k < 4) {
                 xsrc[((npar * 4 + k) * 2 + side) * ROWS + row] = nA;
+                if (XE) put_xe(((npar * 4 + k) * 2 + side) * ROWS + row, nA);
                 xb[bi] = nB;
               } else if (row >= H && row < H + TY && zk >= z0 && zk < z0 + TZ) {
                 fout[a.face_off[side] + zk * ny + yy] = nA;
               }
             }
             // the stage-1 input of the next plane (zi): f0
-            if (k == 1) xsrc[((npar * 4 + 0) * 2 + side) * ROWS + row] = xf0[(it * 2 + side) * ROWS + row];
+            if (k == 1) {
+              const double2 f0 = xf0[(it * 2 + side) * ROWS + row];
+              xsrc[((npar * 4 + 0) * 2 + side) * ROWS + row] = f0;
+              if (XE) put_xe(((npar * 4 + 0) * 2 + side) * ROWS + row, f0);
+            }
           }
         }
         // the y-face row: stages [yk0, yk1], both columns of the lane
@@ -998,6 +1015,9 @@ __global__ void __launch_bounds__(64 * rows4<T>()) fused4_kernel(const typename 
     return;
   }
 
+  double2 zA[2], zB[2];  // z-face slots (ZREG)
+#pragma unroll
+  for (int c = 0; c < 2; ++c) zA[c] = zB[c] = make_double2(0, 0);
 #pragma unroll
   for (int it = 0; it < ITERS; ++it) {
     const int zi = z0 - H + it;
@@ -1025,15 +1045,18 @@ __global__ void __launch_bounds__(64 * rows4<T>()) fused4_kernel(const typename 
       if (active) {
         // level k-1 rows r-1, r, r+1 (published at the end of the previous plane)
         const int lb = level_base4<T>(k - 1) - (k - 1);
-        // First order on full rows: the x-face sources -i g A enter as the
-        // x neighbours outside the box of columns 0 and 127, A / off (the
-        // lanes past the wave's ends of the DPP shifts), so that no select is
-        // needed.  Other rows add them below.
+        // First order: the x-face sources -i g A enter as the x neighbours
+        // outside the box of the face columns, A / off: at the low face (and
+        // at the high one on full rows) as the lane past the wave's end of the
+        // DPP shift, else in place of the zero cell past the row's end.
         T e0x = T(0), e0y = T(0), e1x = T(0), e1y = T(0);
-        if (FO && FULL) {
+        if (XE) {
+          const C s0 = xe[((par * 4 + (k - 1)) * 2 + 0) * ROWS + r];
+          const C s1 = xe[((par * 4 + (k - 1)) * 2 + 1) * ROWS + r];
+          e0x = s0.x, e0y = s0.y, e1x = s1.x, e1y = s1.y;
+        } else if (FO) {
           const double2 s0 = xsrc[((par * 4 + (k - 1)) * 2 + 0) * ROWS + r];
           const double2 s1 = xsrc[((par * 4 + (k - 1)) * 2 + 1) * ROWS + r];
-          const double io = 1.0 / a.off;
           e0x = T(s0.x * io), e0y = T(s0.y * io), e1x = T(s1.x * io), e1y = T(s1.y * io);
         }
 #pragma unroll
@@ -1045,7 +1068,14 @@ __global__ void __launch_bounds__(64 * rows4<T>()) fused4_kernel(const typename 
           // x neighbours: the lane's other column, or the neighbouring lane's
           // (a row is one wave, so by DPP)
           C xm, xp;
-          if (FO && FULL) {
+          if (FO && !FULL) {
+            // the high x face's neighbour: the cell past the row's end
+            C q0 = Yc[k - 1][0], q1 = Yc[k - 1][1];
+            if (c == 1 && 2 * lane == nx) q0.x = e1x, q0.y = e1y;
+            if (c == 0 && 2 * lane + 1 == nx) q1.x = e1x, q1.y = e1y;
+            xm = c == 0 ? dpp_shift_edge_c(Yc[k - 1][1], true, e0x, e0y) : Yc[k - 1][0];
+            xp = c == 0 ? q1 : dpp_shift_c(q0, false);
+          } else if (FO) {
             xm = c == 0 ? dpp_shift_edge_c(Yc[k - 1][1], true, e0x, e0y) : Yc[k - 1][0];
             xp = c == 0 ? Yc[k - 1][1] : dpp_shift_edge_c(Yc[k - 1][0], false, e1x, e1y);
           } else {
@@ -1074,21 +1104,6 @@ __global__ void __launch_bounds__(64 * rows4<T>()) fused4_kernel(const typename 
         if (FO) {
           // face sources -i g_k A_f, in FP64
           const double gk = a.coef[5 - k];
-          // x faces on rows that do not fill the wave: every lane reads both
-          // sides' inputs of its row (one address per wave) and adds them
-          // under selects at the face columns
-          if (!FULL) {
-            const double2 s0 = xsrc[((par * 4 + (k - 1)) * 2 + 0) * ROWS + r];
-            const double2 s1 = xsrc[((par * 4 + (k - 1)) * 2 + 1) * ROWS + r];
-#pragma unroll
-            for (int c = 0; c < 2; ++c) {
-              const int x = 2 * lane + c;
-              const double sr = (x == 0 ? s0.x : 0.0) + (x == xh ? s1.x : 0.0);
-              const double si = (x == 0 ? s0.y : 0.0) + (x == xh ? s1.y : 0.0);
-              o[c].x += T(gk * si);
-              o[c].y -= T(gk * sr);
-            }
-          }
           // the tile's y-face row (whole wave)
           if (r == yrow) {
 #pragma unroll
@@ -1106,15 +1121,21 @@ __global__ void __launch_bounds__(64 * rows4<T>()) fused4_kernel(const typename 
               if (!inx[c]) continue;
               const C ce = Yc[k - 1][c];
               const int si = (r * 2 + c) * 128 + lane;  // A at si, base at si + 64
-              const double2 A = k == 1 ? fin[a.face_off[zface] + ybase + 2 * lane + c] : zch[si];
-              const double2 B = k == 1 ? A : zch[si + 64];
+              const double2 A =
+                  k == 1 ? fin[a.face_off[zface] + ybase + 2 * lane + c] : (ZREG ? zA[c] : zch[si]);
+              const double2 B = k == 1 ? A : (ZREG ? zB[c] : zch[si + 64]);
               o[c].x += T(gk * A.y);
               o[c].y -= T(gk * A.x);
               double2 nB;
               const double2 nA = aux_stage(k, A, B, make_double2((double)ce.x, (double)ce.y), nB);
               if (k < 4) {
-                zch[si] = nA;
-                zch[si + 64] = nB;
+                if (ZREG) {
+                  zA[c] = nA;
+                  zB[c] = nB;
+                } else {
+                  zch[si] = nA;
+                  zch[si + 64] = nB;
+                }
               } else if (own_pt) {
                 fout[a.face_off[zface] + ybase + 2 * lane + c] = nA;
               }
@@ -1175,8 +1196,36 @@ void set_factors(const abc_launch& L, FusedArgs& a) {
   a.sa2 = L.fused_a2;
 }
 
+// rounds of workgroups that a launch takes; over many rounds the partly
+// filled last one hardly counts
+double tile_rounds(long long tiles) {
+  const double r = (double)tiles / kTileSlots;
+  return r < 4 ? std::ceil(r) : r;
+}
+
+// planes per tile of the one-pass sweep for `count` boxes in a launch, and the
+// plane iterations its workgroups take one after the other.  complex64: 8 planes
+// give 128^3 its 256 tiles; many boxes fill the chip with 16 as well, which run
+// through 8 halo planes half as often (us/step, 96^3 x 32 first order
+// 428 -> 357, Dirichlet 324 -> 256, 512 x 512 x 128 first order 369 -> 305)
+struct Depth4 {
+  int tz;
+  double iters;
+};
+Depth4 pick_depth4(bool c64, int order, int ny, int nz, long long count) {
+  const int ty = c64 ? Tile4<float>::TY : Tile4<double>::TY, tz0 = c64 ? Tile4<float>::TZ : Tile4<double>::TZ;
+  Depth4 best{0, 0};
+  for (int tz = tz0; tz <= 16; tz *= 2) {
+    if (tz > tz0 && order == ABC_FIRST && nz <= tz + kHalo4) break;  // one z face per tile
+    const double it =
+        tile_rounds(count * ((ny + ty - 1) / ty) * ((nz + tz - 1) / tz)) * (tz + 2 * kHalo4);
+    if (!best.tz || it < best.iters) best = {tz, it};
+  }
+  return best;
+}
+
 template <typename T>
-FusedArgs make_args4(const abc_launch& L) {
+FusedArgs make_args4(const abc_launch& L, int tz) {
   FusedArgs a{};
   a.nx = L.g.nx;
   a.ny = L.g.ny;
@@ -1184,7 +1233,7 @@ FusedArgs make_args4(const abc_launch& L) {
   a.ntx = 1;
   a.xw = a.nx;
   a.nty = (a.ny + Tile4<T>::TY - 1) / Tile4<T>::TY;
-  const int ntz = (a.nz + Tile4<T>::TZ - 1) / Tile4<T>::TZ;
+  const int ntz = (a.nz + tz - 1) / tz;
   a.ntiles = a.nty * ntz;
   a.tiles_per_xcd = (a.ntiles % 8 == 0) ? a.ntiles / 8 : 0;
   const double s = 1.0 / (2.0 * L.h * L.h);
@@ -1295,13 +1344,6 @@ int fused_max_limit(int order, int nz) {
 
 namespace {
 
-// rounds of workgroups that a launch takes; over many rounds the partly
-// filled last one hardly counts
-double tile_rounds(long long tiles) {
-  const double r = (double)tiles / kTileSlots;
-  return r < 4 ? std::ceil(r) : r;
-}
-
 long long tiles2(const FusedBox& b, int tz) {
   const int ntx = b.nx > kCols ? (b.nx + kChunk - 1) / kChunk : 1;
   return (long long)b.count * ntx * ((b.ny + kTY2 - 1) / kTY2) * ((b.nz + tz - 1) / tz);
@@ -1310,34 +1352,33 @@ long long tiles2(const FusedBox& b, int tz) {
 // Whether the one-pass sweep takes less time than two launches of two stages
 // for one orbital in a box that both cover.  Either is estimated as rounds x
 // planes marched x the time of a plane, the latter as measured at 128^3 and
-// around it (us; the first order's one-pass sweep is slower on partial rows):
+// around it (us; the first order's one-pass sweep differs on partial rows):
 //                    two-stage   one-pass
-//   c128 first         1.45        1.65, 1.85 on rows under 128 columns
+//   c128 first         1.45        1.65, 1.70 on rows under 128 columns
 //   c128 zeroth        1.22        1.29
 //   c128 no condition  1.12        1.15
-//   c64  first         1.19        1.52, 1.74
+//   c64  first         1.19        1.48, 1.39
 //   c64  zeroth        0.88        1.20
 //   c64  no condition  0.79        1.02
 // and the two launches not faster than their 2 (2 c + r) bytes per point, at
 // 5.2 TB/s while state, scratch and potential stay in the last-level cache
 // (180 MB) and 4.6 TB/s beyond.  Measured (two-stage / one-pass, us per
 // step): first order c128, 64 x 64 x 128 21.6 / 41.1, 128^3 40.8 / 43.0, 512 x
-// 512 x 128 582 / 730; c64 128^3 33.5 / 28.1; zeroth order c128, 96 x 96 x 128
+// 512 x 128 582 / 730; c64 96^3 25.9 / 25.0, 128^3 35.5 / 26.6; zeroth order c128, 96 x 96 x 128
 // 25.7 / 32.3, 128^3 35.6 / 33.9, 256 x 256 x 128 145 / 128.
 bool onepass_faster(const abc_params& p, const Geometry& g) {
   const bool c64 = p.dtype == ABC_C64, first = p.order == ABC_FIRST, full = p.nx == kCols;
   const int o = first ? 0 : (p.order == ABC_ZEROTH ? 1 : 2);
   constexpr double c2[2][3] = {{1.45, 1.22, 1.12}, {1.19, 0.88, 0.79}};
-  constexpr double c4[2][3] = {{1.65, 1.29, 1.15}, {1.52, 1.20, 1.02}};
+  constexpr double c4[2][3] = {{1.65, 1.29, 1.15}, {1.48, 1.20, 1.02}};
   const FusedBox b{p.nx, p.ny, p.nz, 1};
   const int tz = fused_pick_depth(p.order, 16, {b});
-  const int ty4 = c64 ? Tile4<float>::TY : Tile4<double>::TY, tz4 = c64 ? Tile4<float>::TZ : Tile4<double>::TZ;
-  const long long n4 = (long long)((p.ny + ty4 - 1) / ty4) * ((p.nz + tz4 - 1) / tz4);
   const double n = (double)g.npts, csz = c64 ? 8 : 16;
   const double bytes = 2 * n * 2.5 * csz, rate = n * 2.5 * csz < 180e6 ? 5.2e6 : 4.6e6;
   const double est2 =
       std::max(2 * (tile_rounds(tiles2(b, tz)) * (tz + 2 * kHalo2) + kTileStart) * c2[c64][o], bytes / rate);
-  const double est4 = (tile_rounds(n4) * (tz4 + 2 * kHalo4) + kTileStart) * c4[c64][o] * (first && !full ? 1.13 : 1.0);
+  const double it4 = pick_depth4(c64, p.order, p.ny, p.nz, 1).iters;
+  const double est4 = (it4 + kTileStart) * c4[c64][o] * (first && !full ? (c64 ? 0.94 : 1.03) : 1.0);
   return est4 <= est2;
 }
 
@@ -1509,18 +1550,21 @@ namespace {
 // that the last step writes the caller's buffers.
 template <typename T, int ORDER>
 void launch4(abc_timer* tm, bool full, dim3 g, dim3 b, hipStream_t st, const typename cpx<T>::t* src,
-             typename cpx<T>::t* dst, const T* V, const FusedArgs& a, const double2* fin, double2* fout) {
-  // first order: one plane buffer, so the face slots fit in LDS
-  constexpr bool DB = ORDER != 3;
-  if (full) abc_launch_kernel(tm, "fused_step", fused4_kernel<T, ORDER, true, DB>, g, b, st, src, dst, V, a, fin, fout);
-  else abc_launch_kernel(tm, "fused_step", fused4_kernel<T, ORDER, false, DB>, g, b, st, src, dst, V, a, fin, fout);
+             typename cpx<T>::t* dst, const T* V, const FusedArgs& a, int tz, const double2* fin, double2* fout) {
+  // first order, complex128: one plane buffer, so the face slots fit in LDS
+  constexpr bool DB = ORDER != 3 || sizeof(T) == 4;
+  auto launch = [&](auto kernel) { abc_launch_kernel(tm, "fused_step", kernel, g, b, st, src, dst, V, a, fin, fout); };
+  constexpr int TZ = Tile4<T>::TZ;
+  if (TZ < 16 && tz == 16) launch(full ? fused4_kernel<T, ORDER, true, DB, 16> : fused4_kernel<T, ORDER, false, DB, 16>);
+  else launch(full ? fused4_kernel<T, ORDER, true, DB, TZ> : fused4_kernel<T, ORDER, false, DB, TZ>);
 }
 
 template <typename T>
 hipError_t step4_t(const abc_launch& L, const abc_scratch& S, void* psi_v, double2* aux, const void* V_v, int n,
                    hipStream_t st, abc_timer* tm) {
   using C = typename cpx<T>::t;
-  FusedArgs a = make_args4<T>(L);
+  const int tz = pick_depth4(sizeof(T) == 4, L.order, L.g.ny, L.g.nz, 1).tz;
+  FusedArgs a = make_args4<T>(L, tz);
   a.has_V = V_v != nullptr;
   C* user = static_cast<C*>(psi_v);
   C* scr = static_cast<C*>(S.y[0]);
@@ -1546,12 +1590,12 @@ hipError_t step4_t(const abc_launch& L, const abc_scratch& S, void* psi_v, doubl
     if (L.fused_shell) {
       // the condition-free sweep, then the boundary-shell rounds (new aux,
       // the boundary's correction added to the swept state)
-      launch4<T, 0>(tm, full, g, b, st, src, dst, V, a, nullptr, nullptr);
+      launch4<T, 0>(tm, full, g, b, st, src, dst, V, a, tz, nullptr, nullptr);
       const hipError_t e = launch_shell_rounds(L, L.shell, src, V_v, fsrc, fdst, dst, st, tm);
       if (e != hipSuccess) return e;
-    } else if (L.order == ABC_FIRST) launch4<T, 3>(tm, full, g, b, st, src, dst, V, a, fsrc, fdst);
-    else if (L.order == ABC_ZEROTH) launch4<T, 2>(tm, full, g, b, st, src, dst, V, a, nullptr, nullptr);
-    else launch4<T, 0>(tm, full, g, b, st, src, dst, V, a, nullptr, nullptr);
+    } else if (L.order == ABC_FIRST) launch4<T, 3>(tm, full, g, b, st, src, dst, V, a, tz, fsrc, fdst);
+    else if (L.order == ABC_ZEROTH) launch4<T, 2>(tm, full, g, b, st, src, dst, V, a, tz, nullptr, nullptr);
+    else launch4<T, 0>(tm, full, g, b, st, src, dst, V, a, tz, nullptr, nullptr);
     if (tm) tm->end_step();
     std::swap(src, dst);
     std::swap(fsrc, fdst);
@@ -1565,7 +1609,8 @@ template <typename T>
 hipError_t step4_orbitals(const abc_launch& L1, int B, const void* src, void* dst, const double2* fsrc, double2* fdst,
                           const void* V_v, hipStream_t st, abc_timer* tm) {
   using C = typename cpx<T>::t;
-  FusedArgs a = make_args4<T>(L1);
+  const int tz = pick_depth4(sizeof(T) == 4, L1.order, L1.g.ny, L1.g.nz, B).tz;
+  FusedArgs a = make_args4<T>(L1, tz);
   a.has_V = V_v != nullptr;
   a.bstride = L1.g.npts;
   a.fstride = L1.g.face_off[6];
@@ -1574,9 +1619,9 @@ hipError_t step4_orbitals(const abc_launch& L1, int B, const void* src, void* ds
   const C* s = static_cast<const C*>(src);
   C* d = static_cast<C*>(dst);
   const T* V = static_cast<const T*>(V_v);
-  if (L1.order == ABC_FIRST) launch4<T, 3>(tm, full, g, b, st, s, d, V, a, fsrc, fdst);
-  else if (L1.order == ABC_ZEROTH) launch4<T, 2>(tm, full, g, b, st, s, d, V, a, nullptr, nullptr);
-  else launch4<T, 0>(tm, full, g, b, st, s, d, V, a, nullptr, nullptr);
+  if (L1.order == ABC_FIRST) launch4<T, 3>(tm, full, g, b, st, s, d, V, a, tz, fsrc, fdst);
+  else if (L1.order == ABC_ZEROTH) launch4<T, 2>(tm, full, g, b, st, s, d, V, a, tz, nullptr, nullptr);
+  else launch4<T, 0>(tm, full, g, b, st, s, d, V, a, tz, nullptr, nullptr);
   return hipGetLastError();
 }
 
