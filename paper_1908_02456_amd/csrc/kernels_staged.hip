@@ -831,7 +831,10 @@ __global__ void __launch_bounds__(tiled_block<T>(R), 4) stage_window_tiled_kerne
 //            product with the R x R kernel spectra, and the inverse transform,
 //            written to Z for the rows t1 < n1 only;
 //   inverse rows + epilogue: the inverse transform along t2 of those rows,
-//            then the face_kernel epilogue on t2 < n2.
+//            then the face_kernel epilogue on t2 < n2; where the result is the
+//            next stage's input (first order, all but a call's last stage),
+//            also that input's rows pass, whose lines are at hand (128^3, R = 1, complex128 157 -> 143 us/step,
+//            48^3 71 -> 58).
 // ---------------------------------------------------------------------------
 
 __device__ __forceinline__ double2 cmul(double2 a, double2 b) {
@@ -1081,7 +1084,7 @@ template <typename T, int R>
 __device__ __forceinline__ void fft_rows_inv_body(
     int bx, int q, const double2* __restrict__ gin, double2* __restrict__ gout, double2* __restrict__ facc,
     double2* __restrict__ aux_out, const typename cpx<T>::t* __restrict__ yin, const LocalBlock& a, const Geometry& g,
-    const FaceFFT& ff, double coef, int mode, int first, const FaceAffine& af, double2* buf) {
+    const FaceFFT& ff, double coef, int mode, int first, const FaceAffine& af, int next, double2* buf) {
   const int f0 = 2 * q;
   const int n1 = g.face_n1[f0], n2 = g.face_n2[f0], B = g.batch;
   const int P1 = ff.P1[q], P2 = ff.P2[q], logL = ff.lg2[q], TW = ff.twr[q];
@@ -1147,6 +1150,7 @@ __device__ __forceinline__ void fft_rows_inv_body(
       si += av.x * yi + av.y * yr;
     }
     const double2 gn = make_double2(coef * sr, coef * si);
+    double2 gs = gn;  // the next stage's input
     if (mode == 0) {
       const double2 g0 = gin[fe];
       facc[fe] = make_double2(g0.x + gn.x, g0.y + gn.y);
@@ -1159,7 +1163,24 @@ __device__ __forceinline__ void fft_rows_inv_body(
       gout[fe] = gn;
     } else {
       const double2 s2 = facc[fe];
-      aux_out[fe] = make_double2(s2.x + gn.x, s2.y + gn.y);
+      gs = make_double2(s2.x + gn.x, s2.y + gn.y);
+      aux_out[fe] = gs;
+    }
+    if (next) buf[t * P2 + t2] = gs;
+  }
+  if (!next) return;
+  for (int e = threadIdx.x; e < TW * (P2 - n2); e += blockDim.x) {
+    const int t = e / (P2 - n2), k = n2 + e - t * (P2 - n2);
+    buf[t * P2 + k] = make_double2(0.0, 0.0);
+  }
+  __syncthreads();
+  fft_dif(buf, tw, P2, logL, TW, true);
+  double2* W = ff.W + ff.woff[q];
+  for (int e = threadIdx.x; e < tot; e += blockDim.x) {
+    const int t = e >> logL, k = e & (P2 - 1), ln = ln0 + t;
+    if (ln < nline) {
+      const int sl = ln / n1, t1 = ln - sl * n1;
+      W[((long long)sl * P1 + t1) * P2 + k] = buf[t * P2 + bit_rev(k, logL)];
     }
   }
 }
@@ -1168,9 +1189,10 @@ template <typename T, int R>
 __global__ void __launch_bounds__(kBlock) fft_rows_inv_kernel(
     const double2* __restrict__ gin, double2* __restrict__ gout, double2* __restrict__ facc,
     double2* __restrict__ aux_out, const typename cpx<T>::t* __restrict__ yin, LocalBlock a, Geometry g, FaceFFT ff,
-    double coef, int mode, int first, FaceAffine af) {
+    double coef, int mode, int first, FaceAffine af, int next) {
   extern __shared__ double2 buf[];
-  fft_rows_inv_body<T, R>(blockIdx.x, blockIdx.y, gin, gout, facc, aux_out, yin, a, g, ff, coef, mode, first, af, buf);
+  fft_rows_inv_body<T, R>(blockIdx.x, blockIdx.y, gin, gout, facc, aux_out, yin, a, g, ff, coef, mode, first, af, next,
+                          buf);
 }
 
 // The column pass of a first-order stage's face operator in the first 3 nf
@@ -1251,20 +1273,22 @@ struct FaceFFTPlan {
 
 // the face operator of one stage by FFT: gout (first order: coef (B g + A E
 // y) with the Taylor modes of face_kernel; zeroth: M E y).  cols launches the
-// column pass in place of its own kernel
+// column pass in place of its own kernel; rows_done: W holds the transformed
+// rows of gin already, next: the last pass leaves those of its result there
 template <typename T, int R>
 hipError_t face_fft_apply(const abc_launch& L, const double2* gin, double2* gout, double2* facc, double2* aux_out,
                           const typename cpx<T>::t* yin, const LocalBlock& a, double coef, int mode, int first,
                           hipStream_t st, abc_timer* tm, const char* label, FaceAffine af = FaceAffine{},
-                          const std::function<void(const FaceFFTPlan&)>& cols = nullptr) {
+                          const std::function<void(const FaceFFTPlan&)>& cols = nullptr, bool rows_done = false,
+                          bool next = false) {
   const FaceFFT& ff = *L.face_fft;
   const Geometry& g = L.g;
   const FaceFFTPlan p(g, ff);
-  fft_rows_fwd_kernel<T><<<dim3(p.nr, 3), p.br, p.lr, st>>>(gin, yin, first, g, ff);
+  if (!rows_done) fft_rows_fwd_kernel<T><<<dim3(p.nr, 3), p.br, p.lr, st>>>(gin, yin, first, g, ff);
   if (cols) cols(p);
   else fft_cols_kernel<R><<<dim3(p.nc, 3), p.bc, p.lc, st>>>(g, ff);
   abc_launch_kernel_lds(tm, label, fft_rows_inv_kernel<T, R>, dim3(p.nr, 3), dim3(p.br), p.lr, st, gin, gout, facc,
-                        aux_out, yin, a, g, ff, coef, mode, first, af);
+                        aux_out, yin, a, g, ff, coef, mode, first, af, (int)next);
   return hipGetLastError();
 }
 
@@ -2813,7 +2837,8 @@ hipError_t step_staged_t(const abc_launch& L, const abc_scratch& S, void* psi_v,
           merged_gnext = gnext;
         } else if (L.face_fft) {
           const hipError_t e = face_fft_apply<T, R>(L, gcur, rec ? gnext : S.src, S.facc, aux, ycur, a, coef, mode,
-                                                    rec ? 1 : 0, st, tm, kBoundLabel[k]);
+                                                    rec ? 1 : 0, st, tm, kBoundLabel[k], FaceAffine{}, nullptr,
+                                                    rec && (s > 0 || k > 1), rec && (s + 1 < n_steps || k < 4));
           if (e != hipSuccess) return e;
         } else if (rec && (L.w == 0 || (window && tiled))) {
           // the stage reads only this operator's input: launched with it below,
@@ -2849,7 +2874,8 @@ hipError_t step_staged_t(const abc_launch& L, const abc_scratch& S, void* psi_v,
                                 acc, state, Vuse, fsrc, sc, g, *L.face_fft, coef, smode, p.nc);
         };
         const hipError_t e = face_fft_apply<T, R>(L, fsrc, merged_gnext, S.facc, aux, ycur, a, coef, mode, 1, st, tm,
-                                                  kBoundLabel[k], FaceAffine{}, cols);
+                                                  kBoundLabel[k], FaceAffine{}, cols, s > 0 || k > 1,
+                                                  s + 1 < n_steps || k < 4);
         if (e != hipSuccess) return e;
       } else if (merged && window) {
         const unsigned nwb = (unsigned)face_window_tiles(g, R);
