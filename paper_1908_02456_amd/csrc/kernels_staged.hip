@@ -495,7 +495,11 @@ struct LocalBlock {
   double2 m[abc::kMaxR * abc::kMaxR];
 };
 
-template <typename T, int R>
+// LOCAL: w = 0, first order.  Wide windows wait for the two loads of a tap, four
+// taps at a time: 100 x 140 x 77, w = 76, first order complex128, 7290 -> 5210
+// us/step, complex64 7440 -> 4740; 48^3 x 8, w = 4, 174 -> 144.  The local operator
+// without the loops: R = 3, 128^3 118 -> 113.
+template <typename T, int R, bool LOCAL>
 __device__ __forceinline__ void face_body(
     long long e, const double2* __restrict__ gin, double2* __restrict__ gout, double2* __restrict__ facc,
     double2* __restrict__ aux_out, const typename cpx<T>::t* __restrict__ yin,
@@ -521,25 +525,35 @@ __device__ __forceinline__ void face_body(
     t1 = (int)((q / n2) % n1);
     l = (int)(q / ((long long)n1 * n2));
   }
-  const int K = 2 * w + 1;
   double sr = 0, si = 0;
-  const int j1lo = max(0, t1 - w), j1hi = min(n1 - 1, t1 + w);
-  const int j2lo = max(0, t2 - w), j2hi = min(n2 - 1, t2 + w);
-  for (int lp = 0; lp < R; ++lp) {
-    const double2* kl = ker + ((long long)(l * R + lp)) * K * K;
-    for (int j1 = j1lo; j1 <= j1hi; ++j1) {
-      const double2* krow = kl + (long long)(t1 - j1 + w) * K;
-      for (int j2 = j2lo; j2 <= j2hi; ++j2) {
-        const double2 kv = krow[t2 - j2 + w];
-        double2 v;
-        if (first) {
-          v = gin[g.face_off[f] + (((long long)lp * n1 + j1) * n2 + j2) * B + b];
-        } else {
-          const auto yv = yin[face_point(g, f, lp, j1, j2) * B + b];
-          v = make_double2((double)yv.x, (double)yv.y);
+  if (LOCAL) {
+#pragma unroll
+    for (int lp = 0; lp < R; ++lp) {
+      const double2 kv = ker[l * R + lp], v = gin[g.face_off[f] + (((long long)lp * n1 + t1) * n2 + t2) * B + b];
+      sr += kv.x * v.x - kv.y * v.y;
+      si += kv.x * v.y + kv.y * v.x;
+    }
+  } else {
+    const int K = 2 * w + 1;
+    const int j1lo = max(0, t1 - w), j1hi = min(n1 - 1, t1 + w);
+    const int j2lo = max(0, t2 - w), j2hi = min(n2 - 1, t2 + w);
+    for (int lp = 0; lp < R; ++lp) {
+      const double2* kl = ker + ((long long)(l * R + lp)) * K * K;
+      for (int j1 = j1lo; j1 <= j1hi; ++j1) {
+        const double2* krow = kl + (long long)(t1 - j1 + w) * K;
+#pragma unroll 4
+        for (int j2 = j2lo; j2 <= j2hi; ++j2) {
+          const double2 kv = krow[t2 - j2 + w];
+          double2 v;
+          if (first) {
+            v = gin[g.face_off[f] + (((long long)lp * n1 + j1) * n2 + j2) * B + b];
+          } else {
+            const auto yv = yin[face_point(g, f, lp, j1, j2) * B + b];
+            v = make_double2((double)yv.x, (double)yv.y);
+          }
+          sr += kv.x * v.x - kv.y * v.y;
+          si += kv.x * v.y + kv.y * v.x;
         }
-        sr += kv.x * v.x - kv.y * v.y;
-        si += kv.x * v.y + kv.y * v.x;
       }
     }
   }
@@ -577,7 +591,7 @@ __global__ void __launch_bounds__(kBlock) face_kernel(
     double2* __restrict__ aux_out, const typename cpx<T>::t* __restrict__ yin,
     const double2* __restrict__ ker, LocalBlock a, Geometry g, int w, double coef, int mode,
     int first) {
-  face_body<T, R>((long long)blockIdx.x * blockDim.x + threadIdx.x, gin, gout, facc, aux_out, yin, ker, a, g, w,
+  face_body<T, R, false>((long long)blockIdx.x * blockDim.x + threadIdx.x, gin, gout, facc, aux_out, yin, ker, a, g, w,
                   coef, mode, first);
 }
 
@@ -778,7 +792,7 @@ __global__ void __launch_bounds__(kBlock) stage_face_kernel(
     stage_body<T, R, PER>((long long)blockIdx.x * blockDim.x + threadIdx.x, yin, yout, acc, state, V, fsrc, nullptr,
                           point_gamma, g, sc, coef, mode);
   else
-    face_body<T, R>((long long)(blockIdx.x - nsb) * blockDim.x + threadIdx.x, gin, gout, facc, aux_out, yin, ker, a,
+    face_body<T, R, true>((long long)(blockIdx.x - nsb) * blockDim.x + threadIdx.x, gin, gout, facc, aux_out, yin, ker, a,
                     g, w, coef, fmode, 1);
 }
 
@@ -796,7 +810,7 @@ __global__ void __launch_bounds__(tiled_block<T>(R), 4) stage_face_tiled_kernel(
     stage_tiled_body<T, R, kSrcFaces>(xcd_tile(blockIdx.x, tg), tg, yin, yout, acc, state, V, fsrc, g, sc, coef, mode,
                                       lds);
   else
-    face_body<T, R>((long long)(blockIdx.x - nsb) * blockDim.x + threadIdx.x, gin, gout, facc, aux_out, yin, ker, a,
+    face_body<T, R, true>((long long)(blockIdx.x - nsb) * blockDim.x + threadIdx.x, gin, gout, facc, aux_out, yin, ker, a,
                     g, w, coef, fmode, 1);
 }
 
