@@ -13,8 +13,8 @@
 //     columns), TY rows in y and TZ planes in z, and loads one halo row/plane
 //     per fused stage on each side;
 //   * one wavefront per y row, two consecutive x columns per lane; rows are
-//     published in LDS as [column parity][1 + lane] with a zero guard cell at
-//     each end (conflict-free, branch-free x neighbours);
+//     published in LDS as [column parity][lane] for the y neighbours, the x
+//     neighbours come by lane shifts;
 //   * the workgroup marches z: when plane zi is loaded, stage k works on plane
 //     zi - k with its input's below/centre planes in registers, the plane above
 //     being the previous stage's fresh output; a factor's input at the plane
@@ -695,7 +695,7 @@ __global__ void __launch_bounds__(64 * (kTY2 + 2 * kHalo2)) fused2_batch_kernel(
 }
 
 // ---------------------------------------------------------------------------
-// One-pass step: all four Horner stages in one z-marching sweep, so the
+// One-pass step: all four stages in one z-marching sweep, so the
 // state, the potential and the result cross HBM once per step (40 B per
 // point at complex128).  The tile is the whole row (nx <= 128) by TY rows by
 // TZ planes, with four-deep halos in y and z; stage k is computed on rows
