@@ -16,13 +16,14 @@
 //   dJ/dV_p += dt sum_{j+m<=3} j! m! / (j+m+1)! Im(conj(y_j[p]) z_m[p]).
 //
 // Checkpoints every `stride` steps (default ceil(sqrt(n))), taken during a
-// forward sweep on the fastest available path; each segment is recomputed
+// forward sweep on the fastest available path up to the last segment, whose own
+// run ends at psi_N; each segment is run once more
 // once, keeping every step's state and its intermediates (the state between
 // the step's two factors and their stage-1 outputs where the two-stage fused
 // kernels apply, else the staged kernels' stage vectors), then walked backwards
 // with one adjoint step per step; the fused adjoint step adds its part of the
 // potential gradient itself.  With
-// stride >= n there is one segment, kept whole: its recompute is the forward
+// stride >= n there is one segment, kept whole: its run is the forward
 // run (4 + 3 psi-sized vectors per step in memory, no separate sweep).
 #include <hip/hip_runtime.h>
 
@@ -254,28 +255,32 @@ abc_status run_adjoint(const abc_launch& L, const abc_launch& La, const abc_scra
     return launch_step_staged(L, S, yout, fout, V, 1, st, nullptr, &kz[3 * (size_t)i], yin, fin);
   };
 
-  // forward sweep with checkpoints; with one segment (stride >= n: every
-  // state and stage vector kept) the segment's own recompute below is the
-  // forward run, and no separate sweep is made
+  // segment c from its checkpoint, keeping each step's state and stage vectors,
+  // every step out of place; its end state goes to X
+  auto seg_z = [&](int c, int i) { return i ? seg[i] : ckp[c]; };
+  auto run_segment = [&](int c) {
+    const int len = std::min(stride, N - c * stride);
+    hipError_t e = hipSuccess;
+    for (int i = 0; i < len && e == hipSuccess; ++i) {
+      double2* next = i + 1 < len ? seg[i + 1] : X;
+      double2* nextf = i + 1 < len ? segf[i + 1] : fX;
+      e = step_keeping(i, seg_z(c, i), nf ? (i ? segf[i] : ckf[c]) : nullptr, next, nf ? nextf : nullptr);
+    }
+    return e;
+  };
+  // forward sweep with checkpoints up to the last segment, whose kept run is the
+  // forward run (with stride >= n that is the only segment: no sweep).  96^3,
+  // 48 steps: 5890 -> 5480 us
   ABC_TRY(hipMemcpyAsync(X, a.psi0, pb, hipMemcpyDeviceToDevice, st));
   if (nf) ABC_TRY(hipMemsetAsync(fX, 0, nf * sizeof(double2), st));
-  const bool single = nck == 1;
-  if (single) {
-    ABC_TRY(hipMemcpyAsync(ckp[0], X, pb, hipMemcpyDeviceToDevice, st));
-    if (nf) ABC_TRY(hipMemcpyAsync(ckf[0], fX, nf * sizeof(double2), hipMemcpyDeviceToDevice, st));
-    ABC_TRY(hipMemcpyAsync(seg[0], ckp[0], pb, hipMemcpyDeviceToDevice, st));
-    if (nf) ABC_TRY(hipMemcpyAsync(segf[0], ckf[0], nf * sizeof(double2), hipMemcpyDeviceToDevice, st));
-    for (int i = 0; i < N; ++i) {
-      double2* next = i + 1 < N ? seg[i + 1] : X;
-      double2* nextf = i + 1 < N ? segf[i + 1] : fX;
-      ABC_TRY(step_keeping(i, seg[i], nf ? segf[i] : nullptr, next, nf ? nextf : nullptr));
-    }
-  }
-  for (int c = 0; c < nck && !single; ++c) {
+  for (int c = 0; c < nck; ++c) {
     ABC_TRY(hipMemcpyAsync(ckp[c], X, pb, hipMemcpyDeviceToDevice, st));
     if (nf) ABC_TRY(hipMemcpyAsync(ckf[c], fX, nf * sizeof(double2), hipMemcpyDeviceToDevice, st));
-    const int k = std::min(stride, N - c * stride);
-    ABC_TRY(a.use_fused ? launch_step_fused(L, S, X, aux, V, k, st) : launch_step_staged(L, S, X, aux, V, k, st));
+    if (c + 1 < nck)
+      ABC_TRY(a.use_fused ? launch_step_fused(L, S, X, aux, V, stride, st)
+                          : launch_step_staged(L, S, X, aux, V, stride, st));
+    else
+      ABC_TRY(run_segment(c));
   }
   // objective at psi_N; the adjoint aux starts at zero
   ABC_TRY(objective(L, X, V, a.objective, lam, a.grad_V, partial, Jd, st));
@@ -287,29 +292,20 @@ abc_status run_adjoint(const abc_launch& L, const abc_launch& La, const abc_scra
   double2* lcur = lam;
   double2* lnext = y0;
   for (int c = nck - 1; c >= 0; --c) {
-    const int s0 = c * stride, len = std::min(stride, N - s0);
-    // recompute the segment, keeping each step's state and stage vectors
-    // (already there with one segment)
-    if (!single) ABC_TRY(hipMemcpyAsync(seg[0], ckp[c], pb, hipMemcpyDeviceToDevice, st));
-    if (nf && !single) ABC_TRY(hipMemcpyAsync(segf[0], ckf[c], nf * sizeof(double2), hipMemcpyDeviceToDevice, st));
-    for (int i = 0; i < len && !single; ++i) {
-      // one step from seg[i] (and segf[i]) into the next slot, out of place
-      double2* next = i + 1 < len ? seg[i + 1] : X;
-      double2* nextf = i + 1 < len ? segf[i + 1] : fX;
-      ABC_TRY(step_keeping(i, seg[i], nf ? segf[i] : nullptr, next, nf ? nextf : nullptr));
-    }
+    const int len = std::min(stride, N - c * stride);
+    if (c + 1 < nck) ABC_TRY(run_segment(c));
     for (int i = len - 1; i >= 0; --i) {
       if (factored) {
         // adjoint step in place, which also adds its part of the V gradient
         double2* const t[2] = {static_cast<double2*>(kz[3 * (size_t)i]), static_cast<double2*>(kz[3 * (size_t)i + 1])};
-        ABC_TRY(launch_step_fused_grad(La, S, lcur, nf ? mu : nullptr, seg[i],
+        ABC_TRY(launch_step_fused_grad(La, S, lcur, nf ? mu : nullptr, seg_z(c, i),
                                        static_cast<double2*>(kz[3 * (size_t)i + 2]), t, V, a.grad_V, L.dt, st));
         continue;
       }
       // adjoint step from lcur into lnext (mu in place), keeping its stage vectors
       ABC_TRY(launch_step_staged(La, S, lnext, nf ? mu : nullptr, V, 1, st, nullptr, ky, lcur));
       vgrad_kernel<<<gb, kBlock, 0, st>>>(a.grad_V, lcur, static_cast<double2*>(ky[0]),
-                                            static_cast<double2*>(ky[1]), static_cast<double2*>(ky[2]), seg[i],
+                                            static_cast<double2*>(ky[1]), static_cast<double2*>(ky[2]), seg_z(c, i),
                                             static_cast<double2*>(kz[3 * i]), static_cast<double2*>(kz[3 * i + 1]),
                                             static_cast<double2*>(kz[3 * i + 2]), npl, L.dt);
       ABC_TRY(hipGetLastError());
