@@ -16,15 +16,14 @@
 //   dJ/dV_p += dt sum_{j+m<=3} j! m! / (j+m+1)! Im(conj(y_j[p]) z_m[p]).
 //
 // Checkpoints every `stride` steps (default ceil(sqrt(n))), taken during a
-// forward sweep on the fastest available path up to the last segment, whose own
-// run ends at psi_N; each segment is run once more
-// once, keeping every step's state and its intermediates (the state between
-// the step's two factors and their stage-1 outputs where the two-stage fused
-// kernels apply, else the staged kernels' stage vectors), then walked backwards
-// with one adjoint step per step; the fused adjoint step adds its part of the
-// potential gradient itself.  With
-// stride >= n there is one segment, kept whole: its run is the forward
-// run (4 + 3 psi-sized vectors per step in memory, no separate sweep).
+// forward sweep on the fastest available path up to the last segment; each
+// segment is run from its checkpoint, keeping every step's state and its
+// intermediates (the state between the step's two factors and their stage-1
+// outputs where the two-stage fused kernels apply, else the staged kernels'
+// stage vectors), then walked backwards with one adjoint step per step; the
+// fused adjoint step adds its part of the potential gradient itself.  The last
+// segment's run ends at psi_N; with stride >= n it is the only one and is the
+// forward run (4 + 3 psi-sized vectors per step in memory, no separate sweep).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
