@@ -711,7 +711,7 @@ __global__ void __launch_bounds__(64 * (kTY2 + 2 * kHalo2)) fused2_batch_kernel(
 constexpr int kHalo4 = 4;
 template <typename T> struct Tile4;
 template <> struct Tile4<double> { static constexpr int TY = 4, TZ = 16; };
-template <> struct Tile4<float> { static constexpr int TY = 8, TZ = 8; };  // TZ: or 2 TZ (pick_depth4)
+template <> struct Tile4<float> { static constexpr int TY = 8, TZ = 8; };  // TZ: 8, 16 or 24 (pick_depth4)
 
 template <typename T>
 __host__ __device__ constexpr int rows4() { return Tile4<T>::TY + 2 * kHalo4; }
@@ -1205,9 +1205,10 @@ double tile_rounds(long long tiles) {
 
 // planes per tile of the one-pass sweep for `count` boxes in a launch, and the
 // plane iterations its workgroups take one after the other.  complex64: 8 planes
-// give 128^3 its 256 tiles; many boxes fill the chip with 16 as well, which run
-// through 8 halo planes half as often (us/step, 96^3 x 32 first order
-// 428 -> 357, Dirichlet 324 -> 256, 512 x 512 x 128 first order 369 -> 305)
+// give 128^3 its 256 tiles; many boxes fill the chip with 16 or 24 as well, which
+// run through the 8 halo planes less often (us/step with 8, 16 and 24: 96^3 x 32
+// first order 428, 357, 332, no condition 324, 256, 237; 48^3 x 32 first order
+// 16 110, 24 99; 512 x 512 x 128 369, 304, 291)
 struct Depth4 {
   int tz;
   double iters;
@@ -1215,7 +1216,7 @@ struct Depth4 {
 Depth4 pick_depth4(bool c64, int order, int ny, int nz, long long count) {
   const int ty = c64 ? Tile4<float>::TY : Tile4<double>::TY, tz0 = c64 ? Tile4<float>::TZ : Tile4<double>::TZ;
   Depth4 best{0, 0};
-  for (int tz = tz0; tz <= 16; tz *= 2) {
+  for (int tz = tz0; tz <= (c64 ? 24 : 16); tz += 8) {
     if (tz > tz0 && order == ABC_FIRST && nz <= tz + kHalo4) break;  // one z face per tile
     const double it =
         tile_rounds(count * ((ny + ty - 1) / ty) * ((nz + tz - 1) / tz)) * (tz + 2 * kHalo4);
@@ -1555,8 +1556,11 @@ void launch4(abc_timer* tm, bool full, dim3 g, dim3 b, hipStream_t st, const typ
   constexpr bool DB = ORDER != 3 || sizeof(T) == 4;
   auto launch = [&](auto kernel) { abc_launch_kernel(tm, "fused_step", kernel, g, b, st, src, dst, V, a, fin, fout); };
   constexpr int TZ = Tile4<T>::TZ;
-  if (TZ < 16 && tz == 16) launch(full ? fused4_kernel<T, ORDER, true, DB, 16> : fused4_kernel<T, ORDER, false, DB, 16>);
-  else launch(full ? fused4_kernel<T, ORDER, true, DB, TZ> : fused4_kernel<T, ORDER, false, DB, TZ>);
+  if constexpr (TZ < 16) {
+    if (tz == 16) return launch(full ? fused4_kernel<T, ORDER, true, DB, 16> : fused4_kernel<T, ORDER, false, DB, 16>);
+    if (tz == 24) return launch(full ? fused4_kernel<T, ORDER, true, DB, 24> : fused4_kernel<T, ORDER, false, DB, 24>);
+  }
+  launch(full ? fused4_kernel<T, ORDER, true, DB, TZ> : fused4_kernel<T, ORDER, false, DB, TZ>);
 }
 
 template <typename T>

@@ -1,5 +1,5 @@
-"""The one-pass sweep at both tile depths that complex64 picks (16 planes for
-boxes with many tiles) and with the high x face inside a lane pair or between
+"""The one-pass sweep at the tile depths that complex64 picks (8 planes, 16 and
+24 for boxes with many tiles) and with the high x face inside a lane pair or between
 two (odd and even rows, full rows), against the oracle: ragged tiles in y and z,
 the shortest boxes that the first order takes.  Tolerances: 1e-12 (complex128)
 and 1e-5 (complex64) of the largest value, as for the other paths.
@@ -17,6 +17,7 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("order", ["first", "zeroth", "dirichlet"])
 @pytest.mark.parametrize("shape,dtype", [((13, 17, 9), "c64"), ((13, 18, 10), "c64"), ((21, 1021, 9), "c64"),
                                          ((26, 1021, 10), "c64"), ((33, 1017, 127), "c64"), ((26, 1021, 128), "c64"),
+                                         ((47, 1021, 9), "c64"), ((43, 1018, 127), "c64"), ((48, 1021, 128), "c64"),
                                          ((21, 13, 9), "c128"), ((22, 14, 10), "c128"), ((37, 15, 127), "c128"),
                                          ((22, 14, 128), "c128")])
 def test_onepass_tiles(shape, dtype, order):
