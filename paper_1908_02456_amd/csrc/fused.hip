@@ -70,8 +70,8 @@ struct FusedArgs {
 // the last-level cache it starts at the end that the first one wrote last, which
 // is still there: 256^3 c128 336 -> 320 us/step, c64 186 -> 175, 320^3 c128
 // 637 -> 609; 128^3, all of it in the cache, stays at 33.6.  One-pass launches
-// read more than they write and measured no gain from it (118 -> 118 at
-// 256x256x128, 30.2 -> 31.1 at 128^3 c64).
+// gain nothing from it (118 -> 118 at 256x256x128), and choosing the direction
+// costs them 0.3 us at their start (128^3 c64, no condition 19.4 -> 19.75).
 __device__ __forceinline__ int tile_of(int b, int ntiles, int per_xcd, int rev) {
   if (per_xcd) return (b & 7) * per_xcd + (rev ? per_xcd - 1 - (b >> 3) : b >> 3);
   return rev ? ntiles - 1 - b : b;
@@ -792,7 +792,8 @@ __global__ void __launch_bounds__(64 * rows4<T>()) fused4_kernel(const typename 
     fin += (long long)blockIdx.y * a.fstride;
     fout += (long long)blockIdx.y * a.fstride;
   }
-  const int tile = tile_of(blockIdx.x, a.ntiles, a.tiles_per_xcd, a.rev);
+  int tile = blockIdx.x;
+  if (a.tiles_per_xcd) tile = (blockIdx.x & 7) * a.tiles_per_xcd + (blockIdx.x >> 3);
   const int ty = tile % a.nty, tz = tile / a.nty;
   const int y0 = ty * TY, z0 = tz * TZ;
   const int nx = a.nx, ny = a.ny, nz = a.nz;
