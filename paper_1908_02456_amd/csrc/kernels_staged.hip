@@ -16,8 +16,9 @@
 #include <rocblas/rocblas.h>
 
 #include <algorithm>
-#include <functional>
 #include <cmath>
+#include <functional>
+#include <type_traits>
 
 #include "abc_internal.h"
 #include "device_util.h"
@@ -603,14 +604,17 @@ __global__ void __launch_bounds__(kBlock) face_kernel(
 // NW-th tap column: down a column, input row i meets the taps i .. i - 3, three
 // of which the row before has loaded already, so that 16 multiply-adds come
 // with two LDS reads, which are a group of four rows ahead.  The taps stand
-// between rows of zeros in place of range checks.  The waves' sums are combined
-// in LDS.
+// between rows of zeros, so that every read is in range; the products of a
+// group's rows beyond the window are left out (zero times an infinite input would
+// reach outputs that the window does not).  The waves' sums are combined in LDS.
 // w = 8 at 128^3, first order, complex128 / complex64, us/step with the sweep:
 // 135 / 118 with one output per lane, range checks and a launch of its own, now
 // 99 / 78; w = 2 104 / 87 -> 88 / 60, w = 15 261 / 245 -> 158 / 148.
 // The first order's local A E y term and the stage update follow as in
 // face_body.
 constexpr int kFT = 16;
+template <int V>
+using Int = std::integral_constant<int, V>;
 inline size_t face_window_lds(int w, int threads) {
   const int S = kFT + 2 * w, K = 2 * w + 1, I = (K + 6) & ~3;
   return (size_t)std::max((S + 3) * S + K * (I + 3), threads / 64 * kFT * kFT) * sizeof(double2);
@@ -710,7 +714,9 @@ __device__ __forceinline__ void face_window_body(
       for (int u = 0; u < 7; ++u) t[u] = tc[u];
 #pragma unroll
       for (int u = 0; u < 4; ++u) v[u] = ic[u * S];
-      for (int i = 0; i < I; i += 4) {
+      // the next group's reads in flight, the products of this group with lo <= row
+      // - output <= hi
+      auto group = [&](int i, auto lo, auto hi) __attribute__((always_inline)) {
         const int n = i + 4 < I ? i + 4 : i;
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
@@ -721,6 +727,7 @@ __device__ __forceinline__ void face_window_body(
         for (int u = 0; u < 4; ++u)
 #pragma unroll
           for (int j = 0; j < 4; ++j) {
+            if (u - j < decltype(lo)::value || u - j > decltype(hi)::value) continue;
             const double2 kv = t[3 + u - j];
             acc[j].x = fma(-kv.y, v[u].y, fma(kv.x, v[u].x, acc[j].x));
             acc[j].y = fma(kv.y, v[u].x, fma(kv.x, v[u].y, acc[j].y));
@@ -732,6 +739,17 @@ __device__ __forceinline__ void face_window_body(
           t[3 + u] = tn[u];
           v[u] = vn[u];
         }
+      };
+      // i + row - output is the tap's row, 0 .. K - 1: all of a group's but in the
+      // first and the last one (w even) or two (w odd)
+      const int mid = w & 1 ? K - 3 : K - 1;
+      group(0, Int<0>(), Int<3>());
+      for (int i = 4; i < mid; i += 4) group(i, Int<-3>(), Int<3>());
+      if (w & 1) {
+        group(mid, Int<-3>(), Int<2>());
+        group(mid + 4, Int<-3>(), Int<-2>());
+      } else {
+        group(mid, Int<-3>(), Int<0>());
       }
     }
   }

@@ -1,0 +1,57 @@
+"""How far one value that is not finite reaches in a step: exactly as far as the
+method's sums, element by element, as in the oracle.  A step that has diverged
+somewhere must not spoil points that the stencil and the face window do not
+connect with it, and an infinity must not become a NaN where nothing is added
+to it.
+"""
+import numpy as np
+import pytest
+import torch
+
+from oracle import integrate
+from paper_1908_02456_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+
+def _solver():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_1908_02456_amd.solver import Solver
+    return Solver
+
+
+def _finite(a):
+    return np.isfinite(a.real) & np.isfinite(a.imag)
+
+
+# window 2, 4, 8: the last group of taps holds one row beyond the window per
+# output; 3, 7, 15: the last two groups do
+@pytest.mark.parametrize("order", ["first", "zeroth"])
+@pytest.mark.parametrize("R,window", [(1, 2), (1, 3), (1, 4), (1, 7), (1, 8), (1, 15), (2, 3), (3, 4)])
+def test_window_reaches_no_further(R, window, order):
+    Solver = _solver()
+    n1 = 10 * window + 30
+    shape, h, dt = (n1, 18, 20), 0.25, 0.002
+    print("case: reach of a window", shape, "R", R, "w", window, order, flush=True)
+    st = integrate.make_setup(shape, h, dt, R, order, s0=1.5, s1=1.5, window=window)
+    psi0 = W.random_complex(shape, seed=81)
+    V = W.random_potential(shape, seed=82)
+    s = Solver(shape, h, dt, radius=R, order=order, s0=1.5, s1=1.5, window=window, path="staged")
+    aux = s.new_aux()
+    aux0 = None
+    if order == "first":
+        flat = np.zeros(s.aux_elems, dtype=np.complex128)
+        flat[(n1 // 2) * shape[1] + 9] = np.nan  # the x- face's outer layer, mid-way along z
+        aux0 = integrate.unpack_aux(st, flat)
+        aux[:flat.size] = torch.from_numpy(flat).cuda()
+    else:
+        psi0[n1 // 2, 9, 0] = np.nan
+    ref, ref_aux, _ = integrate.run(st, psi0, V, 1, aux0=aux0)
+    psi = torch.from_numpy(psi0).cuda()
+    s.step(psi, aux, torch.from_numpy(V).cuda(), 1)
+    assert not _finite(ref).all() and _finite(ref).any()
+    assert np.array_equal(_finite(psi.cpu().numpy()), _finite(ref))
+    if order == "first":
+        flat = integrate.pack_aux(st, ref_aux)
+        assert np.array_equal(_finite(aux.cpu().numpy()[:flat.size]), _finite(flat))
