@@ -403,8 +403,10 @@ __device__ __forceinline__ void stage_tiled_body(
         __builtin_amdgcn_sched_barrier(0);
       }
     }
-    hr += vv * c0.x;
-    hi += vv * c0.y;
+    if (V) {  // without a potential no zero times an infinite state
+      hr += vv * c0.x;
+      hi += vv * c0.y;
+    }
     if (SRC != kSrcNone) {
       if (SRC == kSrcFaces && fy && (z < R || z >= nz - R) && in) {
         const double2 t = src[g.face_off[z < R ? 4 : 5] + (long long)(z < R ? z : nz - 1 - z) * sz + pt];

@@ -55,3 +55,26 @@ def test_window_reaches_no_further(R, window, order):
     if order == "first":
         flat = integrate.pack_aux(st, ref_aux)
         assert np.array_equal(_finite(aux.cpu().numpy()[:flat.size]), _finite(flat))
+
+
+@pytest.mark.parametrize("dtype", ["c128", "c64"])
+@pytest.mark.parametrize("R", [1, 2, 3])
+def test_no_potential_keeps_infinities(R, dtype):
+    # one orbital (the tiled sweep) against the same state twice in a batch (the
+    # general sweep): infinite and NaN parts at the same points
+    Solver = _solver()
+    shape = (20, 21, 22)
+    print("case: infinity without a potential", shape, "R", R, dtype, flush=True)
+    psi0 = W.random_complex(shape, seed=83)
+    psi0[10, 10, 10] = complex(np.inf, 0.5)
+    out = []
+    for batch in (1, 2):
+        s = Solver(shape, 0.25, 0.002, radius=R, order="dirichlet", dtype=dtype, batch=batch, path="staged")
+        full = psi0 if batch == 1 else np.stack([psi0, psi0], axis=-1)
+        psi = torch.from_numpy(full).to(s.cdtype).cuda()
+        s.step(psi, s.new_aux(), None, 1)
+        psi = psi.cpu().numpy()
+        out.append(psi if batch == 1 else psi[..., 0])
+    for f in (np.isnan, np.isinf):
+        assert f(out[1].imag).any()
+        assert np.array_equal(f(out[0].real), f(out[1].real)) and np.array_equal(f(out[0].imag), f(out[1].imag))
