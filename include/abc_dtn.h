@@ -380,6 +380,11 @@ size_t abc_aux_elems(const abc_ctx* ctx);
  * which = 3: box-form sizes, two complex128: (n_Gamma, r), r the dimension
  *            the second order interpolates in (n_Gamma for the other
  *            orders), then (spectral bound of the boundary block, 0).
+ * which = 4: one complex128: (|S - S^T| / |S| in the Frobenius norm, 1 if the
+ *            steps read one triangle of the box-form matrix, else 0), S the
+ *            boundary block with its rows scaled to symmetry; the first is -1
+ *            where it was not measured (small or batched boxes, the second
+ *            order, the first at R > 1).
  * n = capacity in complex128 elements; returns EINVAL if too small. */
 abc_status abc_export(const abc_ctx* ctx, int which, void* host_out, size_t n);
 

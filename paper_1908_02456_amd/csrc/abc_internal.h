@@ -152,6 +152,10 @@ void box_half_plan(int n, std::vector<int2>& units, std::vector<int>& strip0, in
 // smallest n for which the half product is used
 int box_half_min();
 size_t box_half_scratch(int n, size_t nunit);  // elements of rowpart and colpart together
+// |S - S^T| / |S| (Frobenius) of S = diag(w) mat, and the most for which the
+// half product is used
+hipError_t box_asymmetry(const double2* mat, long long ld, int n, const double* w, double* out);
+double box_half_tolerance(int n);
 
 struct abc_launch {
   abc::Geometry g;

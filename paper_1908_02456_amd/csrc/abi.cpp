@@ -37,6 +37,7 @@ struct abc_ctx {
   int n_gamma = 0;
   int box_rank = 0;         // box form: dimension the second order interpolates in
   double box_bound = 0;    // box form: spectral bound of the boundary block
+  double box_asym = -1;    // box form: |S - S^T| / |S| of the (weighted) operator, where measured
   int use_fused = 0;
   double2* box_mat = nullptr;
   double2* box_q = nullptr;
@@ -74,6 +75,45 @@ abc_status dev_upload(abc_ctx* c, const E** ptr, const std::vector<E>& v) {
     return fail(ABC_EDEVICE, "hipMemcpy failed");
   *ptr = static_cast<const E*>(p);
   return ABC_OK;
+}
+
+// Box form, one orbital: the half product (box_half_kernel) where w_i B_ij is
+// symmetric, M = K(s0) itself, or B = s1 I - A K(s1)^{-1} with A diagonal (R = 1,
+// one entry per row), w = 1 / (i A_ii).  The symmetry is measured; beyond rounding,
+// or where the partial sums do not fit any more, the full product stays.
+void setup_box_half(abc_ctx* c, const abc::BoxCoupling& coupling) {
+  const abc_params& p = c->p;
+  const int n = c->n_gamma;
+  bool diag_a = !coupling.row.empty() && (int)coupling.col.size() == n;
+  for (int i = 0; diag_a && i < n; ++i) diag_a = coupling.row[i] == i && coupling.col[i] == i;
+  if (p.batch != 1 || n < box_half_min() || !(p.order == ABC_ZEROTH || diag_a)) return;
+  const size_t mark = c->allocations.size(), bytes = c->bytes;
+  BoxHalf bh{};
+  std::vector<int2> units;
+  std::vector<int> strip0;
+  box_half_plan(n, units, strip0, &bh.cols);
+  bh.nunit = (int)units.size();
+  void* part = nullptr;
+  bool ok = dev_alloc(c, &part, box_half_scratch(n, units.size()) * sizeof(double2)) == ABC_OK &&
+            dev_upload(c, &bh.strip0, strip0) == ABC_OK && dev_upload(c, &bh.units, units) == ABC_OK;
+  if (ok && diag_a) {
+    std::vector<double> w(coupling.val);
+    const double w0 = w[0];
+    for (double& v : w) v = w0 / v;
+    ok = dev_upload(c, &bh.w, w) == ABC_OK;
+  }
+  ok = ok && box_asymmetry(c->box_mat, abc::box_cols(p.order, n), n, bh.w, &c->box_asym) == hipSuccess &&
+       c->box_asym <= box_half_tolerance(n);
+  if (ok) {
+    bh.rowpart = static_cast<double2*>(part);
+    bh.colpart = bh.rowpart + (size_t)bh.nunit * 64;
+    c->L.box_half = bh;
+    return;
+  }
+  for (; c->allocations.size() > mark; c->allocations.pop_back()) (void)hipFree(c->allocations.back());
+  c->bytes = bytes;
+  (void)hipGetLastError();
+  g_last_error.clear();
 }
 
 abc_status check_params(const abc_params& p) {
@@ -234,11 +274,11 @@ abc_status abc_setup(const abc_params* pp, abc_ctx** out) {
     else
       rho = std::max(rho, c->face.symbol_norm) + std::sqrt(3.0) * c->face.coupling_norm;
   }
+  abc::BoxCoupling coupling;
   if (bc && p.form == ABC_FORM_BOX) {
     std::vector<int> glin;
     double bound = 0;
     abc::BoxReduced red;
-    abc::BoxCoupling coupling;
     st = abc::build_box_ops(p, &c->box_mat, &c->box_q, &c->n_gamma, glin, &bound, &c->box_rank,
                             p.batch == 1 ? &red : nullptr, &coupling, err);
     c->box_bound = bound;
@@ -281,31 +321,6 @@ abc_status abc_setup(const abc_params* pp, abc_ctx** out) {
          (st = dev_upload(c, &L.box_aval, coupling.val)) != ABC_OK)) {
       abc_destroy(c);
       return st;
-    }
-    // The operator's upper triangle is enough where w_i B_ij is symmetric:
-    // M = K(s0) itself; B = s1 I - A K(s1)^{-1} with A diagonal (R = 1, one
-    // entry per row), w = 1 / (i A_ii).
-    const bool diag_a = !coupling.row.empty() && (int)coupling.col.size() == c->n_gamma;
-    if (p.batch == 1 && c->n_gamma >= box_half_min() && (p.order == ABC_ZEROTH || diag_a)) {
-      BoxHalf& bh = L.box_half;
-      std::vector<int2> units;
-      std::vector<int> strip0;
-      box_half_plan(c->n_gamma, units, strip0, &bh.cols);
-      bh.nunit = (int)units.size();
-      void* part = nullptr;
-      if ((st = dev_upload(c, &bh.strip0, strip0)) == ABC_OK &&
-          (st = dev_alloc(c, &part, box_half_scratch(c->n_gamma, units.size()) * sizeof(double2))) == ABC_OK) {
-        bh.rowpart = static_cast<double2*>(part);
-        bh.colpart = bh.rowpart + (size_t)bh.nunit * 64;
-        if (diag_a) {
-          std::vector<double> w(coupling.val);
-          const double w0 = w[0];
-          for (double& v : w) v = w0 / v;
-          st = dev_upload(c, &bh.w, w);
-        }
-      }
-      if (st == ABC_OK) st = dev_upload(c, &bh.units, units);
-      if (st != ABC_OK) { abc_destroy(c); return st; }
     }
     // zeroth: M adds to H; first and second: the boundary block (B, or the
     // (f, g) block [[0, I], [B0, B1]]) beside H, coupled through blocks of
@@ -490,6 +505,7 @@ abc_status abc_setup(const abc_params* pp, abc_ctx** out) {
       if (st != ABC_OK) { abc_destroy(c); return st; }
     }
   }
+  if (c->box_mat) setup_box_half(c, coupling);
   *out = c;
   return ABC_OK;
 }
@@ -910,6 +926,12 @@ abc_status abc_export(const abc_ctx* c, int which, void* host_out, size_t n) {
     abc::cd* o = static_cast<abc::cd*>(host_out);
     o[0] = abc::cd((double)c->n_gamma, (double)c->box_rank);
     o[1] = abc::cd(c->box_bound, 0.0);
+    return ABC_OK;
+  }
+  if (which == 4) {
+    if (!c->box_mat) return fail(ABC_EINVAL, "no box-form matrix");
+    if (n < 1) return fail(ABC_EINVAL, "buffer too small");
+    static_cast<abc::cd*>(host_out)[0] = abc::cd(c->box_asym, c->L.box_half.units ? 1.0 : 0.0);
     return ABC_OK;
   }
   if (which == 2) {

@@ -19,6 +19,7 @@
 #include <cmath>
 #include <functional>
 #include <type_traits>
+#include <vector>
 
 #include "abc_internal.h"
 #include "device_util.h"
@@ -1468,6 +1469,10 @@ __global__ void __launch_bounds__(kBlock) box_gemv_rows_kernel(
 // 157 us.  Bound by the matrix stream: it needs two workgroups per compute unit
 // (128 VGPRs; at 154, one, 96 us).  Below kHalfMin the strips are too few (us
 // per step, zeroth: n = 2648 141 against 141, n = 3176 137 against 182).
+// The coefficients come from solves whose result is symmetric up to rounding
+// (0.1 to 1.1e-15 of the Frobenius norm, R = 1 to 3, h 0.05 to 1, s 0.01 to 100), so that
+// the step's operator is the exported one up to that: the setup measures it
+// (box_asym_kernel) and keeps the full product beyond box_half_tolerance.
 // ---------------------------------------------------------------------------
 constexpr int kHalfRows = 64, kHalfWaves = 8, kHalfRW = kHalfRows / kHalfWaves, kHalfColsMax = 448;
 constexpr int kHalfMin = 3000;
@@ -1539,6 +1544,44 @@ __global__ void __launch_bounds__(64 * kHalfWaves, 4) box_half_kernel(const doub
     }
     bh.colpart[(long long)u.x * n + j] = s;
   }
+}
+
+// Frobenius norms for the symmetry of S = diag(w) mat: per tile pair (blockIdx.y
+// <= blockIdx.x) |S_ij - S_ji|^2 and |S_ij|^2 over both tiles
+constexpr int kAsymT = 32;
+__global__ void __launch_bounds__(256) box_asym_kernel(const double2* __restrict__ mat, long long ld, int n,
+                                                       const double* __restrict__ w, double2* __restrict__ part) {
+  __shared__ double2 low[kAsymT][kAsymT + 1];
+  __shared__ double2 red[256];
+  if (blockIdx.y > blockIdx.x) return;
+  const int i0 = blockIdx.y * kAsymT, j0 = blockIdx.x * kAsymT, tx = threadIdx.x % kAsymT, ty = threadIdx.x / kAsymT;
+  for (int r = ty; r < kAsymT; r += 256 / kAsymT)
+    low[r][tx] = (j0 + r < n && i0 + tx < n) ? mat[(j0 + r) * ld + i0 + tx] : make_double2(0, 0);
+  __syncthreads();
+  double d2 = 0, s2 = 0;
+  for (int r = ty; r < kAsymT; r += 256 / kAsymT) {
+    const int i = i0 + r, j = j0 + tx;
+    if (i >= n || j >= n || i > j) continue;
+    const double wi = w ? w[i] : 1.0, wj = w ? w[j] : 1.0;
+    const double2 a = mat[i * ld + j], b = low[tx][r];
+    const double ax = wi * a.x, ay = wi * a.y, bx = wj * b.x, by = wj * b.y;
+    if (i == j) {
+      s2 += ax * ax + ay * ay;
+    } else {
+      s2 += (ax * ax + ay * ay) + (bx * bx + by * by);
+      d2 += 2 * ((ax - bx) * (ax - bx) + (ay - by) * (ay - by));
+    }
+  }
+  red[threadIdx.x] = make_double2(d2, s2);
+  __syncthreads();
+  for (int k = 128; k > 0; k >>= 1) {
+    if (threadIdx.x < k) {
+      red[threadIdx.x].x += red[threadIdx.x + k].x;
+      red[threadIdx.x].y += red[threadIdx.x + k].y;
+    }
+    __syncthreads();
+  }
+  if (threadIdx.x == 0) part[(long long)blockIdx.y * gridDim.x + blockIdx.x] = red[0];
 }
 
 // row i: its units' row sums and 1 / w_i times the column sums of the strips
@@ -3020,6 +3063,32 @@ void box_half_plan(int n, std::vector<int2>& units, std::vector<int>& strip0, in
     strip0.push_back((int)units.size());
   }
 }
+
+// |S - S^T| / |S| of S = diag(w) mat, Frobenius (w null: all 1)
+hipError_t box_asymmetry(const double2* mat, long long ld, int n, const double* w, double* out) {
+  const int t = (n + kAsymT - 1) / kAsymT;
+  std::vector<double2> host((size_t)t * t);
+  double2* part = nullptr;
+  hipError_t e = hipMalloc(reinterpret_cast<void**>(&part), host.size() * sizeof(double2));
+  if (e != hipSuccess) return e;
+  box_asym_kernel<<<dim3(t, t), 256>>>(mat, ld, n, w, part);
+  e = hipGetLastError();
+  if (e == hipSuccess) e = hipMemcpy(host.data(), part, host.size() * sizeof(double2), hipMemcpyDeviceToHost);
+  (void)hipFree(part);
+  if (e != hipSuccess) return e;
+  double d2 = 0, s2 = 0;
+  for (int i = 0; i < t; ++i)
+    for (int j = i; j < t; ++j) {
+      d2 += host[(size_t)i * t + j].x;
+      s2 += host[(size_t)i * t + j].y;
+    }
+  *out = std::sqrt(d2 / s2);
+  return hipSuccess;
+}
+
+// the most that taking one triangle for the other may change the operator, of
+// its norm: what the rounding of n-term sums changes a product by in the mean
+double box_half_tolerance(int n) { return std::sqrt((double)n) * 0x1p-53; }
 
 size_t box_half_scratch(int n, size_t nunit) {
   return nunit * kHalfRows + (size_t)((n + kHalfRows - 1) / kHalfRows) * n;
