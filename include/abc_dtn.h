@@ -260,11 +260,17 @@ abc_status abc_adjoint(abc_ctx* ctx, const void* psi0, const void* V,
  * limit on the tile depth (4, 8 or 16 z-planes per tile, as the box and order
  * allow; the depth taken under a limit follows from the tile count) on the
  * given buffers and keeps the fastest for later abc_step calls; *tz_out (may
- * be NULL) receives the limit (0 on the staged path, which has nothing to tune).  The
+ * be NULL) receives that limit, 4, 8 or 16 (0 on the staged path, which has
+ * nothing to tune); abc_tile_depth tells the depth.  The
  * state is restored afterwards; the call allocates temporary copies of psi
  * and aux and synchronises the stream. */
 abc_status abc_tune(abc_ctx* ctx, void* psi, void* aux, const void* V,
                     void* stream, int* tz_out);
+
+/* z-planes per tile of the sweep that abc_step launches, on any path; 0 where
+ * the sweep is not tiled (periodic boxes, orbital batches on the staged path)
+ * or ctx is NULL. */
+int abc_tile_depth(const abc_ctx* ctx);
 
 /* Batches of independent boxes (uneven sizes, mixed orders and precisions).
  * abc_setup_batch sets up n instances from ps[0..n-1] (each as abc_setup).
@@ -290,7 +296,8 @@ abc_status abc_tune_batch(abc_batch* b, void* const* psi, void* const* aux,
                           const void* const* V, void* stream);
 /* aux elements of instance i (as abc_aux_elems), 0 if out of range */
 size_t abc_batch_aux_elems(const abc_batch* b, int i);
-/* number of descriptor-driven launch groups, and the tile-depth limit of one */
+/* number of descriptor-driven launch groups, and the tile depth (z-planes) of
+ * one's launches */
 int abc_batch_launch_groups(const abc_batch* b);
 int abc_batch_tile_depth(const abc_batch* b, int group);
 void abc_destroy_batch(abc_batch* b);

@@ -27,7 +27,7 @@ EXPORTED = ["abc_params_default", "abc_setup", "abc_step", "abc_diagnostics", "a
             "abc_batch_tile_depth", "abc_destroy_batch", "abc_h2_objective",
             "abc_effective_potential", "abc_potential_iterations", "abc_potential_unconverged", "abc_state_save",
             "abc_state_load",
-            "abc_diagnostics_noalloc", "abc_step_monitored"]
+            "abc_diagnostics_noalloc", "abc_step_monitored", "abc_tile_depth"]
 
 
 class AbcParams(ctypes.Structure):
@@ -82,6 +82,8 @@ def load(path: str = LIB_PATH) -> ctypes.CDLL:
     lib.abc_adjoint.restype = ctypes.c_int
     lib.abc_tune.argtypes = [vp, vp, vp, vp, vp, ctypes.POINTER(ctypes.c_int)]
     lib.abc_tune.restype = ctypes.c_int
+    lib.abc_tile_depth.argtypes = [vp]
+    lib.abc_tile_depth.restype = ctypes.c_int
     lib.abc_setup_batch.argtypes = [P, ctypes.c_int, ctypes.POINTER(vp)]
     lib.abc_setup_batch.restype = ctypes.c_int
     lib.abc_step_batch.argtypes = [vp, vp, vp, vp, ctypes.c_int, ctypes.c_int, vp]

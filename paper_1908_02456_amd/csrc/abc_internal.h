@@ -289,6 +289,8 @@ hipError_t launch_step_staged(const abc_launch& L, const abc_scratch& S, void* p
                               const void* V, int n_steps, hipStream_t st, abc_timer* tm = nullptr,
                               void* const* keep = nullptr, const void* psi_in = nullptr,
                               const double2* aux_in = nullptr);
+// planes per tile of the staged path's sweep; 0 where it is not tiled
+int staged_tile_depth(const abc_launch& L);
 // One step (complex128) out of place on the two-stage kernels (L must satisfy
 // fused_supported): psi_mid receives the state between the step's two factors,
 // keep[0..1] their stage-1 outputs.

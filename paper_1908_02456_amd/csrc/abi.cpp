@@ -514,6 +514,12 @@ size_t abc_aux_elems(const abc_ctx* c) { return c ? c->aux_elems : 0; }
 
 size_t abc_device_bytes(const abc_ctx* c) { return c ? c->bytes : 0; }
 
+int abc_tile_depth(const abc_ctx* c) {
+  if (!c) return 0;
+  if (c->orb) return fused_tile_depth(c->orb->L1, c->orb->B);
+  return c->use_fused ? fused_tile_depth(c->L, 1) : staged_tile_depth(c->L);
+}
+
 int abc_path(const abc_ctx* c) {
   if (!c || !c->use_fused) return ABC_PATH_STAGED;
   return c->L.fused_stages == 4 ? ABC_PATH_ONEPASS : ABC_PATH_FUSED;
@@ -1162,7 +1168,7 @@ int abc_batch_launch_groups(const abc_batch* b) { return b ? (int)b->groups.size
 
 int abc_batch_tile_depth(const abc_batch* b, int group) {
   if (!b || group < 0 || group >= (int)b->groups.size()) return 0;
-  return b->groups[group].limit;
+  return b->groups[group].tz;
 }
 
 namespace {

@@ -30,6 +30,8 @@ struct FusedBox {
 };
 int fused_max_limit(int order, int nz);
 int fused_pick_depth(int order, int limit, const std::vector<FusedBox>& boxes);
+// planes per tile of the launches of a step on L's path, `orbitals` per launch
+int fused_tile_depth(const abc_launch& L, int orbitals);
 
 // Batched two-stage launch over boxes sharing (order, precision, tile depth).
 // fused_batch_build writes 2 descriptor sets (one per launch of a step) into

@@ -1408,6 +1408,11 @@ int fused_pick_depth(int order, int limit, const std::vector<FusedBox>& boxes) {
   return best;
 }
 
+int fused_tile_depth(const abc_launch& L, int orbitals) {
+  if (L.fused_stages == 2) return L.fused_tz;
+  return pick_depth4(L.dtype == ABC_C64, L.order, L.g.ny, L.g.nz, orbitals).tz;
+}
+
 bool fused_supported(const abc_params& p, std::string* why) {
   auto no = [&](const char* m) {
     if (why) *why = m;

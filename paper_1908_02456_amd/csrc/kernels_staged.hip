@@ -465,6 +465,13 @@ int tile_planes(const Geometry& g) {
   return best;
 }
 
+// one orbital, zero outside the box: the tiled sweep (32-bit offsets within a
+// plane)
+template <typename C>
+bool tiled_sweep(const abc_launch& L) {
+  return !L.periodic && L.g.batch == 1 && (long long)L.g.nx * L.g.ny * (long long)sizeof(C) < (1LL << 32) - 16;
+}
+
 inline TileGrid make_tile_grid(const Geometry& g, int TY, int tz) {
   TileGrid tg;
   tg.ntx = (g.nx + kTX - 1) / kTX;
@@ -2815,9 +2822,7 @@ hipError_t step_staged_t(const abc_launch& L, const abc_scratch& S, void* psi_v,
   const LocalBlock a = make_local(L.a_loc);
   const long long nel = g.npts * g.batch;
   const long long nface = g.face_off[6];
-  // one orbital, zero outside the box: the tiled sweep (32-bit offsets within
-  // a plane)
-  const bool tiled = !PER && g.batch == 1 && (long long)g.nx * g.ny * (long long)sizeof(C) < (1LL << 32) - 16;
+  const bool tiled = !PER && tiled_sweep<C>(L);
   const TileGrid tg = make_tile_grid(g, TileShape<T, R>::TY, tile_planes<T, R>(g));
   const unsigned ntile = (unsigned)(tg.ntx * tg.nty * tg.ntz);
   const bool zeroth = L.order == ABC_ZEROTH;
@@ -3101,6 +3106,16 @@ hipError_t launch_step_staged(const abc_launch& L, const abc_scratch& S, void* p
                               const double2* aux_in) {
   if (L.dtype == ABC_C64) return dispatch_step<float>(L, S, psi, aux, V, n_steps, st, tm, keep, psi_in, aux_in);
   return dispatch_step<double>(L, S, psi, aux, V, n_steps, st, tm, keep, psi_in, aux_in);
+}
+
+int staged_tile_depth(const abc_launch& L) {
+  const bool c64 = L.dtype == ABC_C64;
+  if (!(c64 ? tiled_sweep<float2>(L) : tiled_sweep<double2>(L))) return 0;
+  switch (L.g.R) {
+    case 1: return c64 ? tile_planes<float, 1>(L.g) : tile_planes<double, 1>(L.g);
+    case 2: return c64 ? tile_planes<float, 2>(L.g) : tile_planes<double, 2>(L.g);
+    default: return c64 ? tile_planes<float, 3>(L.g) : tile_planes<double, 3>(L.g);
+  }
 }
 
 hipError_t launch_diagnostics(const abc_launch& L, const abc_scratch& S, const void* psi, const double2* aux,

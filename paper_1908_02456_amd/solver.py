@@ -226,13 +226,17 @@ class Solver:
         return float(d[0 if objective == "prob" else 2].item())
 
     def tune(self, psi, aux=None, V=None, stream=None) -> int:
-        """Pick the fused path's tile depth by timing (state restored); returns it."""
+        """Pick the limit on the fused path's tile depth by timing (state restored); returns the limit."""
         self._check_psi(psi)
         vp = self._check_V(V)
         ap = self._check_aux(aux)
         tz = ctypes.c_int(0)
         _lib.check(self._lib.abc_tune(self._ctx, psi.data_ptr(), ap, vp, _stream_handle(stream), ctypes.byref(tz)))
         return tz.value
+
+    def tile_depth(self) -> int:
+        """z-planes per tile of the launches of a step; 0 where the sweep is not tiled."""
+        return int(self._lib.abc_tile_depth(self._ctx))
 
     def diagnostics(self, psi, aux=None, V=None, out: Optional[torch.Tensor] = None, stream=None):
         """Tensor of 3*batch+1 float64: norm, Lyapunov W, energy per orbital, interaction energy."""
@@ -385,6 +389,7 @@ class Batch:
         return torch.zeros(max(self.aux_elems[i], 1), dtype=torch.complex128, device=self.device)
 
     def groups(self):
+        """Tile depth (z-planes) of each launch group."""
         g = int(self._lib.abc_batch_launch_groups(self._b))
         return [int(self._lib.abc_batch_tile_depth(self._b, k)) for k in range(g)]
 
@@ -413,6 +418,7 @@ class Batch:
         _lib.check(self._lib.abc_step_batch(self._b, P, A, Vp, int(n_steps), flags, _stream_handle(stream)))
 
     def tune(self, psis, auxs=None, Vs=None, stream=None):
+        """Pick each group's limit on the tile depth by timing (states restored); returns the depths."""
         P, A, Vp = self._ptrs(psis, auxs, Vs)
         _lib.check(self._lib.abc_tune_batch(self._b, P, A, Vp, _stream_handle(stream)))
         return self.groups()
