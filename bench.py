@@ -116,15 +116,18 @@ def launch_step_share(label):
     return None
 
 
-def launch_io_bytes(label, n, R, csz, rsz, first=True):
+def launch_io_bytes(label, n, R, csz, rsz, first=True, factored=False):
     """Bytes a launch itself reads and writes once at n^3 (state csz,
     potential rsz, FP64 face aux 16 B): the implementation's own traffic,
-    which counts the intermediate stage arrays the method does not need."""
+    which counts the intermediate stage arrays the method does not need.
+    factored: the second half step reads nothing but its own input, as the
+    first one (the step as two quadratic factors, what the kernels do); else it
+    reads the step's initial state and aux as well (a Horner form)."""
     npts = n ** 3
     faces = 6 * R * n * n
     if label == "fused_step":
         return npts * (2 * csz + rsz) + (faces * 32 if first else 0)
-    if label == "fused2_half_a":                    # read psi, V, f; write u2 and its aux
+    if label == "fused2_half_a" or (factored and label == "fused2_half_b"):  # read psi, V, f; write psi and its aux
         return npts * (2 * csz + rsz) + (faces * 32 if first else 0)
     if label == "fused2_half_b":                    # read u2, psi, V, both aux; write psi', f'
         return npts * (3 * csz + rsz) + (faces * 48 if first else 0)
@@ -139,19 +142,25 @@ def launch_io_bytes(label, n, R, csz, rsz, first=True):
     return None
 
 
+def launch_row(label, ms, n, R, csz, rsz):
+    """Table entry of a launch that took ms, at the bytes that it moves itself."""
+    b = launch_io_bytes(label, n, R, csz, rsz, factored=True)
+    return {"launch": label, "ms": ms, "impl_bytes": b, "impl_GB/s": (b / (ms / 1e3) / 1e9) if (b and ms > 0) else None}
+
+
 def roofline(table, n, R, csz, rsz, ms_step, traffic, first=True):
     """Roofline of the dominant grid sweep: its algorithmic bytes (the method's
     bytes per update times the updates the launch performs) over its average
     duration, against the 8 TB/s HBM peak.  impl_frac prices the same launch
-    at its own I/O instead; traffic_ratio is the counted HBM bytes over the
-    algorithmic bytes."""
+    at its own I/O instead (the row's impl_bytes, where it has them); traffic_ratio
+    is the counted HBM bytes over the algorithmic bytes."""
     b_upd = method_bytes_per_update(n, R, csz, rsz, first)
     sweeps = [r for r in table if launch_step_share(r["launch"]) is not None and r["ms"] > 0]
     dom = max(sweeps or table, key=lambda r: r["ms"])
     share = launch_step_share(dom["launch"])
     alg = b_upd * n ** 3 * share if share else None
     achieved = alg / (dom["ms"] / 1e3) / 1e9 if alg else None
-    io = launch_io_bytes(dom["launch"], n, R, csz, rsz, first)
+    io = dom["impl_bytes"] if "impl_bytes" in dom else launch_io_bytes(dom["launch"], n, R, csz, rsz, first)
     step_alg = b_upd * n ** 3
     return {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
             "frac": achieved / HBM_PEAK_GBS if achieved else None,
@@ -777,11 +786,7 @@ def main():
     torch.cuda.synchronize()
     csz = 16 if args.dtype == "c128" else 8
     rsz = 8 if args.dtype == "c128" else 4
-    table = []
-    for label, lms in per_launch:
-        b = launch_io_bytes(label, wl.n, wl.radius, csz, rsz)
-        table.append({"launch": label, "ms": lms, "impl_bytes": b,
-                      "impl_GB/s": (b / (lms / 1e3) / 1e9) if (b and lms > 0) else None})
+    table = [launch_row(label, lms, wl.n, wl.radius, csz, rsz) for label, lms in per_launch]
     log("launches per step: " + ", ".join("%s %.2f us" % (r["launch"], r["ms"] * 1e3) for r in table))
     sweeps = [r["launch"] for r in table if launch_step_share(r["launch"]) is not None]
     dom_label = max((r for r in table if r["launch"] in sweeps), key=lambda r: r["ms"])["launch"] if sweeps else None
