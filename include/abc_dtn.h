@@ -245,9 +245,11 @@ enum { ABC_OBJ_PROB = 0, ABC_OBJ_ENERGY = 1 };
  * grad_V (device, float64 [z][y][x], caller-owned).  psi0 and V are device
  * buffers of the context's box (V may be NULL for V = 0).  Checkpoints every
  * ckpt_stride steps (<= 0: ceil(sqrt(n_steps))) during a forward sweep on
- * the context's path; each segment is recomputed once, keeping its states
- * and stage vectors.  Device memory for about n/stride + 4 stride + 8 states
- * is allocated and freed by the call, which synchronises the stream.  Supported: complex128, one orbital, no mean
+ * the context's path up to the last segment; each segment is run once from its
+ * checkpoint, keeping its states and stage vectors.  Device memory for
+ * n/stride + 4 stride + 1 states (4 more where the two-stage kernels do not
+ * cover the operators) is allocated and freed by the call, which synchronises the
+ * stream.  Supported: complex128, one orbital, no mean
  * field; Dirichlet and periodic boxes; face-form zeroth order (any R) and
  * first order (R = 1).  Others (the box form, the second order): ABC_ENOTSUP.  ABC_ENOMEM if the buffers do
  * not fit, ABC_EDEVICE on HIP failures. */

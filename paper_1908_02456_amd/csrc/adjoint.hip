@@ -23,7 +23,7 @@
 // stage vectors), then walked backwards with one adjoint step per step; the
 // fused adjoint step adds its part of the potential gradient itself.  The last
 // segment's run ends at psi_N; with stride >= n it is the only one and is the
-// forward run (4 + 3 psi-sized vectors per step in memory, no separate sweep).
+// forward run (a state and 3 vectors per step in memory, no separate sweep).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -200,10 +200,17 @@ abc_status run_adjoint(const abc_launch& L, const abc_launch& La, const abc_scra
   const size_t pb = np * sizeof(double2), fb = std::max<size_t>(nf, 1) * sizeof(double2);
   const size_t round = 256;
   const int nb = (int)((np + kBlock - 1) / kBlock);
-  // psi-sized: X, lam, y0, 3 adjoint stage vectors, checkpoints, segment
-  // states and 3 forward vectors per segment step
-  const size_t npsi = 6 + (size_t)nck + nseg + 3 * (size_t)nseg;
-  const size_t total = npsi * (pb + round) + (2 + (size_t)nck + nseg) * (fb + round) +
+  // a step that keeps its intermediates: the two-stage fused kernels (the state
+  // between the factors and their stage-1 outputs kept) wherever they cover
+  // the operators, else the staged kernels (sum form, z1 z2 z3 kept); the V
+  // gradient is formed to match
+  const bool factored = a.use_fused && !L.fused_shell && L.w == 0 && g.R == 1 && !L.periodic;
+  // psi-sized: X, lam, checkpoints, segment states (but the first, its
+  // checkpoint), 3 forward vectors per segment step and, on the staged kernels, y0
+  // and 3 adjoint stage vectors
+  const size_t nst = nseg > 0 ? nseg - 1 : 0;
+  const size_t npsi = 2 + (factored ? 0 : 4) + (size_t)nck + nst + 3 * (size_t)nseg;
+  const size_t total = npsi * (pb + round) + (2 + (size_t)nck + nst) * (fb + round) +
                        ((size_t)nb + 1) * sizeof(double) + 2 * round;
   Arena ar;
   hipError_t e = hipMalloc(&ar.base, total);
@@ -214,19 +221,19 @@ abc_status run_adjoint(const abc_launch& L, const abc_launch& La, const abc_scra
   ar.cap = total;
   double2* X = ar.take<double2>(pb);
   double2* lam = ar.take<double2>(pb);
-  double2* y0 = ar.take<double2>(pb);
-  void* ky[3];
-  for (int i = 0; i < 3; ++i) ky[i] = ar.take<double2>(pb);
+  double2* y0 = factored ? nullptr : ar.take<double2>(pb);
+  void* ky[3] = {nullptr, nullptr, nullptr};
+  for (int i = 0; i < 3 && !factored; ++i) ky[i] = ar.take<double2>(pb);
   std::vector<double2*> ckp(nck), seg(nseg);
   for (auto& q : ckp) q = ar.take<double2>(pb);
-  for (auto& q : seg) q = ar.take<double2>(pb);
+  for (int i = 1; i < nseg; ++i) seg[i] = ar.take<double2>(pb);
   std::vector<void*> kz(3 * (size_t)nseg);
   for (auto& q : kz) q = ar.take<double2>(pb);
   double2* fX = ar.take<double2>(fb);
   double2* mu = ar.take<double2>(fb);
   std::vector<double2*> ckf(nck), segf(nseg);
   for (auto& q : ckf) q = ar.take<double2>(fb);
-  for (auto& q : segf) q = ar.take<double2>(fb);
+  for (int i = 1; i < nseg; ++i) segf[i] = ar.take<double2>(fb);
   double* partial = ar.take<double>((size_t)nb * sizeof(double));
   double* Jd = ar.take<double>(sizeof(double));
   double2* aux = nf ? fX : nullptr;
@@ -241,11 +248,6 @@ abc_status run_adjoint(const abc_launch& L, const abc_launch& La, const abc_scra
     }                                                    \
   } while (0)
 
-  // a step that keeps its intermediates: the two-stage fused kernels (the state
-  // between the factors and their stage-1 outputs kept) wherever they cover
-  // the operators, else the staged kernels (sum form, z1 z2 z3 kept); the V
-  // gradient is formed to match
-  const bool factored = a.use_fused && !L.fused_shell && L.w == 0 && g.R == 1 && !L.periodic;
   auto step_keeping = [&](int i, const double2* yin, const double2* fin, double2* yout, double2* fout) {
     if (factored) {
       double2* const t[2] = {static_cast<double2*>(kz[3 * (size_t)i]), static_cast<double2*>(kz[3 * (size_t)i + 1])};
@@ -286,8 +288,9 @@ abc_status run_adjoint(const abc_launch& L, const abc_launch& La, const abc_scra
   if (nf) ABC_TRY(hipMemsetAsync(mu, 0, nf * sizeof(double2), st));
   const long long npl = (long long)np;
   const unsigned gb = (unsigned)((np + kBlock - 1) / kBlock);
-  // backward over segments; lambda alternates between lam and y0, so the
-  // value before each adjoint step stays where the V gradient reads it
+  // backward over segments; on the staged kernels lambda alternates between lam
+  // and y0, so the value before each adjoint step stays where the V gradient
+  // reads it
   double2* lcur = lam;
   double2* lnext = y0;
   for (int c = nck - 1; c >= 0; --c) {
