@@ -143,7 +143,8 @@ typedef struct {
   int pcg_maxit;        /* iteration cap per solve (>= 1)                   */
   int pcg_fixed;        /* 0: each solve reads its convergence flag on the
                            host after every iteration and stops there (the
-                           step synchronises its stream); k >= 1: each solve
+                           step waits on the host for its solves, and so for
+                           what was queued before them); k >= 1: each solve
                            issues exactly k iterations and reads nothing on
                            the host (iterations after convergence are
                            skipped on the device), so that abc_step can be
@@ -182,9 +183,9 @@ abc_status abc_setup(const abc_params* p, abc_ctx** out);
 
 /* Advance (psi, aux) by n_steps Taylor-4 steps in place.  psi, V, aux as
  * described above (aux may be NULL unless order is ABC_FIRST or ABC_SECOND).
- * No allocation, no host synchronisation, except with ABC_MF_SKYRME, whose
- * potential solves read their convergence flag on the host every 8
- * iterations. */
+ * No allocation, no host synchronisation, except with ABC_MF_SKYRME and
+ * pcg_fixed = 0, whose potential solves read their convergence flags on the
+ * host after every iteration. */
 abc_status abc_step(abc_ctx* ctx, void* psi, void* aux, const void* V,
                     int n_steps, void* stream);
 
@@ -327,8 +328,8 @@ abc_status abc_h2_objective(const abc_params* p, const double* s1, int count,
  * orbitals of |psi_j|^2, solved as in abc_step (the solves start from the
  * context's previous potentials).  psi, V (may be NULL) and out ([z][y][x],
  * the state's real type) are device buffers.  With pcg_fixed = 0 the call
- * synchronises the stream (the solves read their convergence flag on the
- * host).
+ * waits on the host for the solves, and so for what was queued before them
+ * (they read their convergence flags there); out follows in stream order.
  * ABC_ENOTSUP for other mean fields. */
 abc_status abc_effective_potential(abc_ctx* ctx, const void* psi, const void* V,
                                    void* out, void* stream);

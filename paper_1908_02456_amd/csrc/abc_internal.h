@@ -320,7 +320,7 @@ abc_status face_fft_setup(const abc::Geometry& g, int R, int w, const std::vecto
                           std::vector<void*>* allocs, size_t* bytes, std::string& err);
 
 // V + t0 rho + t3 rho^2 + W_Y + W_C for psi ([point][orbital], or orbital
-// arrays when soa) into veff; synchronises the stream during the solves
+// arrays when soa) into veff; waits on the host for the solves unless ps.fixed
 bool potential_needs_blas(const PotentialSolver& ps);
 hipError_t potential_warmup(PotentialSolver& ps);
 hipError_t skyrme_veff(PotentialSolver& ps, const void* psi, bool soa, int B, bool c64, const void* V, void* veff,

@@ -62,9 +62,10 @@ struct OrbitalBatch {
   void* soa[2] = {nullptr, nullptr};     // psi arrays [B][npts]: the state, and its other buffer
   double2* soa_f[2] = {nullptr, nullptr};  // aux arrays [B][nface], the same
   void* veff = nullptr;            // V + mean field (psi's real type), or null
-  // descriptors of the two-stage launches, one set per step-count parity,
-  // built on first use for a given potential buffer and reused after that
-  // (so a warmed-up step issues no copy and can be captured in a graph)
+  // descriptors of the two-stage launches, one set per step-count parity
+  // (alike: a step ends where it began), built on first use for a given
+  // potential buffer and reused after that (so a warmed-up step issues no copy
+  // and can be captured in a graph)
   void* desc_host = nullptr;       // pinned staging, two sets
   void* desc_dev = nullptr;        // two sets
   const void* desc_V[2] = {nullptr, nullptr};

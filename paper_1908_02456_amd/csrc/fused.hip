@@ -184,6 +184,10 @@ enum { kPlain = 0, kKeep = 1, kGrad = 2 };
 // output, so the gradient costs the reads of t and y and the update of gV
 // instead of three kept adjoint stages and a pass of its own (first order,
 // 96^3 x 48 steps with sqrt checkpoints: 8.6 to 5.9 ms with the depth rule).
+// The increment tau - a l is taken as a difference.  Carried as stage 1 formed it
+// instead: the same error but for a single step (80-bit reference, 14 x 15 x 16, dt
+// 1e-2 to 1e-6; one step's probability 8.3e-17 -> 7.5e-17 of its terms) and 14 % of
+// the time.
 template <typename C>
 struct Grad2 {
   const C* t;
@@ -706,7 +710,7 @@ __global__ void __launch_bounds__(64 * (kTY2 + 2 * kHalo2)) fused2_batch_kernel(
 // planes are published in LDS, level j (the output of stage j, level 0 =
 // psi) only on the rows stage j+1 reads, double-buffered (one barrier per
 // plane).  complex128: TY = 4, TZ = 16, 12 waves (about 160 VGPRs);
-// complex64: TY = 8, TZ = 8, 16 waves.
+// complex64: TY = 8, TZ = 8, 16 or 24 (pick_depth4), 16 waves.
 // ---------------------------------------------------------------------------
 constexpr int kHalo4 = 4;
 template <typename T> struct Tile4;
@@ -766,7 +770,11 @@ __global__ void __launch_bounds__(64 * rows4<T>()) fused4_kernel(const typename 
   // complex64: the z-face slots, which only their own thread reads, in
   // registers, and the 64 KB of LDS go to the second plane buffer (96^3 x 32
   // 532 -> 487 us/step); the x-face sources ready in the state's type (445 -> 428).
-  // complex128 has neither the registers nor the LDS for these
+  // complex128 has neither the registers nor the LDS for these.  The sources as
+  // FP32 neighbours against an FP64 product added to the stage's output: the x faces'
+  // rms error against 64 bits is 0.73 of that one's over 60 boxes of 24^3 to 128^3, 1 to
+  // 10 steps from zero auxiliary variables (whole state 1.00); one step from sources
+  // that outweigh the state 3e4 times, 1.4
   constexpr bool ZREG = sizeof(T) == 4;
   constexpr bool XE = FO && sizeof(T) == 4;
   // rows as [column parity][lane] (x neighbours come by DPP, so no guard
@@ -1517,7 +1525,10 @@ abc_status fused_prepare(const abc_params& p, abc_launch& L, std::vector<void*>*
   // with the staged path, w = 8 145 against 141 us per step, exact sections
   // 182 against 185.
   // Orbital batches and the mean field (orbitals as boxes of one launch):
-  // the one-pass sweep for complex64, two launches for complex128.
+  // the one-pass sweep for complex64, two launches for complex128 (two launches
+  // / one pass, us per step, first order: c64 24^3 x 2 17 / 25, 48^3 x 2 21 / 25, 32^3 x 8
+  // 24 / 25, 48^3 x 8 46 / 40, 61^3 x 8 58 / 39, 96^3 x 32 496 / 321; c128 24^3 x 2 20 / 45,
+  // 61^3 x 8 65 / 100, 96^3 x 32 620 / 803): small complex64 batches lose 5 to 8 us by it.
   const bool orbitals = p.batch > 1 || p.meanfield != ABC_MF_NONE;
   const bool large = (double)L.g.npts * (p.dtype == ABC_C64 ? 8 : 16) > 3e9;
   const bool auto4 = fused4_supported(p, nullptr) && !fused_shell_case(p) &&

@@ -398,7 +398,8 @@ __device__ __forceinline__ void stage_tiled_body(
       hi += off[k] * (((a0.y + a1.y) + (a2.y + a3.y)) + (a4.y + a5.y));
       // one k's LDS reads at a time, used up here: left to itself the compiler
       // moves the sum behind the branches below and holds all 4R values until
-      // then (143 registers against 107 at R = 3, complex128)
+      // then (R = 3, complex128: 137 to 161 registers, spilled at the bound of 128,
+      // against 78 to 97)
       if (R > 1) {
         asm volatile("" : "+v"(hr), "+v"(hi));
         __builtin_amdgcn_sched_barrier(0);
